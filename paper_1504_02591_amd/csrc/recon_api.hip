@@ -472,13 +472,27 @@ int log_constant(recon_plan_t* pl, int blocks) {
   return check_launch(pl, "log shift");
 }
 
+// Blocks that a z iteration keeps when it lets a block take several tiles (four per CU).  With the
+// size's tuned number of tiles per block at every batch, a 32^3 pass ran its z step in 4 blocks and a
+// 128^3 pass in 64: 40.6 and 59.5 us per launch, now 8.2 and 14.9 us (whole reconstructions: 32^3 594 ->
+// 465 us, 64^3 from the eq. (approx2) start 1415 -> 978, 128^3 survey 1048 -> 766).  512, 1024 and
+// 2048 blocks time the same there and at batches of 128^3 and 256^3 (within 1 %).
+constexpr long long kZBlocks = 1024;
+
 template <int N>
 struct SizeOps {
   static constexpr int WZ = wz<N>(), WY = wy<N>(), WX = wx<N>();
   static constexpr int TZ = ntz<N>(), TY = nty<N>(), TX = ntx<N>();
   static dim3 gz(const recon_plan_t* pl) { return dim3(N * (N / (2 * WZ)), pl->batch); }
+  // z tiles per block of the z iteration: up to the size's tuned number (ztpb), but no more than
+  // leaves kZBlocks blocks in the launch, so that a small grid's tiles spread over the chip instead of
+  // running one after another in a few blocks
   template <int MODE, int SPLIT = 0>
-  static dim3 gzi(const recon_plan_t* pl) { return dim3(ztiles<N>() / ztpb<N, MODE, SPLIT>(), pl->batch); }
+  static dim3 gzi(const recon_plan_t* pl) {
+    int tpb = ztpb<N, MODE, SPLIT>();
+    while (tpb > 1 && (long long)ztiles<N>() / tpb * pl->batch < kZBlocks) tpb /= 2;
+    return dim3(ztiles<N>() / tpb, pl->batch);
+  }
   static dim3 gy(const recon_plan_t* pl) { return dim3((N / 2 + 1) * (N / WY), pl->batch); }
   static dim3 gx(const recon_plan_t* pl) { return dim3((N / 2 + 1) * N / WX, pl->batch); }
 
