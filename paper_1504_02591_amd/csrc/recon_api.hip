@@ -42,10 +42,10 @@ struct Layout {
          sorted = 0, bcount = 0, bstart = 0, bcursor = 0, bsum = 0, bvalid = 0, slot = 0, stmp = 0, bhist = 0, status = 0,
          tpart = 0, zflag = 0, mflag = 0;
   // network buffers
-  size_t a1 = 0, a2 = 0, d1 = 0, d2 = 0, ybuf = 0, dybuf = 0, upbuf = 0, wk2t = 0, w3 = 0,
-         part_out = 0, part_w1 = 0, part_w2 = 0, g1 = 0, g2 = 0, g3 = 0, grad = 0, lossp = 0, losst = 0, dc = 0, uc = 0,
-         wf1 = 0, wf2 = 0, dh = 0, uh = 0;
-  long long nb_conv = 0, nb_w = 0, nb_loss = 0;
+  size_t a1 = 0, a2 = 0, d1 = 0, d2 = 0, ybuf = 0, dybuf = 0, upbuf = 0,
+         part_out = 0, part_w1 = 0, part_w2 = 0, gred = 0, grad = 0, lossp = 0, losst = 0, dc = 0, uc = 0,
+         wf1 = 0, wf2 = 0, wf2t = 0, dh = 0, uh = 0;
+  long long t_out = 0, t_w = 0, nb_out = 0, nb_w = 0, nb_loss = 0;   // backward tiles and blocks
   long long cnn_n = 0;
   long long nbins = 0, nscan = 0;
 };
@@ -139,8 +139,10 @@ Layout make_layout(const recon_params_t* p) {
     const int lv = cnn_levels(p->flags);
     const long long m = n >> lv, m3 = m * m * m;   // network grid
     L.cnn_n = m;
-    L.nb_conv = m3 / TPOS;
-    L.nb_w = (m / TY) * (m / TZ);
+    L.t_out = b * m3 / (FX * FY * FZ);
+    L.t_w = b * m3 / VCELLS;
+    L.nb_out = L.t_out < kBwdBlocks ? L.t_out : kBwdBlocks;
+    L.nb_w = L.t_w < kBwdBlocks ? L.t_w : kBwdBlocks;
     L.nb_loss = 1024;
     L.a1 = take(b * m3 * CH * 2);
     L.a2 = take(b * m3 * CH * 2);
@@ -161,16 +163,13 @@ Layout make_layout(const recon_params_t* p) {
       L.dh = take(b * h3 * 4);
       L.uh = take(b * h3 * 4);
     }
-    L.wk2t = take(CH * K2 * 2);
-    L.w3 = take(K2 * 4);
     L.wf1 = take(9 * 64 * 16);
     L.wf2 = take(9 * 2 * 64 * 16);
-    L.part_out = take((size_t)b * L.nb_conv * (K2 + 1) * 4);
-    L.part_w1 = take((size_t)b * L.nb_w * CH * (K1P + 1) * 4);
-    L.part_w2 = take((size_t)b * L.nb_w * CH * (K2 + 1) * 4);
-    L.g1 = take(CH * (K1P + 1) * 4);
-    L.g2 = take(CH * (K2 + 1) * 4);
-    L.g3 = take((K2 + 1) * 4);
+    L.wf2t = take(9 * 2 * 64 * 16);
+    L.part_out = take((size_t)L.nb_out * COL3 * 4);
+    L.part_w1 = take((size_t)L.nb_w * COL1 * 4);
+    L.part_w2 = take((size_t)L.nb_w * COL2 * 4);
+    L.gred = take((size_t)kRedSlices * NCOLS * 8);
     L.grad = take(NPARAM * 4);
     L.lossp = take(L.nb_loss * 8);
     L.losst = take(8);
@@ -285,12 +284,12 @@ struct recon_plan_s {
   const float* srt_pos = nullptr;
   long long srt_n = 0;
   const int64_t* srt_off = nullptr;
-  unsigned short *a1 = nullptr, *a2 = nullptr, *d1 = nullptr, *d2 = nullptr,
-                 *wk2t = nullptr;
-  float *ybuf = nullptr, *dybuf = nullptr, *upbuf = nullptr, *w3 = nullptr, *part_out = nullptr,
-        *part_w1 = nullptr, *part_w2 = nullptr, *g1 = nullptr, *g2 = nullptr, *g3 = nullptr, *gradbuf = nullptr,
+  unsigned short *a1 = nullptr, *a2 = nullptr, *d1 = nullptr, *d2 = nullptr;
+  float *ybuf = nullptr, *dybuf = nullptr, *upbuf = nullptr, *part_out = nullptr,
+        *part_w1 = nullptr, *part_w2 = nullptr, *gradbuf = nullptr,
         *dc = nullptr, *uc = nullptr, *dh = nullptr, *uh = nullptr;
-  uint4 *wf1 = nullptr, *wf2 = nullptr;
+  double* gred = nullptr;
+  uint4 *wf1 = nullptr, *wf2 = nullptr, *wf2t = nullptr;
   int cnn_n = 0;                 // network grid: n, or n/2 with RECON_CNN_HALF
   long long cnn_n3 = 0;
   double *lossp = nullptr, *losst = nullptr;
@@ -805,11 +804,9 @@ int prolong4_impl(recon_plan_t* pl, const float* coarse, float scale, float* fin
 int cnn_forward_impl(recon_plan_t* pl, const float* params, const float* delta, const float* up, float* out,
                      float scale) {
   using namespace recon::cnn;
-  const dim3 grid((unsigned)pl->L.nb_conv, pl->batch);
   const Geo3 g = cnn_geo(pl);
   PROF(pl, KP_CNN_FWD);
-  k_prep_weights<<<32, 256, 0, pl->stream>>>(params, pl->wk2t, pl->w3);
-  k_prep_frag<<<(27 * 64 + 255) / 256, 256, 0, pl->stream>>>(params, pl->wf1, pl->wf2);
+  k_prep_frag<<<(45 * 64 + 255) / 256, 256, 0, pl->stream>>>(params, pl->wf1, pl->wf2, pl->wf2t);
   const dim3 gridf((unsigned)(pl->cnn_n3 / (FX * FY * FZ)), pl->batch);
   k_conv_fwd<CIN, 1><<<gridf, 256, 0, pl->stream>>>(nullptr, delta, up, g, pl->wf1, params + OFF_B1, pl->a1);
   k_conv_fwd<CH, 0><<<gridf, 256, 0, pl->stream>>>(pl->a1, nullptr, nullptr, g, pl->wf2, params + OFF_B2, pl->a2);
@@ -940,6 +937,7 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
     pl->upbuf = (float*)(w + L.upbuf);
     pl->wf1 = (uint4*)(w + L.wf1);
     pl->wf2 = (uint4*)(w + L.wf2);
+    pl->wf2t = (uint4*)(w + L.wf2t);
     pl->cnn_n = (int)L.cnn_n;
     pl->cnn_n3 = L.cnn_n * L.cnn_n * L.cnn_n;
     if (params->flags & (RECON_CNN_HALF | RECON_CNN_QUARTER)) {
@@ -950,14 +948,10 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
       pl->dh = (float*)(w + L.dh);
       pl->uh = (float*)(w + L.uh);
     }
-    pl->wk2t = (unsigned short*)(w + L.wk2t);
-    pl->w3 = (float*)(w + L.w3);
     pl->part_out = (float*)(w + L.part_out);
     pl->part_w1 = (float*)(w + L.part_w1);
     pl->part_w2 = (float*)(w + L.part_w2);
-    pl->g1 = (float*)(w + L.g1);
-    pl->g2 = (float*)(w + L.g2);
-    pl->g3 = (float*)(w + L.g3);
+    pl->gred = (double*)(w + L.gred);
     pl->gradbuf = (float*)(w + L.grad);
     pl->lossp = (double*)(w + L.lossp);
     pl->losst = (double*)(w + L.losst);
@@ -1800,29 +1794,24 @@ int recon_cnn_train_step(recon_plan_t* pl, float* params, float* adam_m, float* 
   if (lr > 0.f && (!adam_m || !adam_v || step < 1)) return fail(pl, RECON_EINVAL, "Adam needs moments and step >= 1");
   const long long count = pl->cnn_n3 * pl->batch;
   RECON_TRY(cnn_forward_impl(pl, params, delta, u_p, pl->ybuf, 1.0f));
-  const dim3 grid((unsigned)pl->L.nb_conv, pl->batch);
-  const dim3 gridw((unsigned)pl->L.nb_w, pl->batch);
+  const dim3 gridf((unsigned)(pl->cnn_n3 / (FX * FY * FZ)), pl->batch);
+  const unsigned nbo = (unsigned)pl->L.nb_out, nbw = (unsigned)pl->L.nb_w;
   const Geo3 g = cnn_geo(pl);
   hipStream_t s = pl->stream;
   {
     PROF(pl, KP_CNN_BWD);
     k_loss<<<(unsigned)pl->L.nb_loss, 256, 0, s>>>(pl->ybuf, target_du, count, pl->dybuf, pl->lossp);
-    k_conv_out_bwd<<<grid, 256, 0, s>>>(pl->dybuf, pl->a2, g, pl->w3, pl->d2, pl->part_out);
-    k_wgrad16<CH, K2, 0><<<gridw, 256, 0, s>>>(pl->d2, pl->a1, nullptr, nullptr, g, pl->part_w2);
-    k_conv16<CH, K2, 0, 1><<<grid, 256, 0, s>>>(pl->d2, nullptr, nullptr, g, pl->wk2t, nullptr, pl->a1, pl->d1);
-    k_wgrad16<CIN, K1P, 1><<<gridw, 256, 0, s>>>(pl->d1, nullptr, delta, u_p, g, pl->part_w1);
-    const long long nbo = pl->L.nb_conv * pl->batch, nbw = pl->L.nb_w * pl->batch;
-    k_reduce_cols<<<(K2 + 1 + 255) / 256, 256, 0, s>>>(pl->part_out, nbo, K2 + 1, pl->g3);
-    k_reduce_cols<<<(CH * (K2 + 1) + 255) / 256, 256, 0, s>>>(pl->part_w2, nbw, CH * (K2 + 1), pl->g2);
-    k_reduce_cols<<<(CH * (K1P + 1) + 255) / 256, 256, 0, s>>>(pl->part_w1, nbw, CH * (K1P + 1), pl->g1);
+    k_conv_out_bwd<<<nbo, 256, 0, s>>>(pl->dybuf, pl->a2, g, (int)pl->L.t_out, params + OFF_W3, pl->d2, pl->part_out);
+    k_wgrad<CH, K2, 0><<<nbw, 256, 0, s>>>(pl->d2, pl->a1, nullptr, nullptr, g, (int)pl->L.t_w, pl->part_w2);
+    k_conv_fwd<CH, 0, 1><<<gridf, 256, 0, s>>>(pl->d2, nullptr, nullptr, g, pl->wf2t, nullptr, pl->d1, pl->a1);
+    k_wgrad<CIN, K1P, 1><<<nbw, 256, 0, s>>>(pl->d1, nullptr, delta, u_p, g, (int)pl->L.t_w, pl->part_w1);
+    k_reduce_parts<<<dim3(RB3 + RB2 + RB1 + 1, kRedSlices), 256, 0, s>>>(
+        pl->part_out, nbo, pl->part_w2, pl->part_w1, nbw, pl->gred, pl->lossp, (int)pl->L.nb_loss, pl->losst);
     float* grad = grad_out ? grad_out : pl->gradbuf;
-    k_assemble_grad<<<(NPARAM + 255) / 256, 256, 0, s>>>(pl->g1, pl->g2, pl->g3, grad);
-    k_reduce_loss<<<1, 256, 0, s>>>(pl->lossp, (int)pl->L.nb_loss, pl->losst);
-    if (lr > 0.f) {
-      const float c1 = (float)(1.0 - std::pow(0.9, step)), c2 = (float)(1.0 - std::pow(0.999, step));
-      k_adam<<<(NPARAM + 255) / 256, 256, 0, s>>>(params, adam_m, adam_v, grad, NPARAM, lr, 0.9f, 0.999f, 1e-8f,
-                                                  c1, c2);
-    }
+    const float c1 = lr > 0.f ? (float)(1.0 - std::pow(0.9, step)) : 1.f,
+                c2 = lr > 0.f ? (float)(1.0 - std::pow(0.999, step)) : 1.f;
+    k_grad_adam<<<(NPARAM + 63) / 64, 64, 0, s>>>(pl->gred, grad, params, adam_m, adam_v, lr, 0.9f, 0.999f, 1e-8f, c1,
+                                                  c2);
   }
   RECON_TRY(check_launch(pl, "network training step"));
   double lsum = 0.0;

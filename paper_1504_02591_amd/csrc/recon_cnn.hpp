@@ -10,13 +10,10 @@
 // Parameter vector (FP32, device): W1 [16][27][8], b1 [16], W2 [16][27][16], b2 [16],
 // W3 [1][27][16], b3 [1]; tap t = (dz+1)*9 + (dy+1)*3 + (dx+1), offset (dx, dy, dz).
 //
-// Forward convolutions (k_conv_fwd, k_conv_out_mfma) are implicit GEMMs on
-// v_mfma_f32_16x16x32_bf16 over 16 x 8 x 8 output tiles (see there).  The training
-// kernels (data gradient k_conv16, weight gradient k_wgrad16) use v_mfma_f32_16x16x16bf16_1k:
-// M = 16 output positions (one x row of a 16 x 4 x 4 output tile), N = 16 output channels,
-// K = 27 taps x C_in input channels in blocks of 16.  Operand layout of that instruction:
-// lane l holds A[l%16][4(l/16)+0..3], B[4(l/16)+0..3][l%16], and the result
-// D[4(l/16)+0..3][l%16].
+// The forward convolutions and the data gradient of layer 2 (k_conv_fwd, k_conv_out_mfma) are implicit
+// GEMMs on v_mfma_f32_16x16x32_bf16 over 16 x 8 x 8 output tiles (see there); the weight gradients
+// (k_wgrad) run on the same instruction with positions as K, the output layer's backward
+// (k_conv_out_bwd) on v_mfma_f32_16x16x4_f32.
 #pragma once
 
 #include "recon_kernels.hpp"
@@ -30,10 +27,6 @@ constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + CH * 27 * CIN, OFF_W2 = OFF_B1 + CH,
               OFF_W3 = OFF_B2 + CH, OFF_B3 = OFF_W3 + 27 * CH, NPARAM = OFF_B3 + 1;
 constexpr int K1 = 27 * CIN, K1P = 224;      // layer-1 K padded to a multiple of 16
 constexpr int K2 = 27 * CH;                  // 432
-// output tile: 16 (x) by 4 (y) by 4 (z) positions, halo tile 18 x 6 x 6 cells
-constexpr int TX = 16, TY = 4, TZ = 4, HX = TX + 2, HY = TY + 2, HZ = TZ + 2, HCELLS = HX * HY * HZ;
-constexpr int TPOS = TX * TY * TZ;   // 256
-
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -49,111 +42,6 @@ struct Geo3 {
   float hs;
   float ds[3];
 };
-
-// Tile origin of this block: blockIdx.x runs over (x tiles, y tiles, z tiles), blockIdx.y = realisation.
-__device__ __forceinline__ void tile_origin(int n, int& x0, int& y0, int& z0) {
-  const int ntx = n / TX, nty = n / TY;
-  const int t = blockIdx.x;
-  x0 = (t % ntx) * TX;
-  y0 = ((t / ntx) % nty) * TY;
-  z0 = (t / (ntx * nty)) * TZ;
-}
-
-__device__ __forceinline__ long long halo_cell_global(int n, int x0, int y0, int z0, int hc) {
-  const int hx = hc % HX, hy = (hc / HX) % HY, hz = hc / (HX * HY);
-  const long long x = (x0 - 1 + hx) & (n - 1), y = (y0 - 1 + hy) & (n - 1), z = (z0 - 1 + hz) & (n - 1);
-  return (z * n + y) * n + x;
-}
-
-// Stage the halo tile of a channels-last bf16 tensor with C channels into LDS.
-template <int C>
-__device__ __forceinline__ void stage_bf16(unsigned short* tile, const unsigned short* __restrict__ src, int n, int x0,
-                                           int y0, int z0) {
-  constexpr int CH4 = C / 4;
-  for (int e = threadIdx.x; e < HCELLS * CH4; e += 256) {
-    const int hc = e / CH4, q = e % CH4;
-    const long long g = halo_cell_global(n, x0, y0, z0, hc);
-    *(uint2*)(tile + hc * C + 4 * q) = *(const uint2*)(src + g * C + 4 * q);
-  }
-}
-
-// Stage the assembled 8-channel input x0 = [delta, S_U u_p, r_hat, 0, 0, 0].
-__device__ __forceinline__ void stage_x0(unsigned short* tile, const float* __restrict__ delta,
-                                         const float* __restrict__ up, const Geo3& g, int x0, int y0, int z0) {
-  for (int hc = threadIdx.x; hc < HCELLS; hc += 256) {
-    const int hx = hc % HX, hy = (hc / HX) % HY, hz = hc / (HX * HY);
-    const int x = (x0 - 1 + hx) & (g.n - 1), y = (y0 - 1 + hy) & (g.n - 1), z = (z0 - 1 + hz) & (g.n - 1);
-    const long long c = ((long long)z * g.n + y) * g.n + x;
-    const float rx = fmaf(g.hs, (float)x, g.ds[0]), ry = fmaf(g.hs, (float)y, g.ds[1]),
-                rz = fmaf(g.hs, (float)z, g.ds[2]);
-    const float r2 = rx * rx + ry * ry + rz * rz;
-    const float ir = r2 > 0.f ? rsqrtf(r2) : 0.f;
-    unsigned short* t = tile + hc * CIN;
-    t[0] = to_bf16(delta[c]);
-    t[1] = to_bf16(S_U * up[c]);
-    t[2] = to_bf16(rx * ir);
-    t[3] = to_bf16(ry * ir);
-    t[4] = to_bf16(rz * ir);
-    t[5] = 0;
-    t[6] = 0;
-    t[7] = 0;
-  }
-}
-
-// Halo-tile cell of output row (zr, yr), position m, shifted by tap t.
-__device__ __forceinline__ int tap_cell(int zr, int yr, int m, int t) {
-  const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-  return ((zr + 1 + dz) * HY + (yr + 1 + dy)) * HX + (m + 1 + dx);
-}
-
-// Convolution with C input channels and 16 output channels on MFMA.
-//   SRC 0: input is a bf16 tensor [n^3][C];  SRC 1: input is x0 assembled from (delta, u_p) (C = 8).
-//   EPI 0: out = bf16(relu(acc + bias));     EPI 1: out = bf16(acc) where gate > 0, else 0.
-// wk: weights in MFMA layout [16 out][KP] bf16 (KP >= 27 C, zero padded).
-template <int C, int KP, int SRC, int EPI>
-__global__ void __launch_bounds__(256) k_conv16(const unsigned short* __restrict__ in, const float* __restrict__ delta,
-                                                const float* __restrict__ up, Geo3 g, const unsigned short* __restrict__ wk,
-                                                const float* __restrict__ bias, const unsigned short* __restrict__ gate,
-                                                unsigned short* __restrict__ out) {
-  constexpr int KB = KP / 16;
-  __shared__ unsigned short tile[HCELLS * C];
-  const long long n3 = (long long)g.n * g.n * g.n;
-  const int b = blockIdx.y;
-  int x0, y0, z0;
-  tile_origin(g.n, x0, y0, z0);
-  if (SRC == 0) stage_bf16<C>(tile, in + b * n3 * C, g.n, x0, y0, z0);
-  else stage_x0(tile, delta + b * n3, up + b * n3, g, x0, y0, z0);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = lane & 15, q = lane >> 4;
-  // B operands (weights) for every K block, kept in registers
-  s4 bw[KB];
-#pragma unroll
-  for (int kb = 0; kb < KB; ++kb) bw[kb] = *(const s4*)(wk + m * KP + kb * 16 + 4 * q);
-  __syncthreads();
-#pragma unroll
-  for (int row = 0; row < 4; ++row) {
-    const int rr = wave * 4 + row, zr = rr / TY, yr = rr % TY;
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      const int k = kb * 16 + 4 * q;
-      int t = k / C;
-      if (t > 26) t = 26;                            // padded K: weights are zero there
-      const s4 a = *(const s4*)(tile + tap_cell(zr, yr, m, t) * C + (k % C));
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bw[kb], acc, 0, 0, 0);
-    }
-    // lane holds D[pos = 4q + i][channel = m]
-    const long long rowbase = ((long long)(z0 + zr) * g.n + (y0 + yr)) * g.n + x0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const long long cell = b * n3 + rowbase + 4 * q + i;
-      float v = acc[i];
-      if (EPI == 0) v = fmaxf(v + bias[m], 0.f);
-      else v = from_bf16(gate[cell * CH + m]) > 0.f ? v : 0.f;
-      out[cell * CH + m] = to_bf16(v);
-    }
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Forward convolution on v_mfma_f32_16x16x32_bf16 (inference and the training forward).
@@ -178,31 +66,46 @@ __device__ __forceinline__ int frag_off(int c, int h) {
 }
 
 // Weight fragments: C = 16: wf[(g * 2 + h) * 64 + lane], C = 8: wf[g * 64 + lane], with
-// g = (dz+1)*3 + (dy+1); 8 bf16 per lane in the B layout above.
+// g = (dz+1)*3 + (dy+1); 8 bf16 per lane in the B layout above.  wf2t: layer 2 with its taps flipped and
+// its channels transposed (the data gradient of layer 2 as a forward convolution).
 __global__ void __launch_bounds__(256) k_prep_frag(const float* __restrict__ th, uint4* __restrict__ wf1,
-                                                   uint4* __restrict__ wf2) {
+                                                   uint4* __restrict__ wf2, uint4* __restrict__ wf2t) {
+  constexpr int F1 = 9 * 64, F2 = 9 * 2 * 64;
   const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= 9 * 64 + 9 * 2 * 64) return;
+  if (e >= F1 + 2 * F2) return;
   unsigned short v[8];
-  if (e < 9 * 64) {
+  if (e < F1) {
     const int g = e / 64, lane = e % 64, o = lane % 16, q = lane / 16;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int t = g * 3 + q;                     // dx = q - 1
       v[j] = q < 3 ? to_bf16(th[OFF_W1 + (o * 27 + t) * CIN + j]) : (unsigned short)0;
     }
-    wf1[e] = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
   } else {
-    const int f = e - 9 * 64, g = f / 128, h = (f / 64) % 2, lane = f % 64, o = lane % 16, q = lane / 16;
+    const bool flip = e >= F1 + F2;
+    const int f = e - F1 - (flip ? F2 : 0), g = f / 128, h = (f / 64) % 2, lane = f % 64, o = lane % 16, q = lane / 16;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int k = 8 * q + j, ch = k % 16;
-      const int dx = h == 0 ? (k < 16 ? -1 : 0) : 1;
+      const int t = g * 3 + (h == 0 ? (k < 16 ? 0 : 1) : 2);
       const bool zero = h == 1 && k >= 16;
-      v[j] = zero ? (unsigned short)0 : to_bf16(th[OFF_W2 + (o * 27 + g * 3 + dx + 1) * CH + ch]);
+      const int w = flip ? (ch * 27 + 26 - t) * CH + o : (o * 27 + t) * CH + ch;
+      v[j] = zero ? (unsigned short)0 : to_bf16(th[OFF_W2 + w]);
     }
-    wf2[f] = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
   }
+  uint4* dst = e < F1 ? wf1 + e : (e < F1 + F2 ? wf2 + (e - F1) : wf2t + (e - F1 - F2));
+  *dst = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+}
+
+// One cell of the assembled 8-channel input x0 = [delta, S_U u_p, r_hat, 0, 0, 0] (bf16) at node (x, y, z).
+__device__ __forceinline__ uint4 x0_cell(const Geo3& g, int x, int y, int z, float delta, float up) {
+  const float rx = fmaf(g.hs, (float)x, g.ds[0]), ry = fmaf(g.hs, (float)y, g.ds[1]),
+              rz = fmaf(g.hs, (float)z, g.ds[2]);
+  const float r2 = rx * rx + ry * ry + rz * rz;
+  const float ir = r2 > 0.f ? rsqrtf(r2) : 0.f;
+  const unsigned a0 = to_bf16(delta), a1 = to_bf16(S_U * up);
+  const unsigned a2 = to_bf16(rx * ir), a3 = to_bf16(ry * ir), a4 = to_bf16(rz * ir);
+  return make_uint4(a0 | (a1 << 16), a2 | (a3 << 16), a4, 0u);
 }
 
 // Stage the 18 x 10 x 10 halo of a channels-last bf16 tensor into LDS: every thread issues all of
@@ -230,12 +133,14 @@ __device__ __forceinline__ void stage_halo(unsigned char* lds, const unsigned sh
 }
 
 //   SRC 0: input is a bf16 tensor [n^3][C];  SRC 1: input is x0 assembled from (delta, u_p), C = 8.
-//   out = bf16(relu(acc + bias)), channels-last [n^3][16].
-template <int C, int SRC>
+//   EPI 0: out = bf16(relu(acc + bias));     EPI 1: out = bf16(acc) where gate > 0, else 0 (data gradient).
+//   out and gate: channels-last [n^3][16].
+template <int C, int SRC, int EPI = 0>
 __global__ void __launch_bounds__(256) k_conv_fwd(const unsigned short* __restrict__ in,
                                                      const float* __restrict__ delta, const float* __restrict__ up,
                                                      Geo3 g, const uint4* __restrict__ wf,
-                                                     const float* __restrict__ bias, unsigned short* __restrict__ out) {
+                                                     const float* __restrict__ bias, unsigned short* __restrict__ out,
+                                                     const unsigned short* __restrict__ gate = nullptr) {
   constexpr int NH = C == 16 ? 2 : 1;
   // halo of the input (bf16 channels) during the products, then the output tile (16 channels, bf16)
   constexpr int LDS_IN = GCELLS * C * 2, LDS_OUT = FX * FY * FZ * 32;
@@ -267,13 +172,7 @@ __global__ void __launch_bounds__(256) k_conv_fwd(const unsigned short* __restri
       if (c < GCELLS) {
         const int hx = c % GX, hy = (c / GX) % GY, hz = c / (GX * GY);
         const int x = (x0 - 1 + hx) & msk, y = (y0 - 1 + hy) & msk, z = (z0 - 1 + hz) & msk;
-        const float rx = fmaf(g.hs, (float)x, g.ds[0]), ry = fmaf(g.hs, (float)y, g.ds[1]),
-                    rz = fmaf(g.hs, (float)z, g.ds[2]);
-        const float r2 = rx * rx + ry * ry + rz * rz;
-        const float ir = r2 > 0.f ? rsqrtf(r2) : 0.f;
-        const unsigned a0 = to_bf16(dv[k]), a1 = to_bf16(S_U * uv[k]);
-        const unsigned a2 = to_bf16(rx * ir), a3 = to_bf16(ry * ir), a4 = to_bf16(rz * ir);
-        *(uint4*)(lds + c * 16) = make_uint4(a0 | (a1 << 16), a2 | (a3 << 16), a4, 0u);
+        *(uint4*)(lds + c * 16) = x0_cell(g, x, y, z, dv[k], uv[k]);
       }
     }
   }
@@ -325,7 +224,7 @@ __global__ void __launch_bounds__(256) k_conv_fwd(const unsigned short* __restri
   // epilogue: lane (m, q) holds channel m of cells 4q..4q+3 of each output row; channel pairs are
   // exchanged with the neighbouring lane and the packed words go to the output tile in LDS
   // ([cell][16 channels]), from which every lane stores whole 16-byte halves of cells
-  const float bm = bias[m];
+  const float bm = EPI == 0 ? bias[m] : 0.f;
   const bool even = (m & 1) == 0;
   __syncthreads();                                  // every wave is done with the halo
   unsigned* t32 = (unsigned*)lds;
@@ -335,7 +234,7 @@ __global__ void __launch_bounds__(256) k_conv_fwd(const unsigned short* __restri
     for (int oy = 0; oy < 4; ++oy) {
       unsigned mine[4], other[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) mine[i] = to_bf16(fmaxf(acc[oz][oy][i] + bm, 0.f));
+      for (int i = 0; i < 4; ++i) mine[i] = to_bf16(EPI == 0 ? fmaxf(acc[oz][oy][i] + bm, 0.f) : acc[oz][oy][i]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) other[i] = (unsigned)__shfl_xor((int)mine[i], 1);
       const int cell0 = ((wz0 + oz) * FY + (wy0 + oy)) * FX + 4 * q;
@@ -357,9 +256,17 @@ __global__ void __launch_bounds__(256) k_conv_fwd(const unsigned short* __restri
     const int e = threadIdx.x + k * 256;           // 16-byte half e % 2 of tile cell e / 2
     const int cell = e >> 1, lx = cell % FX, ly = (cell / FX) % FY, lz = cell / (FX * FY);
     const long long row = b * n3 + ((long long)(z0 + lz) * g.n + (y0 + ly)) * g.n + x0 + lx;
-    o128[row * 2 + (e & 1)] = t128[e];
+    uint4 v = t128[e];
+    if constexpr (EPI == 1) {
+      const uint4 gt = ((const uint4*)gate)[row * 2 + (e & 1)];
+      auto open = [](unsigned w, unsigned gw) {
+        return (from_bf16((unsigned short)(gw & 0xFFFFu)) > 0.f ? (w & 0xFFFFu) : 0u) |
+               (from_bf16((unsigned short)(gw >> 16)) > 0.f ? (w & 0xFFFF0000u) : 0u);
+      };
+      v = make_uint4(open(v.x, gt.x), open(v.y, gt.y), open(v.z, gt.z), open(v.w, gt.w));
+    }
+    o128[row * 2 + (e & 1)] = v;
   }
-
 }
 
 // Output layer (16 -> 1) on MFMA for the forward pass: with one output channel the N dimension of
@@ -424,194 +331,321 @@ __global__ void __launch_bounds__(256) k_loss(const float* __restrict__ y, const
   if (threadIdx.x == 0) partial[blockIdx.x] = t1;
 }
 
-// Output-layer backward: dpre2[p][i] = bf16((sum_t W3[t][i] dy[p - d_t]) * [a2[p][i] > 0]),
-// and per-block partials of dW3[t][i] = sum_p dy[p] a2[p + d_t][i] and db3 = sum_p dy[p].
+// ---------------------------------------------------------------------------
+// Backward of the training step.  Every kernel takes several tiles per block in a fixed order and leaves
+// one row of partial sums per block; k_reduce_parts adds the rows in FP64 in a fixed order, so a step
+// is deterministic for a given grid and batch.
+// ---------------------------------------------------------------------------
+constexpr int kBwdBlocks = 1024;   // most blocks (rows of partial sums) of a backward launch
+
+// Output-layer backward: d2[p][i] = bf16((sum_t W3[t][i] dy[p - d_t]) * [a2[p][i] > 0]),
+// and per-block partials of dW3[t][i] = sum_p dy[p - d_t] a2[p][i] (the same sum as over dy[p] a2[p + d_t]:
+// the grid is periodic) and db3 = sum_p dy[p].
+//
+// Both sums are contractions with FP32 operands (dy is never rounded) on v_mfma_f32_16x16x4_f32, tile
+// 16 x 8 x 8 cells, four waves of 16 rows: d2 with M = 16 cells of a row, N = 16 channels, K = 27 taps
+// padded to 28; dW3 with M = taps (two tiles), N = channels, K = 4 cells per instruction.  Only dy needs
+// a halo.  Operand layout: lane l holds A[l%16][l/16], B[l/16][l%16], D[4(l/16)+0..3][l%16].
+// 72 us on a 128^3 network grid (0.14 GB, 240 products of 32 cycles per wave and tile), against 200 us
+// with one FMA and two LDS reads per (tap, channel, cell).
 __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ dy, const unsigned short* __restrict__ a2,
-                                                      Geo3 g, const float* __restrict__ w3,
+                                                      Geo3 g, int tiles, const float* __restrict__ w3f,
                                                       unsigned short* __restrict__ dpre2, float* __restrict__ part) {
-  __shared__ unsigned short tile[HCELLS * CH];
-  __shared__ float dyt[HCELLS];
-  __shared__ float w[27 * CH];
+  constexpr int ROWW = 27 * CH + 1, CELLS = FX * FY * FZ;
+  __shared__ float dyt[GCELLS];
+  __shared__ __align__(16) unsigned short tile[CELLS * CH];   // a2, then d2 in place; at the end the wave sums
+  static_assert(sizeof(float) * 4 * ROWW <= sizeof(tile), "the wave sums reuse the tile");
   const long long n3 = (long long)g.n * g.n * g.n;
-  const int b = blockIdx.y;
-  int x0, y0, z0;
-  tile_origin(g.n, x0, y0, z0);
-  stage_bf16<CH>(tile, a2 + b * n3 * CH, g.n, x0, y0, z0);
-  for (int hc = threadIdx.x; hc < HCELLS; hc += 256) dyt[hc] = dy[b * n3 + halo_cell_global(g.n, x0, y0, z0, hc)];
-  for (int i = threadIdx.x; i < 27 * CH; i += 256) w[i] = w3[i];
+  const int n = g.n, msk = n - 1, nbx = n / FX, nby = n / FY, per = nbx * nby * (n / FZ);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, q = lane >> 4;
+  const int wy0 = 4 * (wave & 1), wz0 = 4 * (wave >> 1);
+  auto tap_off = [](int t) { return (t % 3 - 1) + ((t / 3) % 3 - 1) * GX + (t / 9 - 1) * GX * GY; };
+  float w[7];
+  int da[7], dt[2];
+#pragma unroll
+  for (int s = 0; s < 7; ++s) {
+    const int t = 4 * s + q;
+    w[s] = t < 27 ? from_bf16(to_bf16(w3f[t * CH + m])) : 0.f;
+    da[s] = m - tap_off(t < 27 ? t : 26);
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int t = 16 * a + m;
+    dt[a] = q - tap_off(t < 27 ? t : 26);                  // rows 27..31 of the product are not used
+  }
+  f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+  float bacc = 0.f;
+  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int b = t / per, tt = t % per;
+    const int x0 = (tt % nbx) * FX, y0 = ((tt / nbx) % nby) * FY, z0 = (tt / (nbx * nby)) * FZ;
+    constexpr int PD = (GCELLS + 255) / 256, PA = CELLS * 2 / 256;
+    float dv[PD];
+    uint4 av[PA];
+#pragma unroll
+    for (int k = 0; k < PD; ++k) {
+      const int c0 = threadIdx.x + k * 256, c = c0 < GCELLS ? c0 : GCELLS - 1;
+      const int hx = c % GX, hy = (c / GX) % GY, hz = c / (GX * GY);
+      dv[k] = dy[b * n3 + ((long long)((z0 - 1 + hz) & msk) * n + ((y0 - 1 + hy) & msk)) * n + ((x0 - 1 + hx) & msk)];
+    }
+    const uint4* a128 = (const uint4*)a2;
+#pragma unroll
+    for (int k = 0; k < PA; ++k) {
+      const int e = threadIdx.x + k * 256, cell = e >> 1;
+      const int lx = cell % FX, ly = (cell / FX) % FY, lz = cell / (FX * FY);
+      av[k] = a128[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)];
+    }
+    __syncthreads();                                       // the last tile's stores have left the tile
+#pragma unroll
+    for (int k = 0; k < PD; ++k)
+      if (threadIdx.x + k * 256 < GCELLS) dyt[threadIdx.x + k * 256] = dv[k];
+#pragma unroll
+    for (int k = 0; k < PA; ++k) ((uint4*)tile)[threadIdx.x + k * 256] = av[k];
+    __syncthreads();
+    for (int c = threadIdx.x; c < CELLS; c += 256)
+      bacc += dyt[((c / (FX * FY) + 1) * GY + (c / FX) % FY + 1) * GX + c % FX + 1];
+#pragma unroll 2
+    for (int row = 0; row < 16; ++row) {
+      const int lz = wz0 + (row >> 2), ly = wy0 + (row & 3);
+      const int hrow = ((lz + 1) * GY + ly + 1) * GX + 1;  // halo cell of the row's first cell
+      unsigned short* cells = tile + (lz * FY + ly) * FX * CH;
+      f4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 7; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + da[s]], w[s], d, 0, 0, 0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float bv = from_bf16(cells[(4 * k + q) * CH + m]);
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + 4 * k + dt[0]], bv, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + 4 * k + dt[1]], bv, acc[1], 0, 0, 0);
+      }
+      // the wave alone reads and writes this row: its reads above are issued before these writes
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        unsigned short* c = cells + (4 * q + i) * CH + m;
+        *c = from_bf16(*c) > 0.f ? to_bf16(d[i]) : (unsigned short)0;
+      }
+    }
+    __syncthreads();
+    uint4* o128 = (uint4*)dpre2;
+#pragma unroll
+    for (int k = 0; k < PA; ++k) {
+      const int e = threadIdx.x + k * 256, cell = e >> 1;
+      const int lx = cell % FX, ly = (cell / FX) % FY, lz = cell / (FX * FY);
+      o128[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)] = ((const uint4*)tile)[e];
+    }
+  }
   __syncthreads();
-  {
-    const int m = threadIdx.x % TX, yr = (threadIdx.x / TX) % TY, zr = threadIdx.x / (TX * TY);
-    float d[CH];
+  float* red = (float*)tile;                               // [4 waves][ROWW]
 #pragma unroll
-    for (int i = 0; i < CH; ++i) d[i] = 0.f;
-    for (int t = 0; t < 27; ++t) {
-      const float v = dyt[tap_cell(zr, yr, m, 26 - t)];      // dy(p - d_t)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int i = 0; i < CH; ++i) d[i] = fmaf(w[t * CH + i], v, d[i]);
+    for (int i = 0; i < 4; ++i) {
+      const int t = 16 * a + 4 * q + i;
+      if (t < 27) red[wave * ROWW + t * CH + m] = acc[a][i];
     }
-    const int hc = tap_cell(zr, yr, m, 13);
-    const long long cell = b * n3 + ((long long)(z0 + zr) * g.n + (y0 + yr)) * g.n + x0 + m;
 #pragma unroll
-    for (int i = 0; i < CH; ++i) dpre2[cell * CH + i] = to_bf16(from_bf16(tile[hc * CH + i]) > 0.f ? d[i] : 0.f);
-  }
-  // weight partials: entry e = t * 16 + i (432 entries) plus the bias (entry 432)
-  const long long blk = (long long)b * gridDim.x + blockIdx.x;
-  for (int e = threadIdx.x; e < 27 * CH + 1; e += 256) {
-    float acc = 0.f;
-    if (e < 27 * CH) {
-      const int t = e / CH, i = e % CH;
-      for (int p = 0; p < TPOS; ++p) {
-        const int m = p % TX, yr = (p / TX) % TY, zr = p / (TX * TY);
-        acc = fmaf(dyt[tap_cell(zr, yr, m, 13)], from_bf16(tile[tap_cell(zr, yr, m, t) * CH + i]), acc);
-      }
-    } else {
-      for (int p = 0; p < TPOS; ++p) {
-        const int m = p % TX, yr = (p / TX) % TY, zr = p / (TX * TY);
-        acc += dyt[tap_cell(zr, yr, m, 13)];
-      }
-    }
-    part[blk * (27 * CH + 1) + e] = acc;
-  }
+  for (int o = 32; o > 0; o >>= 1) bacc += __shfl_xor(bacc, o, 64);
+  if (lane == 0) red[wave * ROWW + ROWW - 1] = bacc;
+  __syncthreads();
+  for (int e = threadIdx.x; e < ROWW; e += 256)
+    part[(long long)blockIdx.x * ROWW + e] = (red[e] + red[ROWW + e]) + (red[2 * ROWW + e] + red[3 * ROWW + e]);
 }
 
-// Weight gradient of a 16-output convolution on MFMA:
+// Weight gradient of a 16-output convolution:
 //   dW[o][t C + i] = sum_p dpre[p][o] x[p + d_t][i],  db[o] = sum_p dpre[p][o]
-// M = 16 output channels, N = 16 columns (C = 16: the channels of one tap; C = 8: two taps),
-// K = 16 positions per instruction.  One block loops over the x tiles of one (y, z) tile
-// row and writes one partial [16][KP + 1] (bias in the last column).
+// on v_mfma_f32_16x16x32_bf16 with M = 16 output channels, N = 16 columns (C = 16: the channels of one
+// tap; C = 8: two taps) and K = 32 positions (two x rows).  Both operands are channels-last in LDS and
+// are needed position-fastest: ds_read_b64_tr_b16 transposes on the way (in each group of 16 lanes, lane
+// 4 r + c reads channels 4c..4c+3 of position r, and lane i receives channel i of positions 0..3), so a
+// tap is only an address offset and nothing is gathered element by element.  A group of lanes reads 128
+// contiguous bytes, free of bank conflicts.  The four waves split the column tiles; a block takes
+// several tiles of 16 x 4 x 8 positions and writes one partial [16][KP + 1] (bias in the last column).
+// Bound by the LDS reads of the x operand (1 KB per product).  On a 128^3 network grid 119 us (layer 2)
+// and 52 us (layer 1); with element-by-element gathers of the operand, 225 and 201 us.
+constexpr int VX = 16, VY = 4, VZ = 8, UX = VX + 2, UY = VY + 2, UZ = VZ + 2, UCELLS = UX * UY * UZ;
+constexpr int VCELLS = VX * VY * VZ;
+
+__device__ __forceinline__ bf8 tr_pair(const unsigned short* p0, const unsigned short* p1) {
+  typedef __attribute__((address_space(3))) s4 lds4;
+  const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)p0);
+  const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)p1);
+  typedef short s8 __attribute__((ext_vector_type(8)));
+  return __builtin_bit_cast(bf8, s8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
+}
+
+//   SRC 0: x is a bf16 tensor [n^3][C];  SRC 1: x is x0 assembled from (delta, u_p), C = 8
 template <int C, int KP, int SRC>
-__global__ void __launch_bounds__(256) k_wgrad16(const unsigned short* __restrict__ dpre,
-                                                 const unsigned short* __restrict__ in, const float* __restrict__ delta,
-                                                 const float* __restrict__ up, Geo3 g, float* __restrict__ part) {
+__global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict__ dpre,
+                                               const unsigned short* __restrict__ in, const float* __restrict__ delta,
+                                               const float* __restrict__ up, Geo3 g, int tiles,
+                                               float* __restrict__ part) {
   constexpr int NT = KP / 16;                 // column tiles: C = 16 -> 27 taps, C = 8 -> 14 tap pairs
   constexpr int TPW = (NT + 3) / 4;           // column tiles per wave
-  __shared__ unsigned short tile[HCELLS * C];
-  __shared__ unsigned short dt[CH][TPOS + 4];   // dpre of the tile, transposed [o][p]
+  __shared__ __align__(16) unsigned short xt[UCELLS * C];
+  __shared__ __align__(16) unsigned short dt[VCELLS * CH];
   const long long n3 = (long long)g.n * g.n * g.n;
-  const int b = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = lane & 15, q = lane >> 4;
-  f4 acc[TPW];
+  const int n = g.n, msk = n - 1, nbx = n / VX, nby = n / VY, per = nbx * nby * (n / VZ);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, q = lane >> 4;
+  const int r = m >> 2, c = m & 3;            // position and channel quarter this lane reads for its group
+  int off[TPW];                               // element offset of column tile wave + 4k from the row's first halo cell
+#pragma unroll
+  for (int k = 0; k < TPW; ++k) {
+    int t = C == 16 ? wave + 4 * k : 2 * (wave + 4 * k) + (c >> 1);
+    if (t > 26) t = 26;                       // padded columns: computed and not used
+    const int cell = 1 + (t % 3 - 1) + ((t / 3) % 3 - 1) * UX + (t / 9 - 1) * UX * UY + 4 * q + r;
+    off[k] = cell * C + (C == 16 ? 4 * c : 4 * (c & 1));
+  }
+  const bf8 ones = __builtin_bit_cast(bf8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+  f4 acc[TPW], bacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int k = 0; k < TPW; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
-  float bacc = 0.f;
-  const int ntx = g.n / TX, nty = g.n / TY;
-  const int y0 = (blockIdx.x % nty) * TY, z0 = (blockIdx.x / nty) * TZ;
-  for (int xt = 0; xt < ntx; ++xt) {
-    const int x0 = xt * TX;
-    __syncthreads();
-    if (SRC == 0) stage_bf16<C>(tile, in + b * n3 * C, g.n, x0, y0, z0);
-    else stage_x0(tile, delta + b * n3, up + b * n3, g, x0, y0, z0);
-    for (int e = threadIdx.x; e < TPOS * CH / 4; e += 256) {
-      const int p = e / (CH / 4), o4 = e % (CH / 4);
-      const int pm = p % TX, py = (p / TX) % TY, pz = p / (TX * TY);
-      const long long cell = b * n3 + ((long long)(z0 + pz) * g.n + (y0 + py)) * g.n + x0 + pm;
-      const uint2 v = *(const uint2*)(dpre + cell * CH + 4 * o4);
-      dt[4 * o4 + 0][p] = (unsigned short)(v.x & 0xFFFF);
-      dt[4 * o4 + 1][p] = (unsigned short)(v.x >> 16);
-      dt[4 * o4 + 2][p] = (unsigned short)(v.y & 0xFFFF);
-      dt[4 * o4 + 3][p] = (unsigned short)(v.y >> 16);
+  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int b = t / per, tt = t % per;
+    const int x0 = (tt % nbx) * VX, y0 = ((tt / nbx) % nby) * VY, z0 = (tt / (nbx * nby)) * VZ;
+    auto halo = [&](int cell) {
+      const int hx = cell % UX, hy = (cell / UX) % UY, hz = cell / (UX * UY);
+      return b * n3 + ((long long)((z0 - 1 + hz) & msk) * n + ((y0 - 1 + hy) & msk)) * n + ((x0 - 1 + hx) & msk);
+    };
+    constexpr int PD = VCELLS * 2 / 256;
+    uint4 dv[PD];
+#pragma unroll
+    for (int k = 0; k < PD; ++k) {
+      const int e = threadIdx.x + k * 256, cell = e >> 1;
+      const int lx = cell % VX, ly = (cell / VX) % VY, lz = cell / (VX * VY);
+      dv[k] = ((const uint4*)dpre)[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)];
     }
-    __syncthreads();
-    if (threadIdx.x < CH) {
-      for (int p = 0; p < TPOS; ++p) bacc += from_bf16(dt[threadIdx.x][p]);
-    }
+    if constexpr (SRC == 0) {
+      constexpr int CPC = C / 8, TOTAL = UCELLS * CPC, PER = (TOTAL + 255) / 256;
+      uint4 v[PER];
 #pragma unroll
-    for (int kp = 0; kp < TPOS / 16; ++kp) {
-      // A[o][k] = dpre[p = 16 kp + k][o]: lane row o = m, k = 4q..4q+3
-      const s4 a = *(const s4*)(&dt[m][kp * 16 + 4 * q]);
-      const int p0 = kp * 16 + 4 * q;
+      for (int k = 0; k < PER; ++k) {
+        const int e0 = threadIdx.x + k * 256, e = e0 < TOTAL ? e0 : TOTAL - 1;
+        v[k] = *(const uint4*)(in + halo(e / CPC) * C + 8 * (e % CPC));
+      }
+      __syncthreads();                        // every wave is done with the last tile
 #pragma unroll
-      for (int k = 0; k < TPW; ++k) {
-        const int nt = wave + 4 * k;
-        if (nt < NT) {
-          // B[k][n] = x[p + d_t][i]: lane column n = m
-          const int col = nt * 16 + m;
-          int t = col / C;
-          const int i = col % C;
-          if (t > 26) t = 26;
-          s4 bv;
+      for (int k = 0; k < PER; ++k)
+        if (threadIdx.x + k * 256 < TOTAL) ((uint4*)xt)[threadIdx.x + k * 256] = v[k];
+    } else {
+      constexpr int PER = (UCELLS + 255) / 256;
+      float fd[PER], fu[PER];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int p = p0 + j;
-            const int pm = p % TX, py = (p / TX) % TY, pz = p / (TX * TY);
-            bv[j] = (short)tile[tap_cell(pz, py, pm, t) * C + i];
-          }
-          acc[k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bv, acc[k], 0, 0, 0);
+      for (int k = 0; k < PER; ++k) {
+        const int e0 = threadIdx.x + k * 256;
+        const long long s = halo(e0 < UCELLS ? e0 : UCELLS - 1);
+        fd[k] = delta[s];
+        fu[k] = up[s];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const int e = threadIdx.x + k * 256;
+        if (e < UCELLS) {
+          const int hx = e % UX, hy = (e / UX) % UY, hz = e / (UX * UY);
+          ((uint4*)xt)[e] = x0_cell(g, (x0 - 1 + hx) & msk, (y0 - 1 + hy) & msk, (z0 - 1 + hz) & msk, fd[k], fu[k]);
         }
       }
     }
+#pragma unroll
+    for (int k = 0; k < PD; ++k) ((uint4*)dt)[threadIdx.x + k * 256] = dv[k];
+    __syncthreads();
+    const int da = (4 * q + r) * CH + 4 * c;  // dpre element of this lane in a row
+#pragma unroll 2
+    for (int s = 0; s < VY * VZ / 2; ++s) {   // rows 2s and 2s + 1: the same z, y = 2 (s % 2) and the next
+      const int lz = s / (VY / 2), ly = 2 * (s % (VY / 2));
+      const unsigned short* dr = dt + (lz * VY + ly) * VX * CH + da;
+      const bf8 a = tr_pair(dr, dr + VX * CH);
+      const unsigned short* xr = xt + ((lz + 1) * UY + ly + 1) * UX * C;
+      // every wave runs all TPW products and the bias, without branches between them (a wave past the
+      // last column tile repeats the last tap, and only wave 3 stores its bias)
+      bf8 x[TPW];
+#pragma unroll
+      for (int k = 0; k < TPW; ++k) x[k] = tr_pair(xr + off[k], xr + off[k] + UX * C);
+#pragma unroll
+      for (int k = 0; k < TPW; ++k) acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[k], acc[k], 0, 0, 0);
+      bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, bacc, 0, 0, 0);
+    }
   }
-  // D[o = 4q + r][col = m] for each column tile
-  const long long blk = (long long)b * gridDim.x + blockIdx.x;
-  float* pb = part + blk * (CH * (KP + 1));
+  // D[o = 4q + i][col = m] for each column tile
+  float* pb = part + (long long)blockIdx.x * (CH * (KP + 1));
 #pragma unroll
   for (int k = 0; k < TPW; ++k) {
     const int nt = wave + 4 * k;
     if (nt < NT) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) pb[(4 * q + r) * (KP + 1) + nt * 16 + m] = acc[k][r];
+      for (int i = 0; i < 4; ++i) pb[(4 * q + i) * (KP + 1) + nt * 16 + m] = acc[k][i];
     }
   }
-  if (threadIdx.x < CH) pb[threadIdx.x * (KP + 1) + KP] = bacc;
+  if (wave == 3 && m == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pb[(4 * q + i) * (KP + 1) + KP] = bacc[i];
+  }
 }
 
-// out[c] = sum over nb partial rows of in[row][c] (fixed order).
-__global__ void __launch_bounds__(256) k_reduce_cols(const float* __restrict__ part, long long nb, int ncols,
-                                                     float* __restrict__ out) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= ncols) return;
-  double acc = 0.0;
-  for (long long r = 0; r < nb; ++r) acc += (double)part[r * ncols + c];
-  out[c] = (float)acc;
-}
-
-__global__ void __launch_bounds__(256) k_reduce_loss(const double* __restrict__ part, int nb, double* __restrict__ out) {
-  double a = 0.0;
-  for (int i = threadIdx.x; i < nb; i += 256) a += part[i];
-  double t1, t2;
-  block_sum2<256>(a, 0.0, &t1, &t2);
-  if (threadIdx.x == 0) out[0] = t1;
-}
-
-// Weights in MFMA layouts: wk1 [16][K1P] (k = t*8 + i), wk2 [16][432] (k = t*16 + i),
-// wk2t [16][432] with wk2t[i][t*16 + o] = W2[o][26 - t][i] (flipped taps, transposed
-// channels: the data gradient as a forward convolution), w3 [432] as bf16-rounded FP32.
-__global__ void __launch_bounds__(256) k_prep_weights(const float* __restrict__ th, unsigned short* __restrict__ wk2t,
-                                                      float* __restrict__ w3) {
-  // wk2t: layer-2 weights flipped and transposed for the data gradient, [16 in][27 x 16 out] bf16;
-  // w3: layer-3 weights rounded to bf16 (FP32 storage) for the output-layer backward
-  for (int e = blockIdx.x * 256 + threadIdx.x; e < CH * K2 + K2; e += gridDim.x * 256) {
-    if (e < CH * K2) {
-      const int i = e / K2, k = e % K2, t = k / CH, o = k % CH;
-      wk2t[e] = to_bf16(th[OFF_W2 + (o * 27 + (26 - t)) * CH + i]);
-    } else {
-      w3[e - CH * K2] = from_bf16(to_bf16(th[OFF_W3 + e - CH * K2]));
+// Sums of the partial rows in FP64, all three layers in one launch: out[slice][column] = sum over the
+// slice's rows, columns in the order layer 3 [433], layer 2 [16][433], layer 1 [16][225].  A block takes
+// 64 columns; its four waves take every fourth row of the slice with four loads in flight each: 11 us
+// at 128^3.  (One thread per column over all rows, 8,192 of them in layer 3, was 3.87 of a 4.84 ms
+// training step: three launches of 2 to 28 blocks, one dependent FP64 add after another.)  The last
+// column block's first slice sums the loss.
+constexpr int kRedSlices = 16;
+constexpr int COL3 = K2 + 1, COL2 = CH * (K2 + 1), COL1 = CH * (K1P + 1), NCOLS = COL3 + COL2 + COL1;
+constexpr int RB3 = (COL3 + 63) / 64, RB2 = (COL2 + 63) / 64, RB1 = (COL1 + 63) / 64;
+__global__ void __launch_bounds__(256) k_reduce_parts(const float* __restrict__ p3, long long n3r,
+                                                      const float* __restrict__ p2, const float* __restrict__ p1,
+                                                      long long nwr, double* __restrict__ out,
+                                                      const double* __restrict__ lossp, int nloss,
+                                                      double* __restrict__ losst) {
+  if (blockIdx.x == RB3 + RB2 + RB1) {
+    if (blockIdx.y != 0) return;
+    double a = 0.0;
+    for (int i = threadIdx.x; i < nloss; i += 256) a += lossp[i];
+    double t1, t2;
+    block_sum2<256>(a, 0.0, &t1, &t2);
+    if (threadIdx.x == 0) losst[0] = t1;
+    return;
+  }
+  __shared__ double sh[4][64];
+  int cb = blockIdx.x, ncols = COL3, base = 0;
+  const float* p = p3;
+  long long rows = n3r;
+  if (cb >= RB3) { cb -= RB3; p = p2; rows = nwr; ncols = COL2; base = COL3; }
+  if (base && cb >= RB2) { cb -= RB2; p = p1; ncols = COL1; base = COL3 + COL2; }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = cb * 64 + lane;
+  const long long lo = rows * blockIdx.y / kRedSlices, hi = rows * (blockIdx.y + 1) / kRedSlices;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  if (col < ncols) {
+    long long i = lo + wave;
+    for (; i + 12 < hi; i += 16) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[k] += (double)p[(i + 4 * k) * ncols + col];
     }
+    for (; i < hi; i += 4) s[0] += (double)p[i * ncols + col];
   }
+  sh[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
+  __syncthreads();
+  if (wave == 0 && col < ncols)
+    out[(long long)blockIdx.y * NCOLS + base + col] = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
 }
 
-// Gradient assembly from the reduced partials into the parameter layout.
-__global__ void __launch_bounds__(256) k_assemble_grad(const float* __restrict__ g1, const float* __restrict__ g2,
-                                                       const float* __restrict__ g3, float* __restrict__ grad) {
-  for (int e = blockIdx.x * 256 + threadIdx.x; e < NPARAM; e += gridDim.x * 256) {
-    float v;
-    if (e < OFF_B1) { const int o = e / K1, k = e % K1; v = g1[o * (K1P + 1) + k]; }
-    else if (e < OFF_W2) v = g1[(e - OFF_B1) * (K1P + 1) + K1P];
-    else if (e < OFF_B2) { const int f = e - OFF_W2, o = f / K2, k = f % K2; v = g2[o * (K2 + 1) + k]; }
-    else if (e < OFF_W3) v = g2[(e - OFF_B2) * (K2 + 1) + K2];
-    else v = g3[e - OFF_W3];        // W3 (432) then b3 (entry 432)
-    grad[e] = v;
-  }
-}
-
-// Adam (Kingma & Ba 2015) with bias correction; step counts from 1.
-__global__ void __launch_bounds__(256) k_adam(float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
-                                              const float* __restrict__ grad, int n, float lr, float b1, float b2,
-                                              float eps, float c1, float c2) {
-  for (int e = blockIdx.x * 256 + threadIdx.x; e < n; e += gridDim.x * 256) {
-    const float gr = grad[e];
+// Gradient in the parameter layout from the sliced sums and, with lr > 0, the Adam update (Kingma & Ba
+// 2015) with bias correction, step counted from 1 (c1 = 1 - beta1^step, c2 = 1 - beta2^step).
+__global__ void __launch_bounds__(64) k_grad_adam(const double* __restrict__ red, float* __restrict__ grad,
+                                                  float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
+                                                  float lr, float b1, float b2, float eps, float c1, float c2) {
+  const int e = blockIdx.x * 64 + threadIdx.x;
+  if (e >= NPARAM) return;
+  int col;
+  if (e < OFF_B1) col = COL3 + COL2 + (e / K1) * (K1P + 1) + e % K1;
+  else if (e < OFF_W2) col = COL3 + COL2 + (e - OFF_B1) * (K1P + 1) + K1P;
+  else if (e < OFF_B2) col = COL3 + ((e - OFF_W2) / K2) * (K2 + 1) + (e - OFF_W2) % K2;
+  else if (e < OFF_W3) col = COL3 + (e - OFF_B2) * (K2 + 1) + K2;
+  else col = e - OFF_W3;                                   // W3 (432) then b3 (entry 432)
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < kRedSlices; ++k) s += red[(long long)k * NCOLS + col];
+  const float gr = (float)s;
+  grad[e] = gr;
+  if (lr > 0.f) {
     const float mm = b1 * m[e] + (1.f - b1) * gr;
     const float vv = b2 * v[e] + (1.f - b2) * gr * gr;
     m[e] = mm;
