@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 #include <rocprofiler-sdk-roctx/roctx.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -45,7 +46,7 @@ struct Layout {
   size_t a1 = 0, a2 = 0, d1 = 0, d2 = 0, ybuf = 0, dybuf = 0, upbuf = 0,
          part_out = 0, part_w1 = 0, part_w2 = 0, gred = 0, grad = 0, lossp = 0, losst = 0, dc = 0, uc = 0,
          wf1 = 0, wf2 = 0, wf2t = 0, dh = 0, uh = 0;
-  long long t_out = 0, t_w = 0, nb_out = 0, nb_w = 0, nb_loss = 0;   // backward tiles and blocks
+  long long t_out = 0, t_w = 0, nb_out = 0, nb_w = 0, nslice = 0, nb_loss = 0;   // backward tiles and blocks
   long long cnn_n = 0;
   long long nbins = 0, nscan = 0;
 };
@@ -87,6 +88,27 @@ long long max_partial_blocks(int n) {
   long long xb = (long long)(n / 2 + 1) * n / tx;
   long long zb = (long long)n * n / 2;
   return xb > zb ? xb : zb;
+}
+
+// Shape of the binning of n objects into nbins bricks: bins of a block's LDS histogram (the smallest of the
+// three sizes that holds them all, else the largest), blocks, and objects per block.  A block of the full
+// histogram has a CU's LDS to itself, and clears, stores and reloads 128 KB, so it is given at least
+// 16,384 objects; with the small histograms (up to 8^3 and 16^3 bricks, grids to 128^3 and 256^3) several
+// blocks share a CU and 2,048 or 4,096 objects pay for one.
+struct BinShape {
+  int bins;
+  long long blocks, chunk;
+};
+constexpr int kBinsS = 512, kBinsM = 4096;
+BinShape bin_shape(long long nbins, long long n) {
+  BinShape b;
+  b.bins = nbins <= kBinsS ? kBinsS : (nbins <= kBinsM ? kBinsM : kLdsBins);
+  const long long least = b.bins == kBinsS ? 2048 : (b.bins == kBinsM ? 4096 : 16384);
+  const long long most = b.bins == kLdsBins ? RECON_BIN_BLOCKS : 2 * RECON_BIN_BLOCKS;
+  b.blocks = (n + least - 1) / least;
+  if (b.blocks > most) b.blocks = most;
+  b.chunk = (n + b.blocks - 1) / b.blocks;
+  return b;
 }
 
 Layout make_layout(const recon_params_t* p) {
@@ -131,7 +153,8 @@ Layout make_layout(const recon_params_t* p) {
     L.bstart = take((L.nbins + 2) * 4);
     L.bcursor = take((L.nbins + 2) * 4);
     L.bsum = take(L.nscan * 4);
-    L.bhist = take((size_t)RECON_BIN_BLOCKS * kLdsBins * 4);
+    const BinShape bs = bin_shape(L.nbins, p->max_objects);
+    L.bhist = take((size_t)bs.blocks * bs.bins * 4);
     L.bvalid = take(2 * L.nbins);
   }
   if (p->flags & RECON_CNN_BUFFERS) {
@@ -142,7 +165,9 @@ Layout make_layout(const recon_params_t* p) {
     L.t_out = b * m3 / (FX * FY * FZ);
     L.t_w = b * m3 / VCELLS;
     L.nb_out = L.t_out < kBwdBlocks ? L.t_out : kBwdBlocks;
-    L.nb_w = L.t_w < kBwdBlocks ? L.t_w : kBwdBlocks;
+    const long long rows = b * (m / VY) * (m / 4);   // 256 rows at 64^3, 1024 at 128^3: the partial rows are 42 KB each
+    L.nb_w = std::min<long long>(std::min<long long>(L.t_w, rows), kBwdBlocks);
+    L.nslice = std::max<long long>(1, std::min<long long>(kRedSlices, std::max(L.nb_out, L.nb_w) / 64));
     L.nb_loss = 1024;
     L.a1 = take(b * m3 * CH * 2);
     L.a2 = take(b * m3 * CH * 2);
@@ -169,7 +194,7 @@ Layout make_layout(const recon_params_t* p) {
     L.part_out = take((size_t)L.nb_out * COL3 * 4);
     L.part_w1 = take((size_t)L.nb_w * COL1 * 4);
     L.part_w2 = take((size_t)L.nb_w * COL2 * 4);
-    L.gred = take((size_t)kRedSlices * NCOLS * 8);
+    L.gred = take((size_t)L.nslice * NCOLS * 8);
     L.grad = take(NPARAM * 4);
     L.lossp = take(L.nb_loss * 8);
     L.losst = take(8);
@@ -296,6 +321,7 @@ struct recon_plan_s {
   const float* net = nullptr;
   unsigned *bcount = nullptr, *bstart = nullptr, *bcursor = nullptr, *bsum = nullptr;
   unsigned* bhist = nullptr;   // per-block LDS histograms of the binning count, reused by the scatter
+  int* errblk = nullptr;       // per-block counts of invalid objects, between count and scan (in stmp's memory)
   // brick-sparse integer grids: per-brick validity of each grid, used while sparse_* is set (the
   // bricks that are not valid are zero and are not read)
   unsigned char *bvalid_g = nullptr, *bvalid_r = nullptr;
@@ -412,7 +438,7 @@ const unsigned char* valid_of(const recon_plan_t* pl, int which) {
 }
 
 // Device-side alpha / rho_bar / mask threshold from the totals, then the survey mask.
-int launch_fill_u64(recon_plan_t* pl, void* p, long long count);
+int launch_fill_u64(recon_plan_t* pl, void* p, long long count, int* zero_too = nullptr);
 
 // Scalars, and with randoms the survey mask and its z-tile flags (pl->mflag; tile width tw = 2 wz).
 int scalars_and_mask(recon_plan_t* pl, int nblk_z, int tw) {
@@ -729,15 +755,73 @@ const Ops* ops_for(int n) {
   }
 }
 
-int launch_fill_u64(recon_plan_t* pl, void* p, long long count) {
+int launch_fill_u64(recon_plan_t* pl, void* p, long long count, int* zero_too) {
   long long blocks = (count + kThreads - 1) / kThreads;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) blocks = 1;
   {
     PROF(pl, KP_FILL);
-    k_fill_u64<<<(unsigned)blocks, kThreads, 0, pl->stream>>>((unsigned long long*)p, count);
+    k_fill_u64<<<(unsigned)blocks, kThreads, 0, pl->stream>>>((unsigned long long*)p, count, zero_too);
   }
   return check_launch(pl, "fill");
+}
+
+// Blocks per brick of the launches that walk a brick's objects: small grids have too few bricks to fill the
+// chip (8 at 32^3, 64 at 64^3), so theirs are split (brick_part; at most 16 parts).
+unsigned brick_parts(long long nbins) {
+  const long long p = 4096 / nbins;
+  return (unsigned)(p < 1 ? 1 : (p > 16 ? 16 : p));
+}
+
+template <int BINS>
+void launch_bin_count(recon_plan_t* pl, const BinShape& b, const float* pos, const float* w, long long n,
+                      const long long* off) {
+  k_bin_count_lds<1024, BINS><<<(unsigned)b.blocks, 1024, 0, pl->stream>>>(pos, w, n, b.chunk, off, pl->batch, pl->cic,
+                                                                          pl->bcount, pl->errblk, pl->bhist);
+}
+template <int BINS>
+void launch_bin_scatter(recon_plan_t* pl, const BinShape& b, const float* pos, const float* w, long long n,
+                        const long long* off) {
+  k_bin_scatter_lds<1024, BINS><<<(unsigned)b.blocks, 1024, 0, pl->stream>>>(
+      pos, w, n, b.chunk, off, pl->batch, pl->cic, pl->bcursor, pl->sorted, pl->slot_of, pl->bhist, pl->bcount,
+      pl->L.nbins);
+}
+
+// Objects into brick order (pl->sorted, pl->slot_of, pl->bstart).  The brick counts are zero before and
+// after (cleared at the plan's creation and by every scatter).  prep >= 0: the bricks of `grid` are
+// prepared for a deposit in that mode (k_brick_prepare).  Invalid objects are counted into *errc (replacing
+// it when fresh, else added).
+int bin_objects(recon_plan_t* pl, const float* pos, const float* w, long long n, const long long* off, int prep,
+                unsigned char* valid, unsigned long long* grid, int* errc, bool fresh) {
+  const long long nb = pl->L.nbins;
+  const BinShape bs = bin_shape(nb, n);
+  {
+    PROF(pl, KP_BIN);
+    if (bs.bins == kBinsS) launch_bin_count<kBinsS>(pl, bs, pos, w, n, off);
+    else if (bs.bins == kBinsM) launch_bin_count<kBinsM>(pl, bs, pos, w, n, off);
+    else launch_bin_count<kLdsBins>(pl, bs, pos, w, n, off);
+  }
+  RECON_TRY(check_launch(pl, "bin count"));
+  {
+    PROF(pl, KP_SCAN);
+    const unsigned* bsum = nullptr;
+    if (nb > kScanDirect) {
+      k_scan_blocks<<<(unsigned)pl->L.nscan, 256, 0, pl->stream>>>(pl->bcount, nb, pl->bsum);
+      bsum = pl->bsum;
+    }
+    const long long blocks = pl->L.nscan + (prep >= 0 ? nb : 0);
+    k_scan_prepare<<<(unsigned)blocks, 256, 0, pl->stream>>>(pl->bcount, nb, bsum, (int)pl->L.nscan, pl->bstart,
+                                                             pl->bcursor, pl->n, prep, valid, grid, pl->errblk,
+                                                             (int)bs.blocks, errc, fresh ? 1 : 0);
+  }
+  RECON_TRY(check_launch(pl, "bin scan"));
+  {
+    PROF(pl, KP_BIN);
+    if (bs.bins == kBinsS) launch_bin_scatter<kBinsS>(pl, bs, pos, w, n, off);
+    else if (bs.bins == kBinsM) launch_bin_scatter<kBinsM>(pl, bs, pos, w, n, off);
+    else launch_bin_scatter<kLdsBins>(pl, bs, pos, w, n, off);
+  }
+  return check_launch(pl, "bin scatter");
 }
 
 // The device masks are written only here, so an upload whose flags the device copy already holds
@@ -965,6 +1049,7 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
     pl->bcursor = (unsigned*)(w + L.bcursor);
     pl->bsum = (unsigned*)(w + L.bsum);
     pl->bhist = (unsigned*)(w + L.bhist);
+    pl->errblk = (int*)pl->stmp;   // fewer blocks than objects, so it fits
     pl->bvalid_g = (unsigned char*)(w + L.bvalid);
     pl->bvalid_r = pl->bvalid_g + L.nbins;
   }
@@ -1015,6 +1100,11 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
       delete pl;
       return RECON_EINVAL;
     }
+  }
+  // the brick counts are zero whenever no deposit is running
+  if (pl->bcount && launch_fill_u64(pl, pl->bcount, (L.nbins + 2) / 2) != RECON_OK) {
+    delete pl;
+    return RECON_EDEVICE;
   }
   // twiddles exp(-2 pi i m / N), rounded once from double
   std::vector<float2> tw(n);
@@ -1123,9 +1213,8 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
   unsigned char* valid = which == RECON_GAL ? pl->bvalid_g : pl->bvalid_r;
   bool& sparse = which == RECON_GAL ? pl->sparse_g : pl->sparse_r;
   if (fresh) {
-    HIP_TRY(pl, hipMemsetAsync(errc, 0, sizeof(int), pl->stream));
     if (!(binned && can_sparse)) {
-      RECON_TRY(launch_fill_u64(pl, grid, pl->n3 * pl->batch));
+      RECON_TRY(launch_fill_u64(pl, grid, pl->n3 * pl->batch, errc));
       sparse = false;
     }   // else only the bricks the deposit touches are cleared, after the count below
   } else if (sparse && n > 0 && !binned) {
@@ -1148,62 +1237,17 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
     }
     RECON_TRY(check_launch(pl, "paint (NGP)"));
   } else if (binned) {
-    // brick-binned deposit: count, scan, scatter into brick order, per-brick LDS accumulation
+    // brick-binned deposit: count, scan (with the preparation of the grid's bricks), scatter into brick
+    // order, per-brick LDS accumulation
     pl->srt_which = -1;   // the sorted copy is being replaced
-    long long blocks = (n + kThreads - 1) / kThreads;
-    if (blocks > 8192) blocks = 8192;
     const long long nb = pl->L.nbins;
-    RECON_TRY(launch_fill_u64(pl, pl->bcount, (nb + 2) / 2));
-    const long long nbs = (pl->n + kBrick - 1) / kBrick;
-    const bool lds_bins = RECON_BIN_WINDOW || nbs * nbs * nbs <= kLdsBins;   // windows above 512^3
-    long long lblocks = (n + 16383) / 16384;
-    if (lblocks > RECON_BIN_BLOCKS) lblocks = RECON_BIN_BLOCKS;
-    const long long chunk = (n + lblocks - 1) / lblocks;
-    {
-      PROF(pl, KP_BIN);
-      if (lds_bins)
-        k_bin_count_lds<1024><<<(unsigned)lblocks, 1024, 0, pl->stream>>>(pos, w, n, chunk, (const long long*)offsets,
-                                                                   pl->batch, pl->cic, pl->bcount, errc,
-                                                                   pl->bhist);
-      else
-        k_bin_count<<<(unsigned)blocks, kThreads, 0, pl->stream>>>(pos, w, n, (const long long*)offsets, pl->batch,
-                                                                   pl->cic, pl->bcount, errc);
-    }
-    RECON_TRY(check_launch(pl, "bin count"));
-    if (can_sparse && (fresh || sparse)) {
-      // clear the bricks this deposit touches (new grid), or those of them not held yet (accumulate)
-      {
-        PROF(pl, KP_FILL);
-        k_brick_prepare<<<(unsigned)nb, 256, 0, pl->stream>>>(pl->bcount, pl->n, fresh ? 0 : 1, valid,
-                                                              (unsigned long long*)grid);
-      }
-      RECON_TRY(check_launch(pl, "brick prepare"));
-      sparse = true;
-    }
-    {
-      PROF(pl, KP_SCAN);
-      k_scan_blocks<<<(unsigned)pl->L.nscan, 256, 0, pl->stream>>>(pl->bcount, nb, pl->bsum);
-      k_scan_top<<<1, 256, 0, pl->stream>>>(pl->bsum, (int)pl->L.nscan);
-      k_scan_apply<<<(unsigned)pl->L.nscan, 256, 0, pl->stream>>>(pl->bcount, nb, pl->bsum, pl->bstart,
-                                                                  pl->bcursor);
-    }
-    RECON_TRY(check_launch(pl, "bin scan"));
-    {
-      PROF(pl, KP_BIN);
-      if (lds_bins)
-        k_bin_scatter_lds<1024><<<(unsigned)lblocks, 1024, 0, pl->stream>>>(pos, w, n, chunk, (const long long*)offsets,
-                                                                     pl->batch, pl->cic, pl->bcursor, pl->sorted,
-                                                                     pl->slot_of, pl->bhist);
-      else
-        k_bin_scatter<<<(unsigned)blocks, kThreads, 0, pl->stream>>>(pos, w, n, (const long long*)offsets,
-                                                                     pl->batch, pl->cic, pl->bcursor, pl->sorted,
-                                                                     pl->slot_of);
-    }
-    RECON_TRY(check_launch(pl, "bin scatter"));
+    const int prep = can_sparse && (fresh || sparse) ? (fresh ? 0 : 1) : -1;
+    RECON_TRY(bin_objects(pl, pos, w, n, (const long long*)offsets, prep, valid, (unsigned long long*)grid, errc, fresh));
+    if (prep >= 0) sparse = true;
     {
       PROF(pl, KP_PAINT);
-      k_brick_deposit<RECON_BRICK_NT><<<(unsigned)nb, RECON_BRICK_NT, 0, pl->stream>>>(pl->sorted, pl->bstart, pl->cic,
-                                                            (unsigned long long*)grid);
+      k_brick_deposit<RECON_BRICK_NT><<<dim3((unsigned)nb, brick_parts(nb)), RECON_BRICK_NT, 0, pl->stream>>>(
+          pl->sorted, pl->bstart, pl->cic, (unsigned long long*)grid);
     }
     RECON_TRY(check_launch(pl, "brick deposit"));
     pl->srt_which = which;
@@ -1652,21 +1696,20 @@ int recon_shift(recon_plan_t* pl, int which_flags, const float* pos, int64_t n, 
     return fail(pl, RECON_EINVAL, "RECON_SHIFT_AS_PAINTED: not the catalogue painted last through the bricks");
   if (n == 0) return RECON_OK;
   Marker mark(which == RECON_GAL ? "a10 shift (galaxies)" : "a10 shift (randoms)");
-  HIP_TRY(pl, hipMemsetAsync(pl->err + 2, 0, sizeof(int), pl->stream));
   long long blocks = (n + kThreads - 1) / kThreads;
   if (blocks > 8192) blocks = 8192;
   if (as_painted) {
     // the catalogue painted last through the bricks: shift its brick-ordered copy, then reorder
     {
       PROF(pl, KP_SHIFT);
-      k_shift_brick<512><<<(unsigned)pl->L.nbins, 512, 0, pl->stream>>>(
+      k_shift_brick<512><<<dim3((unsigned)pl->L.nbins, brick_parts(pl->L.nbins)), 512, 0, pl->stream>>>(
           pl->sorted, pl->bstart, pl->psi, pl->cic, (float)pl->p.observer[0], (float)pl->p.observer[1],
           (float)pl->p.observer[2], (float)pl->p.growth, which == RECON_GAL ? 1 : 0, pl->stmp);
       // one trip per block: per XCD, ceil(chunks / 8) chunks of 256 objects in groups of kObjBatch
       const long long chunks = (n + kThreads - 1) / kThreads;
       const long long ub = 8 * (((chunks + 7) / 8 + kObjBatch - 1) / kObjBatch);
       k_shift_unpermute<<<(unsigned)ub, kThreads, 0, pl->stream>>>(
-          pl->slot_of, pl->stmp, n, pos, disp_out, pos_out, pl->err + 2);
+          pl->slot_of, pl->stmp, n, pos, disp_out, pos_out);
     }
     return check_launch(pl, "shift (brick order)");
   }
@@ -1675,7 +1718,7 @@ int recon_shift(recon_plan_t* pl, int which_flags, const float* pos, int64_t n, 
     k_shift<<<(unsigned)blocks, kThreads, 0, pl->stream>>>(
         pos, n, (const long long*)offsets, pl->batch, pl->psi, pl->cic, (float)pl->p.observer[0],
         (float)pl->p.observer[1], (float)pl->p.observer[2], (float)pl->p.growth, which == RECON_GAL ? 1 : 0,
-        disp_out, pos_out, pl->err + 2);
+        disp_out, pos_out);
   }
   return check_launch(pl, "shift");
 }
@@ -1805,12 +1848,12 @@ int recon_cnn_train_step(recon_plan_t* pl, float* params, float* adam_m, float* 
     k_wgrad<CH, K2, 0><<<nbw, 256, 0, s>>>(pl->d2, pl->a1, nullptr, nullptr, g, (int)pl->L.t_w, pl->part_w2);
     k_conv_fwd<CH, 0, 1><<<gridf, 256, 0, s>>>(pl->d2, nullptr, nullptr, g, pl->wf2t, nullptr, pl->d1, pl->a1);
     k_wgrad<CIN, K1P, 1><<<nbw, 256, 0, s>>>(pl->d1, nullptr, delta, u_p, g, (int)pl->L.t_w, pl->part_w1);
-    k_reduce_parts<<<dim3(RB3 + RB2 + RB1 + 1, kRedSlices), 256, 0, s>>>(
+    k_reduce_parts<<<dim3(RB3 + RB2 + RB1 + 1, (unsigned)pl->L.nslice), 256, 0, s>>>(
         pl->part_out, nbo, pl->part_w2, pl->part_w1, nbw, pl->gred, pl->lossp, (int)pl->L.nb_loss, pl->losst);
     float* grad = grad_out ? grad_out : pl->gradbuf;
     const float c1 = lr > 0.f ? (float)(1.0 - std::pow(0.9, step)) : 1.f,
                 c2 = lr > 0.f ? (float)(1.0 - std::pow(0.999, step)) : 1.f;
-    k_grad_adam<<<(NPARAM + 63) / 64, 64, 0, s>>>(pl->gred, grad, params, adam_m, adam_v, lr, 0.9f, 0.999f, 1e-8f, c1,
+    k_grad_adam<<<(NPARAM + 63) / 64, 64, 0, s>>>(pl->gred, (int)pl->L.nslice, grad, params, adam_m, adam_v, lr, 0.9f, 0.999f, 1e-8f, c1,
                                                   c2);
   }
   RECON_TRY(check_launch(pl, "network training step"));

@@ -587,7 +587,7 @@ __global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict_
 // at 128^3.  (One thread per column over all rows, 8,192 of them in layer 3, was 3.87 of a 4.84 ms
 // training step: three launches of 2 to 28 blocks, one dependent FP64 add after another.)  The last
 // column block's first slice sums the loss.
-constexpr int kRedSlices = 16;
+constexpr int kRedSlices = 16;   // at most; one per 64 rows
 constexpr int COL3 = K2 + 1, COL2 = CH * (K2 + 1), COL1 = CH * (K1P + 1), NCOLS = COL3 + COL2 + COL1;
 constexpr int RB3 = (COL3 + 63) / 64, RB2 = (COL2 + 63) / 64, RB1 = (COL1 + 63) / 64;
 __global__ void __launch_bounds__(256) k_reduce_parts(const float* __restrict__ p3, long long n3r,
@@ -611,7 +611,7 @@ __global__ void __launch_bounds__(256) k_reduce_parts(const float* __restrict__ 
   if (cb >= RB3) { cb -= RB3; p = p2; rows = nwr; ncols = COL2; base = COL3; }
   if (base && cb >= RB2) { cb -= RB2; p = p1; ncols = COL1; base = COL3 + COL2; }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = cb * 64 + lane;
-  const long long lo = rows * blockIdx.y / kRedSlices, hi = rows * (blockIdx.y + 1) / kRedSlices;
+  const long long lo = rows * blockIdx.y / gridDim.y, hi = rows * (blockIdx.y + 1) / gridDim.y;
   double s[4] = {0.0, 0.0, 0.0, 0.0};
   if (col < ncols) {
     long long i = lo + wave;
@@ -629,7 +629,7 @@ __global__ void __launch_bounds__(256) k_reduce_parts(const float* __restrict__ 
 
 // Gradient in the parameter layout from the sliced sums and, with lr > 0, the Adam update (Kingma & Ba
 // 2015) with bias correction, step counted from 1 (c1 = 1 - beta1^step, c2 = 1 - beta2^step).
-__global__ void __launch_bounds__(64) k_grad_adam(const double* __restrict__ red, float* __restrict__ grad,
+__global__ void __launch_bounds__(64) k_grad_adam(const double* __restrict__ red, int slices, float* __restrict__ grad,
                                                   float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
                                                   float lr, float b1, float b2, float eps, float c1, float c2) {
   const int e = blockIdx.x * 64 + threadIdx.x;
@@ -640,9 +640,13 @@ __global__ void __launch_bounds__(64) k_grad_adam(const double* __restrict__ red
   else if (e < OFF_B2) col = COL3 + ((e - OFF_W2) / K2) * (K2 + 1) + (e - OFF_W2) % K2;
   else if (e < OFF_W3) col = COL3 + (e - OFF_B2) * (K2 + 1) + K2;
   else col = e - OFF_W3;                                   // W3 (432) then b3 (entry 432)
-  double s = 0.0;
+  double s4[4] = {0.0, 0.0, 0.0, 0.0};                     // four loads in flight
+  for (int k = 0; k < slices; k += 4) {
 #pragma unroll
-  for (int k = 0; k < kRedSlices; ++k) s += red[(long long)k * NCOLS + col];
+    for (int i = 0; i < 4; ++i)
+      if (k + i < slices) s4[i] += red[(long long)(k + i) * NCOLS + col];
+  }
+  const double s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
   const float gr = (float)s;
   grad[e] = gr;
   if (lr > 0.f) {

@@ -77,7 +77,9 @@ __device__ __forceinline__ long long ceil_div_ll(long long a, long long b) { ret
 // ---------------------------------------------------------------------------
 // Fill, deposit, totals, mask
 // ---------------------------------------------------------------------------
-__global__ void k_fill_u64(unsigned long long* p, long long count) {
+// (zero_too: one more int to clear, or null)
+__global__ void k_fill_u64(unsigned long long* p, long long count, int* zero_too = nullptr) {
+  if (zero_too && blockIdx.x == 0 && threadIdx.x == 0) *zero_too = 0;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < count;
        i += (long long)gridDim.x * blockDim.x)
     p[i] = 0ull;
@@ -238,7 +240,7 @@ __device__ __forceinline__ long long brick_of_block() {
   const long long nblk = gridDim.x;
   return (nblk & 7) ? (long long)blockIdx.x : (long long)(blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
 }
-constexpr int kLdsBins = 32768;   // bins a block histograms in LDS (128 KB)
+constexpr int kLdsBins = 32768;   // most bins a block histograms in LDS (128 KB)
 
 // Cell coordinate of an object; false for a non-finite / far position or a bad weight.
 __device__ __forceinline__ bool cic_locate(float px, float py, float pz, float wv, const CicGeo& g, int ii[3],
@@ -289,82 +291,53 @@ __device__ __forceinline__ void load_objects(const float* __restrict__ pos, cons
   }
 }
 
-__global__ void __launch_bounds__(256) k_bin_count(const float* __restrict__ pos, const float* __restrict__ w,
-                                                   long long n, const long long* __restrict__ off, int batch,
-                                                   CicGeo g, unsigned* __restrict__ counts, int* __restrict__ err) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    int ii[3];
-    unsigned long long tau[3];
-    if (!cic_locate(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], w ? w[i] : 1.0f, g, ii, tau)) {
-      atomicAdd(err, 1);
-      continue;
-    }
-    const int b = off ? find_realisation(off, batch, i) : 0;
-    atomicAdd(counts + brick_key(ii, g.n, b), 1u);
-  }
-}
-
-__global__ void __launch_bounds__(256) k_bin_scatter(const float* __restrict__ pos, const float* __restrict__ w,
-                                                     long long n, const long long* __restrict__ off, int batch,
-                                                     CicGeo g, unsigned* __restrict__ cursor,
-                                                     float4* __restrict__ sorted, unsigned* __restrict__ slot_of) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    int ii[3];
-    unsigned long long tau[3];
-    const float px = pos[3 * i], py = pos[3 * i + 1], pz = pos[3 * i + 2], wv = w ? w[i] : 1.0f;
-    if (!cic_locate(px, py, pz, wv, g, ii, tau)) {
-      slot_of[i] = 0xFFFFFFFFu;   // not in the sorted copy
-      continue;
-    }
-    const int b = off ? find_realisation(off, batch, i) : 0;
-    const unsigned slot = atomicAdd(cursor + brick_key(ii, g.n, b), 1u);
-    sorted[slot] = make_float4(px, py, pz, wv);
-    slot_of[i] = slot;
-  }
-}
-
 // Count with a per-block LDS histogram over the bins of the realisation that owns the
 // chunk's first object; one global atomic per (block, non-empty bin).  Objects whose bin
 // lies outside that window (a chunk crossing realisations) use a direct global atomic.
-// The block's histogram is also stored in bhist[block][bin] (when not null), so that the scatter,
+// The invalid objects of the block go to errblk[block], which the scan adds up.
+// The block's histogram is also stored in bhist[block][bin], so that the scatter,
 // which splits the catalogue into the same chunks, need not count again.
 // First brick key of the LDS window of the binning block that takes objects [lo, ...): the block's
-// realisation when all of its bricks fit (every size up to 512^3); above that, kLdsBins bricks centred
+// realisation when all of its bricks fit (every size up to 512^3); above that, kBins bricks centred
 // on the brick of the chunk's first object, inside its realisation, so that a catalogue stored in
 // spatial order (a lattice formed plane by plane) keeps each block's objects in its window.  Objects
 // outside the window go to global atomics; the count and the scatter take the same window.
+template <int kBins>
 __device__ __forceinline__ long long bin_window(const float* __restrict__ pos, long long lo,
                                                 const long long* __restrict__ off, int batch, const CicGeo& g) {
   const int nbs = (g.n + kBrick - 1) / kBrick;
   const long long per = (long long)nbs * nbs * nbs;
   const int b = off ? find_realisation(off, batch, lo) : 0;
   const long long rb = (long long)b * per;
-  if (per <= kLdsBins) return rb;
+  if (per <= kBins) return rb;
   int ii[3];
   unsigned long long tau[3];
   if (!cic_locate(pos[3 * lo], pos[3 * lo + 1], pos[3 * lo + 2], 1.0f, g, ii, tau)) return rb;
-  long long base = brick_key(ii, g.n, b) - kLdsBins / 2;
+  long long base = brick_key(ii, g.n, b) - kBins / 2;
   if (base < rb) base = rb;
-  if (base > rb + per - kLdsBins) base = rb + per - kLdsBins;
+  if (base > rb + per - kBins) base = rb + per - kBins;
   return base;
 }
 
-template <int NT>
+template <int NT, int kBins>
 __global__ void __launch_bounds__(NT) k_bin_count_lds(const float* __restrict__ pos, const float* __restrict__ w,
                                                        long long n, long long chunk,
                                                        const long long* __restrict__ off, int batch, CicGeo g,
-                                                       unsigned* __restrict__ counts, int* __restrict__ err,
+                                                       unsigned* __restrict__ counts, int* __restrict__ errblk,
                                                        unsigned* __restrict__ bhist) {
-  __shared__ unsigned hist[kLdsBins];
+  __shared__ unsigned hist[kBins];
+  __shared__ int bad;
   const long long lo = blockIdx.x * chunk;
-  if (lo >= n) return;
+  if (lo >= n) {                                         // (whole block)
+    if (threadIdx.x == 0) errblk[blockIdx.x] = 0;
+    return;
+  }
   const long long hi = lo + chunk < n ? lo + chunk : n;
   const int nbs = (g.n + kBrick - 1) / kBrick;
   const long long per = (long long)nbs * nbs * nbs;
-  const long long base = bin_window(pos, lo, off, batch, g);
-  for (int i = threadIdx.x; i < kLdsBins; i += NT) hist[i] = 0u;
+  const long long base = bin_window<kBins>(pos, lo, off, batch, g);
+  for (int i = threadIdx.x; i < kBins; i += NT) hist[i] = 0u;
+  if (threadIdx.x == 0) bad = 0;
   __syncthreads();
   constexpr int U = kObjBatch;
   for (long long i0 = lo + threadIdx.x; i0 < hi; i0 += (long long)NT * U) {
@@ -377,59 +350,50 @@ __global__ void __launch_bounds__(NT) k_bin_count_lds(const float* __restrict__ 
       int ii[3];
       unsigned long long tau[3];
       if (!cic_locate(px[u], py[u], pz[u], wv[u], g, ii, tau)) {
-        atomicAdd(err, 1);
+        atomicAdd(&bad, 1);
         continue;
       }
       const int b = off ? find_realisation(off, batch, i) : 0;
       const long long key = brick_key(ii, g.n, b);
       const long long rel = key - base;
-      if (rel >= 0 && rel < kLdsBins) atomicAdd(&hist[rel], 1u);
+      if (rel >= 0 && rel < kBins) atomicAdd(&hist[rel], 1u);
       else atomicAdd(counts + key, 1u);
     }
   }
   __syncthreads();
+  if (threadIdx.x == 0) errblk[blockIdx.x] = bad;
   const long long nb_total = per * batch;
-  for (int i = threadIdx.x; i < kLdsBins; i += NT) {
+  for (int i = threadIdx.x; i < kBins; i += NT) {
     const unsigned c = hist[i];
     if (c && base + i < nb_total) atomicAdd(counts + base + i, c);
-    if (bhist) bhist[(long long)blockIdx.x * kLdsBins + i] = c;
+    bhist[(long long)blockIdx.x * kBins + i] = c;
   }
 }
 
 // Scatter into brick order: each block reserves one contiguous slot range per non-empty
 // bin of its window, then ranks its objects inside the range with LDS atomics.
-template <int NT>
+template <int NT, int kBins>
 __global__ void __launch_bounds__(NT) k_bin_scatter_lds(const float* __restrict__ pos, const float* __restrict__ w,
                                                          long long n, long long chunk,
                                                          const long long* __restrict__ off, int batch, CicGeo g,
                                                          unsigned* __restrict__ cursor, float4* __restrict__ sorted,
                                                          unsigned* __restrict__ slot_of,
-                                                         const unsigned* __restrict__ bhist) {
-  __shared__ unsigned hist[kLdsBins];
+                                                         const unsigned* __restrict__ bhist,
+                                                         unsigned* __restrict__ counts, long long ncounts) {
+  __shared__ unsigned hist[kBins];
+  // the counts are used up (the scan has read them): cleared for the next deposit
+  for (long long i = blockIdx.x * (long long)NT + threadIdx.x; i < ncounts; i += (long long)gridDim.x * NT) counts[i] = 0u;
   const long long lo = blockIdx.x * chunk;
   if (lo >= n) return;
   const long long hi = lo + chunk < n ? lo + chunk : n;
   const int nbs = (g.n + kBrick - 1) / kBrick;
   const long long per = (long long)nbs * nbs * nbs;
-  const long long base = bin_window(pos, lo, off, batch, g);
+  const long long base = bin_window<kBins>(pos, lo, off, batch, g);
   const long long nb_total = per * batch;
-  if (bhist) {
-    // the count kernel's histogram of this very chunk
-    for (int i = threadIdx.x; i < kLdsBins; i += NT) hist[i] = bhist[(long long)blockIdx.x * kLdsBins + i];
-  } else {
-    for (int i = threadIdx.x; i < kLdsBins; i += NT) hist[i] = 0u;
-    __syncthreads();
-    for (long long i = lo + threadIdx.x; i < hi; i += NT) {
-      int ii[3];
-      unsigned long long tau[3];
-      if (!cic_locate(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], w ? w[i] : 1.0f, g, ii, tau)) continue;
-      const int b = off ? find_realisation(off, batch, i) : 0;
-      const long long rel = brick_key(ii, g.n, b) - base;
-      if (rel >= 0 && rel < kLdsBins) atomicAdd(&hist[rel], 1u);
-    }
-  }
+  // the count kernel's histogram of this very chunk
+  for (int i = threadIdx.x; i < kBins; i += NT) hist[i] = bhist[(long long)blockIdx.x * kBins + i];
   __syncthreads();
-  for (int i = threadIdx.x; i < kLdsBins; i += NT) {
+  for (int i = threadIdx.x; i < kBins; i += NT) {
     const unsigned c = hist[i];
     if (c && base + i < nb_total) hist[i] = atomicAdd(cursor + base + i, c);
   }
@@ -451,15 +415,16 @@ __global__ void __launch_bounds__(NT) k_bin_scatter_lds(const float* __restrict_
       const int b = off ? find_realisation(off, batch, i) : 0;
       const long long key = brick_key(ii, g.n, b);
       const long long rel = key - base;
-      const unsigned slot = (rel >= 0 && rel < kLdsBins) ? atomicAdd(&hist[rel], 1u) : atomicAdd(cursor + key, 1u);
+      const unsigned slot = (rel >= 0 && rel < kBins) ? atomicAdd(&hist[rel], 1u) : atomicAdd(cursor + key, 1u);
       sorted[slot] = make_float4(px[u], py[u], pz[u], wv[u]);
       slot_of[i] = slot;
     }
   }
 }
 
-// Exclusive scan of uint32 counts in three kernels: block totals, scan of the totals, apply.
+// Totals of runs of 256 * kScanItems counts (only where there are more than kScanDirect of them).
 constexpr int kScanItems = 16;
+constexpr long long kScanDirect = 65536;
 __global__ void __launch_bounds__(256) k_scan_blocks(const unsigned* __restrict__ in, long long n,
                                                      unsigned* __restrict__ bsum) {
   const long long base = (long long)blockIdx.x * 256 * kScanItems;
@@ -476,54 +441,72 @@ __global__ void __launch_bounds__(256) k_scan_blocks(const unsigned* __restrict_
   if (threadIdx.x == 0) bsum[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
 }
 
-// In-place exclusive scan of nb block totals by one block.
-__global__ void __launch_bounds__(256) k_scan_top(unsigned* __restrict__ bsum, int nb) {
-  __shared__ unsigned sh[256];
-  unsigned carry = 0;
-  for (int base = 0; base < nb; base += 256) {
-    const int i = base + threadIdx.x;
-    const unsigned v = i < nb ? bsum[i] : 0u;
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      unsigned t = threadIdx.x >= o ? sh[threadIdx.x - o] : 0u;
-      __syncthreads();
-      sh[threadIdx.x] += t;
-      __syncthreads();
-    }
-    if (i < nb) bsum[i] = carry + sh[threadIdx.x] - v;
-    carry += sh[255];
-    __syncthreads();
+// Exclusive scan of the counts by one block of 256 threads per run of 256 * kScanItems: out[i] = sum of
+// in[0..i) (n + 1 entries; out[n] = total), cursor = copy of out[0..n).  What comes before the run is
+// added up by the block itself, from the counts (bsum null; at most kScanDirect of them, a few loads per
+// thread) or from the runs' totals.  Each thread scans kScanItems consecutive counts, the threads' sums
+// are scanned with lane shuffles: 3 us, where three launches with a 256-wide scan in LDS (16 barriers) for
+// every 256 counts took 20 us at any size.
+__device__ __forceinline__ void scan_run(const unsigned* __restrict__ in, long long n,
+                                         const unsigned* __restrict__ bsum, long long run,
+                                         unsigned* __restrict__ out, unsigned* __restrict__ cursor) {
+  __shared__ unsigned ws[2][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long long first = run * 256 * kScanItems;
+  unsigned before = 0;
+  if (bsum) {
+    for (long long i = threadIdx.x; i < run; i += 256) before += bsum[i];
+  } else {
+    for (long long i = threadIdx.x; i < first; i += 256) before += in[i];
   }
-}
-
-// out[i] = exclusive prefix of in (out has n + 1 entries; out[n] = total); cursor = copy of out[0..n).
-__global__ void __launch_bounds__(256) k_scan_apply(const unsigned* __restrict__ in, long long n,
-                                                    const unsigned* __restrict__ bsum, unsigned* __restrict__ out,
-                                                    unsigned* __restrict__ cursor) {
-  __shared__ unsigned sh[256];
-  const long long base = (long long)blockIdx.x * 256 * kScanItems;
-  unsigned carry = bsum[blockIdx.x];
+  const long long i0 = first + (long long)threadIdx.x * kScanItems;
+  unsigned v[kScanItems], sum = 0;
+#pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
-    const long long i = base + (long long)k * 256 + threadIdx.x;
-    const unsigned v = i < n ? in[i] : 0u;
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      unsigned t = threadIdx.x >= o ? sh[threadIdx.x - o] : 0u;
-      __syncthreads();
-      sh[threadIdx.x] += t;
-      __syncthreads();
+    v[k] = i0 + k < n ? in[i0 + k] : 0u;
+    sum += v[k];
+  }
+  unsigned inc = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned t = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += t;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+  if (lane == 63) { ws[0][wave] = inc; ws[1][wave] = before; }
+  __syncthreads();
+  unsigned ex = ws[1][0] + ws[1][1] + ws[1][2] + ws[1][3] + inc - sum;
+  for (int w = 0; w < wave; ++w) ex += ws[0][w];
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    if (i0 + k < n) {
+      out[i0 + k] = ex;
+      cursor[i0 + k] = ex;
+      ex += v[k];
+      if (i0 + k == n - 1) out[n] = ex;
     }
-    const unsigned ex = carry + sh[threadIdx.x] - v;
-    if (i < n) { out[i] = ex; cursor[i] = ex; }
-    if (i == n - 1) out[n] = ex + v;
-    carry += sh[255];
-    __syncthreads();
   }
 }
 
-// One block per brick: LDS accumulation of the (BS+1)^3 footprint, then a flush with
+// Part blockIdx.y of a brick's objects [lo, hi): the launch has gridDim.y blocks per brick, of which a
+// brick uses as many as leave each at least kPartObjects objects.  False for a block with no part.
+constexpr unsigned kPartObjects = 1024;
+__device__ __forceinline__ bool brick_part(unsigned& lo, unsigned& hi) {
+  const unsigned cnt = hi - lo;
+  if (cnt == 0) return false;
+  if (gridDim.y > 1) {
+    unsigned parts = (cnt + kPartObjects - 1) / kPartObjects;
+    if (parts > gridDim.y) parts = gridDim.y;
+    if (blockIdx.y >= parts) return false;
+    const unsigned first = lo;
+    lo = first + (unsigned)((unsigned long long)cnt * blockIdx.y / parts);
+    hi = first + (unsigned)((unsigned long long)cnt * (blockIdx.y + 1) / parts);
+  }
+  return true;
+}
+
+// One block per brick (or several, brick_part): LDS accumulation of the (BS+1)^3 footprint, then a flush with
 // 64-bit atomics (bricks overlap by one cell on their upper faces).  NT threads walk the brick's
 // objects side by side (a brick of the survey's randoms holds about 8,700 of them).
 template <int NT>
@@ -533,8 +516,8 @@ __global__ void __launch_bounds__(NT) k_brick_deposit(const float4* __restrict__
   constexpr int T = kBrick + 1;
   __shared__ unsigned long long acc[T * T * T];
   const long long key = brick_of_block();
-  const unsigned lo = start[key], hi = start[key + 1];
-  if (lo == hi) return;
+  unsigned lo = start[key], hi = start[key + 1];
+  if (!brick_part(lo, hi)) return;
   const int nbs = (g.n + kBrick - 1) / kBrick;
   const long long per = (long long)nbs * nbs * nbs;
   const int b = (int)(key / per);
@@ -590,12 +573,11 @@ __global__ void __launch_bounds__(NT) k_brick_deposit(const float4* __restrict__
 //   2 (densify):    clear every brick that is not valid, valid = 1 (before a deposit that does not go
 //                   through the bricks)
 // Requires n to be a multiple of the brick size.
-__global__ void __launch_bounds__(256) k_brick_prepare(const unsigned* __restrict__ count, int n, int mode,
-                                                       unsigned char* __restrict__ valid,
-                                                       unsigned long long* __restrict__ grid) {
+__device__ __forceinline__ void brick_prepare(const unsigned* __restrict__ count, int n, int mode, long long key,
+                                              unsigned char* __restrict__ valid,
+                                              unsigned long long* __restrict__ grid) {
   const int nbs = n / kBrick;
   const long long per = (long long)nbs * nbs * nbs;
-  const long long key = blockIdx.x;
   const int b = (int)(key / per);
   const long long kk = key - (long long)b * per;
   const int bx = (int)(kk % nbs), by = (int)((kk / nbs) % nbs), bz = (int)(kk / ((long long)nbs * nbs));
@@ -622,6 +604,36 @@ __global__ void __launch_bounds__(256) k_brick_prepare(const unsigned* __restric
     }
   }
   if (threadIdx.x == 0) valid[key] = (unsigned char)(mode == 0 ? touched : (mode == 1 ? (was || touched) : 1));
+}
+
+__global__ void __launch_bounds__(256) k_brick_prepare(const unsigned* __restrict__ count, int n, int mode,
+                                                       unsigned char* __restrict__ valid,
+                                                       unsigned long long* __restrict__ grid) {
+  brick_prepare(count, n, mode, blockIdx.x, valid, grid);
+}
+
+// The scan of the brick counts (the first `runs` blocks) and, when valid is given, the preparation of the
+// grid's bricks (one block each after those), which both only read the counts, in one launch.
+__global__ void __launch_bounds__(256) k_scan_prepare(const unsigned* __restrict__ count, long long nbins,
+                                                      const unsigned* __restrict__ bsum, int runs,
+                                                      unsigned* __restrict__ out, unsigned* __restrict__ cursor, int n,
+                                                      int mode, unsigned char* __restrict__ valid,
+                                                      unsigned long long* __restrict__ grid,
+                                                      const int* __restrict__ errblk, int nerr, int* __restrict__ err,
+                                                      int fresh) {
+  if (blockIdx.x == 0) {
+    // invalid objects of this deposit: replace the grid's count (new grid) or add to it
+    __shared__ int bad;
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+    int mine = 0;
+    for (int i = threadIdx.x; i < nerr; i += 256) mine += errblk[i];
+    if (mine) atomicAdd(&bad, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) *err = (fresh ? 0 : *err) + bad;
+  }
+  if ((int)blockIdx.x < runs) scan_run(count, nbins, bsum, blockIdx.x, out, cursor);
+  else brick_prepare(count, n, mode, (long long)blockIdx.x - runs, valid, grid);
 }
 
 // Validity of the brick holding cell (x, y, z) of realisation b (null: every brick is valid).
@@ -2166,14 +2178,13 @@ __global__ void __launch_bounds__(256) k_shift(const float* __restrict__ pos, lo
                                                const long long* __restrict__ off, int batch,
                                                const float* __restrict__ psi, CicGeo cg, float ox, float oy,
                                                float oz, float growth, int galaxies, float* __restrict__ disp,
-                                               float* __restrict__ pos_out, int* __restrict__ err) {
+                                               float* __restrict__ pos_out) {
   const long long n3 = (long long)cg.n * cg.n * cg.n;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
     const float px = pos[3 * i], py = pos[3 * i + 1], pz = pos[3 * i + 2];
     float uu[3];
     if (!shift_coords(px, py, pz, cg, uu)) {
-      atomicAdd(err, 1);
 #pragma unroll
       for (int a = 0; a < 3; ++a) disp[3 * i + a] = 0.f;
       continue;
@@ -2205,8 +2216,8 @@ __global__ void __launch_bounds__(NT) k_shift_brick(const float4* __restrict__ s
   constexpr int F = kBrick + 1, F3 = F * F * F;
   __shared__ float px_[F3], py_[F3], pz_[F3];
   const long long key = brick_of_block();
-  const unsigned lo = start[key], hi = start[key + 1];
-  if (lo == hi) return;
+  unsigned lo = start[key], hi = start[key + 1];
+  if (!brick_part(lo, hi)) return;
   const int n = cg.n, m = n - 1;
   const int nbs = (n + kBrick - 1) / kBrick;
   const long long per = (long long)nbs * nbs * nbs;
@@ -2255,7 +2266,7 @@ __global__ void __launch_bounds__(NT) k_shift_brick(const float4* __restrict__ s
 }
 
 // Back to the caller's order: object i takes the displacement of its slot (an object the deposit
-// rejected has no slot: counted in err, displacement 0, as in k_shift).  Consecutive objects of one
+// rejected has no slot: displacement 0, as in k_shift).  Consecutive objects of one
 // scatter chunk have their slots in short runs per brick, so their staged results share lines; the
 // 8 XCDs (workgroups are dealt to them round robin) each take a contiguous eighth of the objects,
 // and a block takes U adjacent 256-object chunks, so that the chunks in flight on one XCD form a
@@ -2264,7 +2275,7 @@ __global__ void __launch_bounds__(NT) k_shift_brick(const float4* __restrict__ s
 __global__ void __launch_bounds__(256) k_shift_unpermute(const unsigned* __restrict__ slot_of,
                                                          const float4* __restrict__ tmp, long long n,
                                                          const float* __restrict__ pos, float* __restrict__ disp,
-                                                         float* __restrict__ pos_out, int* __restrict__ err) {
+                                                         float* __restrict__ pos_out) {
   const long long chunks = (n + 255) / 256, per_x = gridDim.x / 8;
   const int xcd = blockIdx.x % 8;
   const long long c_lo = chunks * xcd / 8, c_hi = chunks * (xcd + 1) / 8;
@@ -2286,7 +2297,6 @@ __global__ void __launch_bounds__(256) k_shift_unpermute(const unsigned* __restr
       const long long i = c * 256 + threadIdx.x;
       if (c >= c_hi || i >= n) continue;
       const float4 d = dd[u];
-      if (sl[u] >= n) atomicAdd(err, 1);
       disp[3 * i] = d.x;
       disp[3 * i + 1] = d.y;
       disp[3 * i + 2] = d.z;

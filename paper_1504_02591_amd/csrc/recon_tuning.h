@@ -87,8 +87,7 @@
 // (fan-out 6.25 -> 7.05 ms, fan-in 5.88 -> 6.90 ms) while the z and x passes gained (8.80 -> 8.32,
 // 6.09 -> 5.95 ms): the y passes hint their loads only at tiles of 16 columns or more.
 // Binning above 512^3 (more bricks than one LDS histogram holds): per-block windows of the LDS
-// histogram centred on the chunk's first object (RECON_BIN_WINDOW=1) instead of global atomics for
-// every object: 1024^3 precision-study reconstruction (1.07e9 lattice particles) 773.7 -> 631.8 ms.
+// histogram centred on the chunk's first object instead of global atomics for every object: 1024^3 precision-study reconstruction (1.07e9 lattice particles) 773.7 -> 631.8 ms.
 #ifndef RECON_X_WAVES
 #define RECON_X_WAVES 0
 #endif
@@ -106,7 +105,4 @@
 #endif
 #ifndef RECON_STREAM
 #define RECON_STREAM 3
-#endif
-#ifndef RECON_BIN_WINDOW
-#define RECON_BIN_WINDOW 1
 #endif

@@ -94,3 +94,82 @@ def test_training_gradient_against_64_bits(gpu_lib, m, batch):
         print(f"m={m} batch={batch} grad {name}: rel L2 {e:.2e}", flush=True)
         assert e < 5e-3, name
         off += size
+
+
+def clumped(n, box, m, seed):
+    """Positions over the box and beyond it, a third of them inside one cell, some on nodes and faces."""
+    rng = np.random.default_rng(seed)
+    pos = (rng.random((m, 3)) * 1.1 * box - 0.05 * box).astype(np.float32)
+    k = m // 3
+    pos[:k] = ((rng.random((k, 3)) * 0.9 + n // 2 + 0.05) * (box / n)).astype(np.float32)
+    faces = np.array([[i & 1, (i >> 1) & 1, i >> 2] for i in range(8)], dtype=np.float32) * np.float32(box)
+    pos[k:k + 8] = faces[:m - k]
+    return pos, (rng.random(m) * 3).astype(np.float32)
+
+
+# histogram sizes (512, 4096, 32768 bins; more: windows), one or several binning blocks, bricks split into
+# parts (32^3 to 256^3) or not, scans with and without run totals (more than 65,536 bricks)
+@pytest.mark.parametrize("n,batch,m", [(8, 1, 5000), (16, 3, 1023), (32, 1, 1), (32, 1, 2049), (32, 1, 60001),
+                                       (32, 65, 40000), (64, 1, 100003), (128, 1, 4097), (128, 9, 30011),
+                                       (256, 1, 70001), (256, 17, 50021)])
+def test_binned_deposit_and_shift_match_the_direct_ones(gpu_lib, n, batch, m):
+    from paper_1504_02591_amd import native
+    box = 10.0 * n
+    pos, w = clumped(n, box, m, 7 * n + batch)
+    rng = np.random.default_rng(3)
+    cuts = np.sort(rng.integers(0, m + 1, batch - 1))
+    off = None if batch == 1 else torch.tensor(np.concatenate([[0], cuts, [m]]), device=dev())
+    pos, w = torch.from_numpy(pos).to(dev()), torch.from_numpy(w).to(dev())
+    kw = dict(box_len=box, observer=(-300.0, 4.0 * n, 7.0 * n), bias=1.5, growth=0.8, smooth_r=10.0, randoms=False,
+              batch=batch)
+    direct, binned = native.Plan(n, **kw), native.Plan(n, max_objects=m, **kw)
+    for weights in (w, None):
+        for plan in (direct, binned):
+            plan.paint(native.GAL, pos, weights, off)
+        assert torch.equal(direct.grid(native.GAL), binned.grid(native.GAL))
+    for plan in (direct, binned):                      # a second deposit on top
+        plan.paint(native.GAL, pos, w, off, accumulate=True)
+    assert torch.equal(direct.grid(native.GAL), binned.grid(native.GAL))
+    if batch * n ** 3 <= 16 * 128 ** 3:                # the shift of the brick-ordered copy, any displacement
+        psi = field(n, 1).repeat(batch, 1, 1, 1)
+        for plan in (direct, binned):
+            plan.set_delta(psi)
+            plan.solve()
+            plan.iterate(1, 0.0)
+        assert torch.equal(direct.shift(native.GAL, pos, off), binned.shift(native.GAL, pos, off))
+    direct.close()
+    binned.close()
+
+
+def test_invalid_objects_are_counted_per_grid(gpu_lib):
+    # an invalid object makes solve refuse until its grid is painted anew; an accumulating deposit keeps
+    # the refusal, and a valid one on top does not lift it
+    from paper_1504_02591_amd import native
+    n, m = 32, 5000
+    pos, _ = clumped(n, 320.0, m, 5)
+    good = torch.from_numpy(pos).to(dev())
+    bad = good.clone()
+    bad[m - 1, 1] = float("nan")
+    plan = native.Plan(n, 320.0, (-300.0, 0.0, 0.0), 1.0, 0.5, 20.0, randoms=False, max_objects=m)
+
+    def refused():
+        try:
+            plan.solve()
+        except native.ReconError as e:
+            assert e.code == native.RECON_EINVAL and "1 objects" in str(e)
+            return True
+        return False
+
+    plan.paint(native.GAL, bad)
+    assert refused() and refused()
+    plan.paint(native.GAL, good, accumulate=True)
+    assert refused()
+    plan.paint(native.GAL, good)
+    assert not refused()
+    plan.paint(native.GAL, good)
+    plan.paint(native.GAL, bad, accumulate=True)
+    assert refused()
+    plan.paint(native.GAL, good[:0])
+    plan.paint(native.GAL, good, accumulate=True)
+    assert not refused()
+    plan.close()
