@@ -1207,9 +1207,14 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
   const bool first = which == RECON_GAL ? !pl->painted_g : !pl->painted_r;
   int* errc = pl->err + which;   // invalid-object counter of this grid
   const bool fresh = !(flags & RECON_PAINT_ACCUMULATE) || first;
-  const bool binned = n > 0 && !(flags & RECON_PAINT_NGP) && n <= pl->p.max_objects;
   // brick-sparse grid: bricks tile the grid and the brick buffers exist
   const bool can_sparse = pl->L.nbins > 0 && pl->n >= 2 * kBrick;
+  // A nearest-grid-point deposit goes through the bricks too where the grid is large enough that clearing
+  // and reading it whole costs more than the binning (from 128^3 on), unless the brick-ordered copy of a
+  // cloud-in-cell deposit, which a later shift may name, would be lost.  Its own copy is not one that
+  // RECON_SHIFT_AS_PAINTED may name.
+  const bool ngp = (flags & RECON_PAINT_NGP) != 0;
+  const bool binned = n > 0 && n <= pl->p.max_objects && (!ngp || (pl->n >= 128 && pl->srt_which < 0));
   unsigned char* valid = which == RECON_GAL ? pl->bvalid_g : pl->bvalid_r;
   bool& sparse = which == RECON_GAL ? pl->sparse_g : pl->sparse_r;
   if (fresh) {
@@ -1227,7 +1232,7 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
     RECON_TRY(check_launch(pl, "brick densify"));
     sparse = false;
   }
-  if (n > 0 && (flags & RECON_PAINT_NGP)) {
+  if (n > 0 && ngp && !binned) {
     long long blocks = (n + kThreads - 1) / kThreads;
     if (blocks > 8192) blocks = 8192;
     {
@@ -1246,14 +1251,21 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
     if (prep >= 0) sparse = true;
     {
       PROF(pl, KP_PAINT);
-      k_brick_deposit<RECON_BRICK_NT><<<dim3((unsigned)nb, brick_parts(nb)), RECON_BRICK_NT, 0, pl->stream>>>(
-          pl->sorted, pl->bstart, pl->cic, (unsigned long long*)grid);
+      const dim3 blocks((unsigned)nb, brick_parts(nb));
+      if (ngp)
+        k_brick_deposit<RECON_BRICK_NT, true><<<blocks, RECON_BRICK_NT, 0, pl->stream>>>(
+            pl->sorted, pl->bstart, pl->cic, (unsigned long long*)grid);
+      else
+        k_brick_deposit<RECON_BRICK_NT, false><<<blocks, RECON_BRICK_NT, 0, pl->stream>>>(
+            pl->sorted, pl->bstart, pl->cic, (unsigned long long*)grid);
     }
     RECON_TRY(check_launch(pl, "brick deposit"));
-    pl->srt_which = which;
-    pl->srt_pos = pos;
-    pl->srt_n = n;
-    pl->srt_off = offsets;
+    if (!ngp) {
+      pl->srt_which = which;
+      pl->srt_pos = pos;
+      pl->srt_n = n;
+      pl->srt_off = offsets;
+    }
   } else if (n > 0) {
     long long blocks = (n + kThreads - 1) / kThreads;
     if (blocks > 8192) blocks = 8192;
@@ -1698,8 +1710,17 @@ int recon_shift(recon_plan_t* pl, int which_flags, const float* pos, int64_t n, 
   Marker mark(which == RECON_GAL ? "a10 shift (galaxies)" : "a10 shift (randoms)");
   long long blocks = (n + kThreads - 1) / kThreads;
   if (blocks > 8192) blocks = 8192;
-  if (as_painted) {
-    // the catalogue painted last through the bricks: shift its brick-ordered copy, then reorder
+  // A catalogue that is not in brick order is put there first where that is cheaper than gathering the
+  // displacement object by object: the displacement is larger than the L2s (from 256^3 on), there are
+  // objects enough per brick (staging a brick's footprint costs about as much as 20 objects' gathers), and
+  // the brick-ordered copy of a deposit is not in the way.
+  const bool bin_first = !as_painted && pl->srt_which < 0 && n <= pl->p.max_objects && pl->n >= 256 &&
+                         n >= 32 * pl->L.nbins && n >= (1 << 18);
+  if (bin_first) {
+    RECON_TRY(bin_objects(pl, pos, nullptr, n, (const long long*)offsets, -1, nullptr, nullptr, pl->err + 2, true));
+  }
+  if (as_painted || bin_first) {
+    // shift the brick-ordered copy, then reorder
     {
       PROF(pl, KP_SHIFT);
       k_shift_brick<512><<<dim3((unsigned)pl->L.nbins, brick_parts(pl->L.nbins)), 512, 0, pl->stream>>>(

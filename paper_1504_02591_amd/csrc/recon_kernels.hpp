@@ -509,7 +509,8 @@ __device__ __forceinline__ bool brick_part(unsigned& lo, unsigned& hi) {
 // One block per brick (or several, brick_part): LDS accumulation of the (BS+1)^3 footprint, then a flush with
 // 64-bit atomics (bricks overlap by one cell on their upper faces).  NT threads walk the brick's
 // objects side by side (a brick of the survey's randoms holds about 8,700 of them).
-template <int NT>
+// NGP: the whole weight on the nearest node (k_paint_ngp's rule), which lies in the same footprint.
+template <int NT, bool NGP>
 __global__ void __launch_bounds__(NT) k_brick_deposit(const float4* __restrict__ sorted,
                                                       const unsigned* __restrict__ start, CicGeo g,
                                                       unsigned long long* __restrict__ grid) {
@@ -542,6 +543,12 @@ __global__ void __launch_bounds__(NT) k_brick_deposit(const float4* __restrict__
       cic_locate(r.x, r.y, r.z, r.w, g, ii, tau);
       const unsigned long long wq = (unsigned long long)__double2ll_rn((double)r.w * 4294967296.0);
       const int lx = ii[0] - bx * kBrick, ly = ii[1] - by * kBrick, lz = ii[2] - bz * kBrick;
+      if constexpr (NGP) {
+        // the fraction t is at least 1/2 exactly when floor(2^16 t) is at least 2^15
+        const int ux = lx + (tau[0] >= 32768u), uy = ly + (tau[1] >= 32768u), uz = lz + (tau[2] >= 32768u);
+        if (wq) atomicAdd(&acc[(uz * T + uy) * T + ux], wq);
+        continue;
+      }
       unsigned long long share[8];
       cic_shares(wq, tau, share);
 #pragma unroll
@@ -2297,13 +2304,18 @@ __global__ void __launch_bounds__(256) k_shift_unpermute(const unsigned* __restr
       const long long i = c * 256 + threadIdx.x;
       if (c >= c_hi || i >= n) continue;
       const float4 d = dd[u];
+      float q[3] = {0.f, 0.f, 0.f};
+      if (pos_out) {                                         // (read before disp is written, which may be pos)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) q[a] = pos[3 * i + a];
+      }
       disp[3 * i] = d.x;
       disp[3 * i + 1] = d.y;
       disp[3 * i + 2] = d.z;
       if (pos_out) {
-        pos_out[3 * i] = __fadd_rn(pos[3 * i], d.x);
-        pos_out[3 * i + 1] = __fadd_rn(pos[3 * i + 1], d.y);
-        pos_out[3 * i + 2] = __fadd_rn(pos[3 * i + 2], d.z);
+        pos_out[3 * i] = __fadd_rn(q[0], d.x);
+        pos_out[3 * i + 1] = __fadd_rn(q[1], d.y);
+        pos_out[3 * i + 2] = __fadd_rn(q[2], d.z);
       }
     }
   }

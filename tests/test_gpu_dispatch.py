@@ -173,3 +173,91 @@ def test_invalid_objects_are_counted_per_grid(gpu_lib):
     plan.paint(native.GAL, good, accumulate=True)
     assert not refused()
     plan.close()
+
+
+# nearest-grid-point deposits: through the bricks from 128^3 on (weights, ragged batches, on top of and
+# under cloud-in-cell deposits), per-object atomics below
+@pytest.mark.parametrize("n,batch,m", [(64, 1, 3001), (128, 1, 1), (128, 1, 20011), (128, 9, 30011), (256, 1, 70001)])
+def test_ngp_deposit_through_the_bricks_matches_the_direct_one(gpu_lib, n, batch, m):
+    from paper_1504_02591_amd import native
+    box = 10.0 * n
+    pos, w = clumped(n, box, m, n + batch)
+    k = m // 5                                           # exactly half-way, a hair below and above, and t = 1
+    pos[:k] = (np.floor(pos[:k] / 10.0) + 0.5) * 10.0
+    pos[:k // 3, 0] = np.nextafter(pos[:k // 3, 0], np.float32(0))
+    pos[k // 3:k // 2, 1] = -1e-9
+    rng = np.random.default_rng(3)
+    cuts = np.sort(rng.integers(0, m + 1, batch - 1))
+    off = None if batch == 1 else torch.tensor(np.concatenate([[0], cuts, [m]]), device=dev())
+    pos, w = torch.from_numpy(pos).to(dev()), torch.from_numpy(w).to(dev())
+    kw = dict(box_len=box, observer=(-300.0, 4.0 * n, 7.0 * n), bias=1.5, growth=0.8, smooth_r=10.0, randoms=False,
+              batch=batch)
+    direct, binned = native.Plan(n, **kw), native.Plan(n, max_objects=m, **kw)
+    for steps in ([(w, True)], [(None, True)], [(w, True), (None, True)], [(w, False), (w, True)],
+                  [(None, True), (w, False)]):
+        for plan in (direct, binned):
+            for i, (weights, ngp) in enumerate(steps):
+                plan.paint(native.GAL, pos, weights, off, accumulate=i > 0, ngp=ngp)
+        assert torch.equal(direct.grid(native.GAL), binned.grid(native.GAL))
+    direct.close()
+    binned.close()
+
+
+@pytest.mark.parametrize("m", [(1 << 18) - 1, 1 << 18, 300007])
+def test_shift_in_brick_order_without_a_deposited_copy(gpu_lib, m):
+    # 256^3, enough objects per brick: the shift bins the catalogue itself; the same bits as object by object
+    from paper_1504_02591_amd import native
+    n = 256
+    box = 10.0 * n
+    pos, _ = clumped(n, box, m, 11)
+    pos[m // 2] = np.inf
+    pos = torch.from_numpy(pos).to(dev())
+    kw = dict(box_len=box, observer=(-300.0, 4.0 * n, 7.0 * n), bias=1.5, growth=0.8, smooth_r=10.0, randoms=False)
+    direct, binned = native.Plan(n, **kw), native.Plan(n, max_objects=m, **kw)
+    d = field(n, 4)
+    out = []
+    for plan in (direct, binned):
+        plan.set_delta(d)
+        plan.solve()
+        plan.iterate(1, 0.0)
+        out.append((plan.shift(native.GAL, pos, want_pos=True), plan.shift(native.RAN, pos)))
+    (a, b) = out
+    ok = torch.isfinite(pos).all(1)
+    assert torch.equal(a[0][0], b[0][0]) and torch.equal(a[1], b[1])
+    assert torch.equal(a[0][1][ok], b[0][1][ok]) and not ok.all() and a[1][~ok].abs().max() == 0
+    # a deposited copy stays what it was: the shift of another catalogue leaves it alone
+    binned.paint(native.GAL, pos[:m // 2])
+    first = pos[:m // 2]
+    binned.paint(native.GAL, first)
+    binned.solve()
+    binned.iterate(1, 0.0)
+    want = binned.shift(native.GAL, first.clone())
+    binned.shift(native.GAL, pos)
+    assert torch.equal(binned.shift(native.GAL, first), want)
+    direct.close()
+    binned.close()
+
+
+def test_ngp_deposit_keeps_the_cic_copy_a_shift_may_name(gpu_lib):
+    import ctypes
+    from paper_1504_02591_amd import native
+    n, m = 128, 5000
+    pos, _ = clumped(n, 1280.0, m, 6)
+    ran = torch.from_numpy(pos).to(dev())
+    gal = torch.from_numpy(clumped(n, 1280.0, m, 8)[0]).to(dev())
+    plan = native.Plan(n, 1280.0, (-300.0, 0.0, 0.0), 1.0, 0.5, 20.0, max_objects=m)
+    plan.paint(native.RAN, ran)
+    plan.paint(native.GAL, gal, ngp=True)
+    plan.solve()
+    plan.iterate(1, 0.0)
+    want, got = plan.shift(native.RAN, ran.clone()), torch.empty_like(ran)
+
+    def named(which, t):
+        return plan.lib.recon_shift(plan.handle, which | native.SHIFT_AS_PAINTED, ctypes.c_void_p(t.data_ptr()), m,
+                                    None, ctypes.c_void_p(got.data_ptr()), None)
+
+    assert named(native.RAN, ran) == native.RECON_OK
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    assert named(native.GAL, gal) == native.RECON_EINVAL   # an NGP deposit's copy is not one to name
+    plan.close()
