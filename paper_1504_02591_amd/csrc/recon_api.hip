@@ -223,11 +223,12 @@ struct Profiler {
 
 }  // namespace
 
-// Small host buffer for the per-pass read-backs of the convergence sums: pinned memory
-// (hipHostMalloc), so that the copy is a direct DMA instead of a staged copy into pageable memory, or
-// ordinary host memory for a plan that may not call HIP allocation routines.
+// Small host buffer for what the host reads back (convergence sums, status): pinned memory
+// (hipHostMalloc) that the reducing kernels write into directly, or ordinary host memory, filled by
+// copies, for a plan that may not call HIP allocation routines.
 struct PinnedDoubles {
   double* p = nullptr;
+  double* dev = nullptr;       // the same memory as kernels address it (null: copies)
   size_t n = 0;
   bool pinned = true;
   PinnedDoubles() = default;
@@ -239,7 +240,7 @@ struct PinnedDoubles {
       if (pinned) (void)hipHostFree(p);
       else delete[] p;
     }
-    p = nullptr;
+    p = dev = nullptr;
     n = 0;
   }
   bool assign(size_t count, double v, bool pin) {
@@ -247,6 +248,7 @@ struct PinnedDoubles {
     pinned = pin;
     if (pin) {
       if (hipHostMalloc((void**)&p, count * sizeof(double), hipHostMallocDefault) != hipSuccess) p = nullptr;
+      if (p && hipHostGetDevicePointer((void**)&dev, p, 0) != hipSuccess) dev = nullptr;
     } else {
       p = new (std::nothrow) double[count];
     }
@@ -255,8 +257,6 @@ struct PinnedDoubles {
     for (size_t i = 0; i < count; ++i) p[i] = v;
     return true;
   }
-  double* data() { return p; }
-  double& operator[](size_t i) { return p[i]; }
 };
 
 // The library's own device scratch for plans that cannot allocate (recon_plan_noalloc): one array per
@@ -342,14 +342,20 @@ struct recon_plan_s {
   std::vector<std::vector<double>> hist;
   std::vector<int> h_fan, h_fin, h_it;
   std::vector<int> up_fan, up_fin, up_it;     // what the device masks hold (empty: not yet uploaded)
-  PinnedDoubles h_red, h_red2;
+  // what the host reads: sums of the pass [2 B] and of a non-gradient start [2 B], the cross sums [2 B],
+  // invalid-object counts [2] and status [B]
+  PinnedDoubles host;
+  double *h_red = nullptr, *h_red2 = nullptr, *h_stat = nullptr;
+  double *hd_red = nullptr, *hd_red2 = nullptr, *hd_stat = nullptr;   // as kernels address them, or null
+  hipEvent_t ev = nullptr;     // what the host waits for, so that work queued behind it is not waited for
   std::string msg;
   Profiler prof;
-  // steady-state pass graph (RECON_PASS_GRAPHS): fan-out, z step, fan-in, x step, norm reduction
+  // steady-state pass graph (RECON_PASS_GRAPHS): z step, fan-in, x step, norm reduction
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t pass_graph = nullptr;
   ~recon_plan_s() {
     for (hipEvent_t e : prof.pool) (void)hipEventDestroy(e);
+    if (ev) (void)hipEventDestroy(ev);
     if (pass_graph) (void)hipGraphExecDestroy(pass_graph);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
   }
@@ -416,6 +422,30 @@ struct ProfScope {
   } while (0)
 
 // ---------------------------------------------------------------------------
+// Reading results back.  Kernels write what the host needs into its pinned buffer; queue_read() records
+// the event after them and wait_read() waits for it, so that what is queued between the two runs while the
+// host waits, reads and queues the next work.  A plan without pinned memory copies instead and waits for
+// its stream.
+// ---------------------------------------------------------------------------
+int queue_read(recon_plan_t* pl, double* to, const double* from, size_t count) {
+  if (pl->hd_red) {
+    HIP_TRY(pl, hipEventRecord(pl->ev, pl->stream));
+  } else {
+    HIP_TRY(pl, hipMemcpyAsync(to, from, count * sizeof(double), hipMemcpyDeviceToHost, pl->stream));
+  }
+  return RECON_OK;
+}
+
+int wait_read(recon_plan_t* pl) {
+  if (pl->hd_red) {
+    HIP_TRY(pl, hipEventSynchronize(pl->ev));
+  } else {
+    HIP_TRY(pl, hipStreamSynchronize(pl->stream));
+  }
+  return RECON_OK;
+}
+
+// ---------------------------------------------------------------------------
 // Per-size launchers
 // ---------------------------------------------------------------------------
 struct Ops {
@@ -424,7 +454,8 @@ struct Ops {
   int (*fanout)(recon_plan_t*, const int*, bool comb);   // comb: combined state Y for the z iteration
   int (*combine)(recon_plan_t*, const int*);              // full state Y -> combined state Y
   int (*ziter)(recon_plan_t*, int mode, const int*);
-  int (*fanin_xiter)(recon_plan_t*, bool first, const int*, float omega);
+  int (*fanin)(recon_plan_t*, const int*);
+  int (*xiter)(recon_plan_t*, bool first, const int*, float omega);
   int (*zfinal)(recon_plan_t*, float* psi, float* u, bool cross, const int*, bool comb);
   int (*refan)(recon_plan_t*, const int*, const float2* d);  // state X again from the spectrum d
   int (*helm)(recon_plan_t*, const float*);  // fan-out of the Helmholtz projection of a real field
@@ -443,8 +474,9 @@ int launch_fill_u64(recon_plan_t* pl, void* p, long long count, int* zero_too = 
 // Scalars, and with randoms the survey mask and its z-tile flags (pl->mflag; tile width tw = 2 wz).
 int scalars_and_mask(recon_plan_t* pl, int nblk_z, int tw) {
   k_scalars<<<pl->batch, 256, 0, pl->stream>>>(pl->tpart, nblk_z, pl->n3, pl->p.mask_tau, pl->randoms ? 1 : 0,
-                                               pl->totals, pl->dscal, pl->thr, pl->status);
+                                               pl->totals, pl->dscal, pl->thr, pl->status, pl->err, pl->hd_stat);
   RECON_TRY(check_launch(pl, "scalars"));
+  if (pl->hd_stat) HIP_TRY(pl, hipEventRecord(pl->ev, pl->stream));    // recon_solve waits for this much
   if (pl->randoms) {
     const unsigned char* v = valid_of(pl, RECON_RAN);
     if (v && tw % kBrick == 0) {
@@ -488,7 +520,7 @@ int log_constant(recon_plan_t* pl, int blocks) {
   if (!(pl->p.flags & RECON_LOGNORMAL) || !pl->delta) return RECON_OK;
   {
     PROF(pl, KP_REDUCE);
-    k_reduce_pairs<<<pl->batch, 1024, 0, pl->stream>>>(pl->partials, blocks, pl->red + 2 * pl->batch);
+    k_reduce_pairs<<<pl->batch, 1024, 0, pl->stream>>>(pl->partials, blocks, pl->red + 2 * pl->batch, nullptr);
   }
   RECON_TRY(check_launch(pl, "reduce (log mean)"));
   long long nb = (pl->n3 * pl->batch + 255) / 256;
@@ -684,20 +716,24 @@ struct SizeOps {
       {
         PROF(pl, KP_REDUCE);
         // every mode other than the plain one runs one tile per block: the same grid
-        k_reduce_pairs<<<pl->batch, 1024, 0, s>>>(pl->partials, (int)gzi<ZI_FFTA>(pl).x, pl->red + 2 * pl->batch);
+        double* host = !pl->hd_red ? nullptr : (mode == ZI_CROSS ? pl->hd_red2 : pl->hd_red + 2 * pl->batch);
+        k_reduce_pairs<<<pl->batch, 1024, 0, s>>>(pl->partials, (int)gzi<ZI_FFTA>(pl).x, pl->red + 2 * pl->batch, host);
       }
       RECON_TRY(check_launch(pl, "reduce (start sums)"));
     }
     return RECON_OK;
   }
 
-  static int fanin_xiter(recon_plan_t* pl, bool first, const int* act, float omega) {
-    hipStream_t s = pl->stream;
+  static int fanin(recon_plan_t* pl, const int* act) {
     {
       PROF(pl, KP_Y_FANIN);
-      k_y_fanin<N><<<gy(pl), dim3(TY), 0, s>>>(pl->w0, pl->w1, pl->geo, act, pl->tw);
+      k_y_fanin<N><<<gy(pl), dim3(TY), 0, pl->stream>>>(pl->w0, pl->w1, pl->geo, act, pl->tw);
     }
-    RECON_TRY(check_launch(pl, "y fan-in"));
+    return check_launch(pl, "y fan-in");
+  }
+
+  static int xiter(recon_plan_t* pl, bool first, const int* act, float omega) {
+    hipStream_t s = pl->stream;
     {
       PROF(pl, KP_X_ITER);
       k_x_iter<N><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->ds, first ? pl->ds : pl->dn, pl->dn,
@@ -706,7 +742,7 @@ struct SizeOps {
     RECON_TRY(check_launch(pl, "x iteration"));
     {
       PROF(pl, KP_REDUCE);
-      k_reduce_pairs<<<pl->batch, 1024, 0, s>>>(pl->partials, (int)gx(pl).x, pl->red);
+      k_reduce_pairs<<<pl->batch, 1024, 0, s>>>(pl->partials, (int)gx(pl).x, pl->red, pl->hd_red);
     }
     return check_launch(pl, "reduce (norm)");
   }
@@ -727,7 +763,7 @@ struct SizeOps {
     if (cross) {
       {
         PROF(pl, KP_REDUCE);
-        k_reduce_pairs<<<pl->batch, 1024, 0, s>>>(pl->partials, (int)gz(pl).x, pl->red + 2 * pl->batch);
+        k_reduce_pairs<<<pl->batch, 1024, 0, s>>>(pl->partials, (int)gz(pl).x, pl->red + 2 * pl->batch, pl->hd_red2);
       }
       RECON_TRY(check_launch(pl, "reduce (cross sum)"));
     }
@@ -735,7 +771,7 @@ struct SizeOps {
   }
 
   static const Ops* table() {
-    static const Ops ops = {setup, setup_delta, fanout, combine, ziter, fanin_xiter, zfinal, refan, helm,
+    static const Ops ops = {setup, setup_delta, fanout, combine, ziter, fanin, xiter, zfinal, refan, helm,
                             (int)((N / 2 + 1) * N / WX), (int)(N * (N / (2 * WZ)))};
     return &ops;
   }
@@ -913,9 +949,9 @@ int pass_graph_launch(recon_plan_t* pl, const Ops* ops) {
       pl->stream = keep;
       return fail(pl, RECON_EDEVICE, "graph capture could not start");
     }
-    rc = ops->fanout(pl, pl->act_fan, true);
-    if (rc == RECON_OK) rc = ops->ziter(pl, ZI_PLAIN, pl->act_it);
-    if (rc == RECON_OK) rc = ops->fanin_xiter(pl, false, pl->act_it, relax_weight(pl));
+    rc = ops->ziter(pl, ZI_PLAIN, pl->act_it);
+    if (rc == RECON_OK) rc = ops->fanin(pl, pl->act_it);
+    if (rc == RECON_OK) rc = ops->xiter(pl, false, pl->act_it, relax_weight(pl));
     const hipError_t ec = hipStreamEndCapture(pl->cap_stream, &graph);
     pl->stream = keep;
     if (rc != RECON_OK) {
@@ -1089,9 +1125,18 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
   pl->h_fan.assign(pl->batch, 0);
   pl->h_fin.assign(pl->batch, 0);
   pl->h_it.assign(pl->batch, 0);
-  if (!pl->h_red.assign(4 * pl->batch, 0.0, pinned) || !pl->h_red2.assign(2 * pl->batch, 0.0, pinned)) {
+  if (!pl->host.assign(7 * (size_t)pl->batch + 2, 0.0, pinned) ||
+      (pinned && hipEventCreateWithFlags(&pl->ev, hipEventDisableTiming) != hipSuccess)) {
     delete pl;
     return RECON_EDEVICE;
+  }
+  pl->h_red = pl->host.p;
+  pl->h_red2 = pl->h_red + 4 * pl->batch;
+  pl->h_stat = pl->h_red2 + 2 * pl->batch;
+  if (pl->host.dev && pl->ev) {
+    pl->hd_red = pl->host.dev;
+    pl->hd_red2 = pl->hd_red + 4 * pl->batch;
+    pl->hd_stat = pl->hd_red2 + 2 * pl->batch;
   }
 
   {
@@ -1310,12 +1355,21 @@ int recon_solve(recon_plan_t* pl, int start, const void* net) {
     if (pl->randoms && !pl->painted_r) return fail(pl, RECON_ESTATE, "randoms were not painted");
     Marker mark("a2-a6 totals, smoothing, mask, overdensity, D_s");
     RECON_TRY(ops->setup(pl));
-    // one read-back: invalid-object counters and the totals status of every realisation
+    // one read-back: invalid-object counters and the totals status of every realisation.  They are known
+    // once the totals are, right after the forward z pass: the rest of the setup runs on while the caller
+    // goes on.
     std::vector<int> st(pl->batch, 0);
     int errs[2] = {0, 0};
-    HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, 2 * sizeof(int), hipMemcpyDeviceToHost, pl->stream));
-    HIP_TRY(pl, hipMemcpyAsync(st.data(), pl->status, sizeof(int) * pl->batch, hipMemcpyDeviceToHost, pl->stream));
-    HIP_TRY(pl, hipStreamSynchronize(pl->stream));
+    if (pl->hd_stat) {
+      RECON_TRY(wait_read(pl));
+      errs[0] = (int)pl->h_stat[0];
+      errs[1] = (int)pl->h_stat[1];
+      for (int b = 0; b < pl->batch; ++b) st[b] = (int)pl->h_stat[2 + b];
+    } else {
+      HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, 2 * sizeof(int), hipMemcpyDeviceToHost, pl->stream));
+      HIP_TRY(pl, hipMemcpyAsync(st.data(), pl->status, sizeof(int) * pl->batch, hipMemcpyDeviceToHost, pl->stream));
+      HIP_TRY(pl, hipStreamSynchronize(pl->stream));
+    }
     const int errcount = errs[0] + (pl->randoms ? errs[1] : 0);
     if (errcount) return fail(pl, RECON_EINVAL, std::to_string(errcount) + " objects had invalid positions or weights");
     for (int b = 0; b < pl->batch; ++b) {
@@ -1385,6 +1439,16 @@ double plain_eps1_bound(double beta, double num0, double den0, double s2) {
   const double bd = beta * std::sqrt(std::fmax(s2, 0.0)), dn = std::sqrt(std::fmax(den0, 0.0));
   if (dn > bd) bound = std::fmin(bound, (std::sqrt(std::fmax(num0, 0.0)) + bd) / (dn - bd));
   return bound;
+}
+
+// eps that realisation b's next pass is likely to give: the last one times the last ratio (after one pass,
+// times the contraction of the pass; before any, unknown).
+double expect_eps(const recon_plan_t* pl, int b, double beta) {
+  const std::vector<double>& h = pl->hist[b];
+  if (h.empty()) return INFINITY;
+  const double rate = h.size() > 1 ? h[h.size() - 1] / h[h.size() - 2]
+                                   : ((pl->p.flags & RECON_RELAXED) ? beta / (2.0 + beta) : beta);
+  return h.back() * rate;
 }
 
 int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out, double* eps_out) {
@@ -1508,8 +1572,8 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
     RECON_TRY(full_state());
     RECON_TRY(upload_mask(pl, pl->act_fin, pl->h_fin));
     RECON_TRY(ops->zfinal(pl, pl->psi, nullptr, true, pl->act_fin, false));
-    HIP_TRY(pl, hipMemcpyAsync(pl->h_red2.data(), pl->red + 2 * B, 16 * B, hipMemcpyDeviceToHost, pl->stream));
-    HIP_TRY(pl, hipStreamSynchronize(pl->stream));
+    RECON_TRY(queue_read(pl, pl->h_red2, pl->red + 2 * B, 2 * B));
+    RECON_TRY(wait_read(pl));
     for (int b = 0; b < B; ++b) {
       if (!pl->pending1[b]) continue;
       pl->psi_valid[b] = 1;
@@ -1565,19 +1629,21 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
       RECON_TRY(upload_mask(pl, pl->act_fin, pl->h_fin));
       RECON_TRY(ops->combine(pl, pl->act_fin));
     }
-    RECON_TRY(upload_mask(pl, pl->act_fan, pl->h_fan));
     RECON_TRY(upload_mask(pl, pl->act_it, pl->h_it));
+    if (any_fan) {
+      RECON_TRY(upload_mask(pl, pl->act_fan, pl->h_fan));
+      RECON_TRY(ops->fanout(pl, pl->act_fan, true));
+    }
     const bool steady = mode == ZI_PLAIN && !first;
     const bool graph = steady && (pl->p.flags & RECON_PASS_GRAPHS) && !pl->prof.on;
-    if (graph) {
-      RECON_TRY(pass_graph_launch(pl, ops));
-    } else {
-      if (any_fan) RECON_TRY(ops->fanout(pl, pl->act_fan, true));
-      RECON_TRY(ops->ziter(pl, mode, pl->act_it));
-    }
+    if (graph) RECON_TRY(pass_graph_launch(pl, ops));
+    else RECON_TRY(ops->ziter(pl, mode, pl->act_it));
     if (cross) {
-      HIP_TRY(pl, hipMemcpyAsync(pl->h_red2.data(), pl->red + 2 * B, 16 * B, hipMemcpyDeviceToHost, pl->stream));
-      HIP_TRY(pl, hipStreamSynchronize(pl->stream));
+      // the fan-in is queued before the wait: a realisation that drops out of the pass here is rebuilt
+      // from D_1 or D_s, so what it leaves in W0 and W1 is not read
+      RECON_TRY(queue_read(pl, pl->h_red2, pl->red + 2 * B, 2 * B));
+      RECON_TRY(ops->fanin(pl, pl->act_it));
+      RECON_TRY(wait_read(pl));
       bool rest = false;
       for (int b = 0; b < B; ++b) {
         if (!pl->h_it[b] || !pl->pending1[b]) continue;
@@ -1600,14 +1666,37 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
       RECON_TRY(upload_mask(pl, pl->act_it, pl->h_it));
     }
     // relaxed passes mix with D_n; the first pass after a non-gradient start has no D_0 and is plain
-    if (!graph) RECON_TRY(ops->fanin_xiter(pl, first, pl->act_it, start_pass ? 1.f : relax_weight(pl)));
-    // the start pass also reads S1, S2 (red[2B..4B)): one copy of both halves
-    HIP_TRY(pl, hipMemcpyAsync(pl->h_red.data(), pl->red, (start_pass ? 32 : 16) * B, hipMemcpyDeviceToHost,
-                               pl->stream));
-    HIP_TRY(pl, hipStreamSynchronize(pl->stream));
+    if (!graph) {
+      if (!cross) RECON_TRY(ops->fanin(pl, pl->act_it));
+      RECON_TRY(ops->xiter(pl, first, pl->act_it, start_pass ? 1.f : relax_weight(pl)));
+    }
+    // the start pass also reads S1, S2 (red[2B..4B)): both halves together
+    RECON_TRY(queue_read(pl, pl->h_red, pl->red, (start_pass ? 4 : 2) * B));
+    // While the host waits for the norm and decides, the fan-out that the realisations need next is already
+    // running: the combined one for those sure to go on (passes left in this call, and eps expected well
+    // above the tolerance), the full one when all are sure to stop.  Which of them ran is the
+    // realisation's state Y, so a wrong guess costs its time and nothing else; where it is not clear,
+    // nothing is run ahead.  (Waiting first left the GPU idle for 15 us a pass: a fifth of a 64^3 pass.)
+    bool go_on = false, all_stop = true;
+    for (int b = 0; b < B; ++b) {
+      pl->h_fan[b] = 0;
+      if (!pl->h_it[b]) continue;
+      const double expect = fixed ? INFINITY : expect_eps(pl, b, beta) / tol;
+      const bool last = it + 1 == max_iter;
+      pl->h_fan[b] = !last && expect > 1.5;
+      go_on = go_on || pl->h_fan[b];
+      all_stop = all_stop && (last || expect < 0.67);
+    }
+    const int ahead = go_on ? SY_COMB : (all_stop ? SY_FULL : SY_NONE);
+    if (ahead == SY_FULL) pl->h_fan = pl->h_it;
+    if (ahead != SY_NONE) {
+      RECON_TRY(upload_mask(pl, pl->act_fan, pl->h_fan));
+      RECON_TRY(ops->fanout(pl, pl->act_fan, ahead == SY_COMB));
+    }
+    RECON_TRY(wait_read(pl));
     for (int b = 0; b < B; ++b) {
       if (!pl->h_it[b]) continue;
-      pl->st_y[b] = SY_NONE;
+      pl->st_y[b] = pl->h_fan[b] ? ahead : SY_NONE;
       pl->psi_valid[b] = 0;
       const bool was_start = pl->passes[b] == 0 && pl->start_b[b] != RECON_START_PLAIN;
       pl->passes[b] += 1;

@@ -797,13 +797,15 @@ __global__ void __launch_bounds__(256) k_mask_brick(const long long* __restrict_
 
 // Per-realisation scalars from the exact totals {W_g, W_r, n_occ}:
 //   alpha = W_g / W_r, 1/rho_bar = N^3 / (W_g 2^-32), mask threshold floor(tau 27 W_r / n_occ);
-// status[b] bit 0: galaxy total is zero, bit 1: random total is zero.
+// status[b] bit 0: galaxy total is zero, bit 1: random total is zero.  host (pinned host memory, or null):
+// the two invalid-object counts, then the status of every realisation.
 // One block per realisation: sums the per-tile integer partials (exact, any order), then derives
 // the scalars; tot[b] keeps the totals.
 __global__ void __launch_bounds__(256) k_scalars(const unsigned long long* __restrict__ tpart, int nblk, long long n3,
                                                  double tau, int randoms, unsigned long long* __restrict__ tot,
                                                  DeltaScal* __restrict__ sc, long long* __restrict__ thr,
-                                                 int* __restrict__ status) {
+                                                 int* __restrict__ status, const int* __restrict__ err,
+                                                 double* __restrict__ host) {
   const int b = blockIdx.x;
   unsigned long long acc[3] = {0ull, 0ull, 0ull};
   for (int i = threadIdx.x; i < nblk; i += 256) {
@@ -844,6 +846,10 @@ __global__ void __launch_bounds__(256) k_scalars(const unsigned long long* __res
     sc[b] = d;
     thr[b] = th;
     status[b] = st;
+    if (host) {
+      host[2 + b] = (double)st;
+      if (b == 0) { host[0] = (double)err[0]; host[1] = (double)err[1]; }
+    }
   }
 }
 
@@ -2076,9 +2082,10 @@ __global__ void RECON_X_ITER_BOUNDS(N) k_x_iter(float2* __restrict__ a0, float2*
   if (act) x_store<N>(v, a1, row, j);
 }
 
-// Fixed-order reduction of per-block partial pairs: out[b] = sum over blocks.
+// Fixed-order reduction of per-block partial pairs: out[b] = sum over blocks, also written to the host's
+// pinned buffer (host, when not null), so that no copy has to follow.
 __global__ void __launch_bounds__(1024) k_reduce_pairs(const double* __restrict__ partials, int nblk,
-                                                       double* __restrict__ out) {
+                                                       double* __restrict__ out, double* __restrict__ host) {
   // one block per realisation; four independent accumulators per thread keep many loads in flight
   constexpr int NT = 1024;
   const int b = blockIdx.x;
@@ -2100,7 +2107,11 @@ __global__ void __launch_bounds__(1024) k_reduce_pairs(const double* __restrict_
   }
   double t0, t1;
   block_sum2<NT>((s0[0] + s0[1]) + (s0[2] + s0[3]), (s1[0] + s1[1]) + (s1[2] + s1[3]), &t0, &t1);
-  if (threadIdx.x == 0) { out[2 * b] = t0; out[2 * b + 1] = t1; }
+  if (threadIdx.x == 0) {
+    out[2 * b] = t0;
+    out[2 * b + 1] = t1;
+    if (host) { host[2 * b] = t0; host[2 * b + 1] = t1; }
+  }
 }
 
 // ---------------------------------------------------------------------------

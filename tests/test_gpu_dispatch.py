@@ -261,3 +261,55 @@ def test_ngp_deposit_keeps_the_cic_copy_a_shift_may_name(gpu_lib):
     assert torch.equal(got, want)
     assert named(native.GAL, gal) == native.RECON_EINVAL   # an NGP deposit's copy is not one to name
     plan.close()
+
+
+@pytest.mark.parametrize("start,relaxed,graphs", [("PLAIN", False, False), ("PLAIN", True, True), ("FFTA2", False, True)])
+def test_work_queued_ahead_of_the_convergence_test_changes_nothing(gpu_lib, start, relaxed, graphs):
+    # tolerances on either side of every pass's eps (so that the expected next eps is right, wrong and
+    # undecided in turn), in one call, in calls of one pass, and resumed after the end: the same passes and the
+    # same bits as a fixed number of passes; two realisations that stop at different passes, too
+    from paper_1504_02591_amd import native
+    n, total = 32, 7
+    s = getattr(native, "START_" + start)
+    kw = dict(box_len=320.0, observer=(-300.0, 128.0, 224.0), bias=1.0, growth=0.7, smooth_r=10.0, randoms=False,
+              start_buffers=start != "PLAIN", relaxed=relaxed, graphs=graphs)
+    d = field(n, 21)
+    plan = native.Plan(n, **kw)
+
+    def run(pieces, tol):
+        plan.set_delta(d)
+        plan.solve(s)
+        for k in pieces:
+            rc, passes, eps = plan.iterate(k, tol)
+        return rc, passes[0], eps[0], plan.psi()
+
+    fixed = {k: run([k], 0.0) for k in range(1, total + 1)}
+    eps = fixed[total][2]
+    for k in range(1, total):
+        for f in (1.0 - 1e-6, 1.0 + 1e-6, 0.8, 1.25):
+            tol = eps[k - 1] * f
+            stop = next((i + 1 for i, e in enumerate(eps) if e <= tol), None)
+            if stop is None:
+                continue
+            rc, passes, _, psi = run([total], tol)
+            assert passes == stop and rc == native.RECON_OK and torch.equal(psi, fixed[stop][3])
+            rc, passes, _, psi = run([1] * stop, tol)
+            assert passes == stop and rc == native.RECON_OK and torch.equal(psi, fixed[stop][3])
+    for pieces in ([2, 1, 3], [1, 0, 4], [0, 5]):        # resumed, also straight after a displacement was formed
+        assert torch.equal(run(pieces, 0.0)[3], fixed[sum(pieces)][3])
+    plan.close()
+    smooth = torch.fft.irfftn(torch.fft.rfftn(d.cpu()) * (torch.arange(n // 2 + 1) < 2), s=(n, n, n)).to(dev())
+    both = native.Plan(n, batch=2, **kw)
+    tol = eps[3]
+    both.set_delta(torch.stack([d, smooth.contiguous()]))
+    both.solve(s)
+    _, passes, _ = both.iterate(total, tol)
+    psi = both.psi()
+    one = native.Plan(n, **kw)
+    for b, f in enumerate((d, smooth.contiguous())):
+        one.set_delta(f)
+        one.solve(s)
+        _, p, _ = one.iterate(total, tol)
+        assert p[0] == passes[b] and torch.equal(one.psi()[0], psi[b])
+    one.close()
+    both.close()
