@@ -1,11 +1,10 @@
 """Autotuner for the transform tile shapes and the middle radix split (csrc/recon_tuning.h).
 
 Knobs (compile-time, see recon_tuning.h): RECON_TILE_Z (packed z column pairs per block),
-RECON_TILE_Y (y-pass columns), RECON_TILE_X (x-pass rows), RECON_MID_512 / RECON_MID_1024
-(split of the middle radix factor), RECON_Z_TPB (z tiles per block of the z iteration, whose
-next tile is staged while the current one is finished), RECON_Z_WAVE (wave-local z iteration at
-512^3), and per-size copies of the tile and tiles-per-block knobs for 256^3 (_256) and 1024^3
-(_1024).  Each grid size tunes its own knobs (SIZE_KNOBS), one knob at a time around the current
+RECON_TILE_Y (y-pass columns) and RECON_Z_TPB (z tiles per block of the z iteration, whose next
+tile is staged while the current one is finished) of the sizes below 256, RECON_TILE_X (x-pass
+rows) with copies of its own for 256^3 (_256) and 1024^3 (_1024), and RECON_MID_512 /
+RECON_MID_1024 (split of the middle radix factor).  Each grid size tunes its own knobs (SIZE_KNOBS), one knob at a time around the current
 setting: every single-knob variant is compiled (in parallel, on the host), each is timed on the GPU
 in a process of its own on the correction pass of an n^3 field, or of a batch of them (the dominant
 cost of a reconstruction), and each knob takes its fastest value.  The combined choice is timed
@@ -34,11 +33,10 @@ TUNING = os.path.join(HERE, "csrc", "recon_tuning.h")
 # knobs timed at each grid size (recon_tuning.h): the general ones at 512^3 (every size without its own
 # values takes them), the per-size ones at 256^3 (the batched workload) and 1024^3
 SIZE_KNOBS = {
-    512: {"RECON_TILE_Z": [8, 16], "RECON_TILE_Y": [8, 16], "RECON_TILE_X": [2, 4, 8], "RECON_MID_512": [0, 1, 2],
-          "RECON_Z_TPB": [1, 2, 4, 8], "RECON_Z_WAVE": [0, 1]},
-    256: {"RECON_TILE_Z_256": [8, 16], "RECON_TILE_Y_256": [8, 16], "RECON_TILE_X_256": [2, 4, 8],
-          "RECON_Z_TPB_256": [1, 2, 4, 8]},
-    1024: {"RECON_TILE_X_1024": [2, 4, 8], "RECON_MID_1024": [0, 1, 2], "RECON_Z_TPB_1024": [1, 2, 4, 8]},
+    128: {"RECON_TILE_Z": [8, 16], "RECON_TILE_Y": [8, 16], "RECON_Z_TPB": [1, 2, 4, 8]},
+    512: {"RECON_TILE_X": [2, 4, 8], "RECON_MID_512": [0, 1, 2]},
+    256: {"RECON_TILE_X_256": [2, 4, 8]},
+    1024: {"RECON_TILE_X_1024": [2, 4, 8], "RECON_MID_1024": [0, 1, 2]},
 }
 KNOBS = {k: v for d in SIZE_KNOBS.values() for k, v in d.items()}
 
@@ -212,8 +210,8 @@ def cmd_write(a):
     lines = ["// Tuning knobs of the transform kernels, written by paper_1504_02591_amd/autotune.py (a -D on the",
              "// compiler command line overrides them).  Tiles: packed z column pairs, y-pass columns, x-pass",
              "// rows per block; middle radix split of the 512- and 1024-point transforms; z tiles per block of",
-             "// the z iteration; wave-local z iteration at 512^3.  The general knobs are timed at 512^3 and",
-             "// serve every size without its own; the _256 and _1024 knobs are timed at those sizes."]
+             "// the z iteration.  The z and y knobs are timed at 128^3 and serve the sizes below 256 (the larger",
+             "// ones' tiles are fixed); RECON_TILE_X is timed at 512^3 and serves every size without its own."]
     for size in sorted(blocks):
         lines += blocks[size]
     lines.append("#pragma once")

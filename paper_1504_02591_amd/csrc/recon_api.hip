@@ -540,6 +540,8 @@ template <int N>
 struct SizeOps {
   static constexpr int WZ = wz<N>(), WY = wy<N>(), WX = wx<N>();
   static constexpr int TZ = ntz<N>(), TY = nty<N>(), TX = ntx<N>();
+  static constexpr int TYP = YTile<N, yp_col<N>()>::NT;                               // plain y passes
+  template <int NA> static constexpr int TZG = ZTile<N, zg_col<N, NA>()>::NT;  // z forward of grids
   static dim3 gz(const recon_plan_t* pl) { return dim3(N * (N / (2 * WZ)), pl->batch); }
   // z tiles per block of the z iteration: up to the size's tuned number (ztpb), but no more than
   // leaves kZBlocks blocks in the launch, so that a small grid's tiles spread over the chip instead of
@@ -547,8 +549,8 @@ struct SizeOps {
   template <int MODE, int SPLIT = 0>
   static dim3 gzi(const recon_plan_t* pl) {
     int tpb = ztpb<N, MODE, SPLIT>();
-    while (tpb > 1 && (long long)ztiles<N>() / tpb * pl->batch < kZBlocks) tpb /= 2;
-    return dim3(ztiles<N>() / tpb, pl->batch);
+    while (tpb > 1 && (long long)ztiles<N, SPLIT>() / tpb * pl->batch < kZBlocks) tpb /= 2;
+    return dim3(ztiles<N, SPLIT>() / tpb, pl->batch);
   }
   static dim3 gy(const recon_plan_t* pl) { return dim3((N / 2 + 1) * (N / WY), pl->batch); }
   static dim3 gx(const recon_plan_t* pl) { return dim3((N / 2 + 1) * N / WX, pl->batch); }
@@ -558,7 +560,7 @@ struct SizeOps {
     if (pl->randoms) {
       {
         PROF(pl, KP_Z_FWD_GRID);
-        k_z_fwd_grid<N, 2><<<gz(pl), dim3(TZ), 0, s>>>(pl->grid_g, pl->grid_r, pl->w0, pl->w1, pl->tpart, pl->tw,
+        k_z_fwd_grid<N, 2><<<gz(pl), dim3(TZG<2>), 0, s>>>(pl->grid_g, pl->grid_r, pl->w0, pl->w1, pl->tpart, pl->tw,
                                                        valid_of(pl, RECON_GAL), valid_of(pl, RECON_RAN), pl->zflag);
       }
       RECON_TRY(check_launch(pl, "z forward (grids)"));
@@ -567,7 +569,7 @@ struct SizeOps {
       RECON_TRY(scalars_and_mask(pl, (int)gz(pl).x, 2 * WZ));
       {
         PROF(pl, KP_Y_FWD);
-        k_y_plain<N, 2, false><<<gy(pl), dim3(TY), 0, s>>>(pl->w0, pl->w1, pl->tw, pl->zflag);
+        k_y_plain<N, 2, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, pl->w1, pl->tw, pl->zflag);
       }
       RECON_TRY(check_launch(pl, "y forward"));
       {
@@ -577,7 +579,7 @@ struct SizeOps {
       RECON_TRY(check_launch(pl, "x smooth"));
       {
         PROF(pl, KP_Y_INV);
-        k_y_plain<N, 2, true><<<gy(pl), dim3(TY), 0, s>>>(pl->w0, pl->w1, pl->tw, pl->mflag);
+        k_y_plain<N, 2, true><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, pl->w1, pl->tw, pl->mflag);
       }
       RECON_TRY(check_launch(pl, "y inverse"));
       {
@@ -591,13 +593,13 @@ struct SizeOps {
     } else {
       {
         PROF(pl, KP_Z_FWD_GRID);
-        k_z_fwd_grid<N, 1><<<gz(pl), dim3(TZ), 0, s>>>(pl->grid_g, nullptr, pl->w0, nullptr, pl->tpart, pl->tw,
+        k_z_fwd_grid<N, 1><<<gz(pl), dim3(TZG<1>), 0, s>>>(pl->grid_g, nullptr, pl->w0, nullptr, pl->tpart, pl->tw,
                                                        valid_of(pl, RECON_GAL), nullptr, pl->zflag);
       }
       RECON_TRY(check_launch(pl, "z forward (grid)"));
       {
         PROF(pl, KP_Y_FWD);
-        k_y_plain<N, 1, false><<<gy(pl), dim3(TY), 0, s>>>(pl->w0, nullptr, pl->tw, pl->zflag);
+        k_y_plain<N, 1, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, nullptr, pl->tw, pl->zflag);
       }
       RECON_TRY(check_launch(pl, "y forward"));
       {
@@ -607,7 +609,7 @@ struct SizeOps {
       RECON_TRY(check_launch(pl, "x smooth"));
       {
         PROF(pl, KP_Y_INV);
-        k_y_plain<N, 1, true><<<gy(pl), dim3(TY), 0, s>>>(pl->w0, nullptr, pl->tw);
+        k_y_plain<N, 1, true><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, nullptr, pl->tw);
       }
       RECON_TRY(check_launch(pl, "y inverse"));
       RECON_TRY(scalars_and_mask(pl, (int)gz(pl).x, 2 * WZ));
@@ -628,7 +630,7 @@ struct SizeOps {
     hipStream_t s = pl->stream;
     {
       PROF(pl, KP_Y_FWD);
-      k_y_plain<N, 1, false><<<gy(pl), dim3(TY), 0, s>>>(pl->w0, nullptr, pl->tw, mflag);
+      k_y_plain<N, 1, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, nullptr, pl->tw, mflag);
     }
     RECON_TRY(check_launch(pl, "y forward (delta)"));
     {
@@ -653,7 +655,7 @@ struct SizeOps {
     hipStream_t s = pl->stream;
     k_z_fwd_real<N><<<gz(pl), dim3(TZ), 0, s>>>(f, pl->w0, pl->tw);
     RECON_TRY(check_launch(pl, "z forward (Helmholtz)"));
-    k_y_plain<N, 1, false><<<gy(pl), dim3(TY), 0, s>>>(pl->w0, nullptr, pl->tw);
+    k_y_plain<N, 1, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, nullptr, pl->tw);
     RECON_TRY(check_launch(pl, "y forward (Helmholtz)"));
     k_x_start<N, true><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->ds, pl->geo, pl->tw);
     return check_launch(pl, "x start (Helmholtz)");
@@ -686,30 +688,36 @@ struct SizeOps {
     return check_launch(pl, "y combine");
   }
 
+  template <int MODE>
+  static void zstep(recon_plan_t* pl, const int* act) {
+    float* corr = MODE == ZI_PLAIN ? nullptr : pl->corr;
+    double* part = MODE == ZI_PLAIN ? nullptr : pl->partials;
+    const float* up = MODE == ZI_LEARNED ? pl->upbuf : nullptr;
+    if constexpr (z_col<N>())
+      k_z_iter_c<N, MODE><<<gzi<MODE>(pl), dim3(TZ), 0, pl->stream>>>(pl->w0, pl->w1, pl->w2, pl->geo, corr, part, act,
+                                                                     pl->tw, up);
+    else
+      k_z_iter<N, MODE><<<gzi<MODE>(pl), dim3(TZ), 0, pl->stream>>>(pl->w0, pl->w1, pl->w2, pl->geo, corr, part, act,
+                                                                   pl->tw, up);
+  }
+
+  template <int TERMS>
+  static void zsplit(recon_plan_t* pl, const int* act) {
+    if constexpr (N >= 64)
+      k_z_iter<N, ZI_PLAIN, TERMS><<<gzi<ZI_PLAIN, TERMS>(pl), dim3(ntzs<N, TERMS>()), 0, pl->stream>>>(
+          pl->w0, pl->w1, pl->w2, pl->geo, nullptr, nullptr, act, pl->tw);
+  }
+
   static int ziter(recon_plan_t* pl, int mode, const int* act) {
     hipStream_t s = pl->stream;
     {
       PROF(pl, KP_Z_ITER);
-      if (mode == ZI_FFTA)
-        k_z_iter<N, ZI_FFTA><<<gzi<ZI_FFTA>(pl), dim3(TZ), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->geo, pl->corr,
-                                                               pl->partials, act, pl->tw);
-      else if (mode == ZI_LEARNED)
-        k_z_iter<N, ZI_LEARNED><<<gzi<ZI_LEARNED>(pl), dim3(TZ), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->geo, pl->corr,
-                                                                  pl->partials, act, pl->tw, pl->upbuf);
-      else if (mode == ZI_CROSS)
-        k_z_iter<N, ZI_CROSS><<<gzi<ZI_CROSS>(pl), dim3(TZ), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->geo, pl->corr,
-                                                                pl->partials, act, pl->tw);
-      else if (N >= 64 && (pl->p.flags & RECON_FFT_SPLITBF16))
-        k_z_iter<N, ZI_PLAIN, N >= 64 ? 2 : 0><<<gzi<ZI_PLAIN, N >= 64 ? 2 : 0>(pl), dim3(TZ), 0, s>>>(
-            pl->w0, pl->w1, pl->w2, pl->geo, nullptr, nullptr, act, pl->tw);
-      else if (N >= 64 && (pl->p.flags & RECON_FFT_SPLITBF16_X3))
-        k_z_iter<N, ZI_PLAIN, N >= 64 ? 3 : 0><<<gzi<ZI_PLAIN, N >= 64 ? 3 : 0>(pl), dim3(TZ), 0, s>>>(
-            pl->w0, pl->w1, pl->w2, pl->geo, nullptr, nullptr, act, pl->tw);
-      else if constexpr (N == 512 && RECON_Z_WAVE && wz<N>() == 16)
-        k_z_iter_w<N><<<gzi<ZI_PLAIN>(pl), dim3(1024), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->geo, act, pl->tw);
-      else
-        k_z_iter<N, ZI_PLAIN><<<gzi<ZI_PLAIN>(pl), dim3(TZ), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->geo, nullptr,
-                                                                nullptr, act, pl->tw);
+      if (mode == ZI_FFTA) zstep<ZI_FFTA>(pl, act);
+      else if (mode == ZI_LEARNED) zstep<ZI_LEARNED>(pl, act);
+      else if (mode == ZI_CROSS) zstep<ZI_CROSS>(pl, act);
+      else if (N >= 64 && (pl->p.flags & RECON_FFT_SPLITBF16)) zsplit<2>(pl, act);
+      else if (N >= 64 && (pl->p.flags & RECON_FFT_SPLITBF16_X3)) zsplit<3>(pl, act);
+      else zstep<ZI_PLAIN>(pl, act);
     }
     RECON_TRY(check_launch(pl, "z iteration"));
     if (mode != ZI_PLAIN) {
@@ -749,15 +757,16 @@ struct SizeOps {
 
   static int zfinal(recon_plan_t* pl, float* psi, float* u, bool cross, const int* act, bool comb) {
     hipStream_t s = pl->stream;
-    if (comb && (psi || cross)) return fail(pl, RECON_EINVAL, "internal: the combined state gives u only");
+    if (comb ? (psi || cross || !u) : (u || !psi))
+      return fail(pl, RECON_EINVAL, "internal: the combined state gives u only, the full state Psi only");
     {
       PROF(pl, KP_Z_FINAL);
-      if (comb)
-        k_z_final<N, true><<<gz(pl), dim3(TZ), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->geo, nullptr, u, nullptr,
-                                                       pl->partials, act, pl->tw);
-      else
-        k_z_final<N, false><<<gz(pl), dim3(TZ), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->geo, psi, u,
-                                                        cross ? pl->corr : nullptr, pl->partials, act, pl->tw);
+      auto go = [&](auto kernel) {
+        kernel<<<gz(pl), dim3(TZ), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->geo, psi, u, pl->corr, pl->partials, act, pl->tw);
+      };
+      if (comb) go(k_z_final<N, ZF_U>);
+      else if (cross) go(k_z_final<N, ZF_CROSS>);
+      else go(k_z_final<N, ZF_PSI>);
     }
     RECON_TRY(check_launch(pl, "z final"));
     if (cross) {

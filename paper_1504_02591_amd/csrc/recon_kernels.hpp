@@ -47,28 +47,40 @@ enum ZIterMode { ZI_PLAIN = 0, ZI_FFTA = 1, ZI_LEARNED = 2, ZI_CROSS = 3 };
 // component), 12 bytes per node, and the shift reads each component's rows.
 
 // Tile shapes (compile-time tuning knobs from recon_tuning.h): packed z columns, y-pass columns,
-// x-pass rows.  Each block runs one radix-8 fragment per thread, (N/8) * tile threads.
+// x-pass rows.  A block of the radix-8 engine runs one fragment per thread, (N/8) * tile threads.
 constexpr int cmin(int a, int b) { return a < b ? a : b; }
-// Knobs per grid size: the 256^3 and 1024^3 values are tuned on their own (recon_tuning.h), every
-// other size takes the general value.
-template <int N> constexpr int tile_z() { return N == 256 ? RECON_TILE_Z_256 : RECON_TILE_Z; }
-template <int N> constexpr int tile_y() { return N == 256 ? RECON_TILE_Y_256 : RECON_TILE_Y; }
 template <int N> constexpr int tile_x() {
   return N == 256 ? RECON_TILE_X_256 : (N == 1024 ? RECON_TILE_X_1024 : RECON_TILE_X);
 }
-template <int N> constexpr int z_tpb() {
-  return N == 256 ? RECON_Z_TPB_256 : (N == 1024 ? RECON_Z_TPB_1024 : RECON_Z_TPB);
-}
-// (1024-point columns need 8-column tiles to fit the LDS)
-template <int N> constexpr int wz() { return N >= 1024 ? 8 : cmin(N / 2, tile_z<N>()); }
-template <int N> constexpr int wy() { return N >= 1024 ? 8 : cmin(N, tile_y<N>()); }
+// The z and y passes run on the column engine from 256 on: tiles of 16 columns (packed, in z) and one block
+// of N threads per tile, 16 elements each.  Below 256 a grid has too few tiles to fill the chip with
+// N-thread blocks, and the radix-8 engine with its tile knobs stays; so it does for the matrix-core variants
+// of the z iteration at every size, with 8 columns at 1024 (more would not fit the LDS).  Both sides on a
+// batch of eight 256^3 (where the engine gives least; ms): z iteration 0.404 against 0.523, y passes 0.412
+// against 0.440; one 512^3: 0.462 / 0.556 and 0.473 / 0.488; one 1024^3: 6.3 / 8.4 and 4.0 / 5.9.
+template <int N> constexpr bool z_col() { return N >= 256; }
+template <int N> constexpr int wz() { return z_col<N>() ? 16 : cmin(N / 2, RECON_TILE_Z); }
+template <int N, int SPLIT> constexpr int wzs() { return SPLIT > 0 && N >= 1024 ? 8 : wz<N>(); }
+template <int N> constexpr int wy() { return N >= 256 ? 16 : cmin(N, RECON_TILE_Y); }
 template <int N> constexpr int wx() { return tile_x<N>(); }
+// y passes: engine, elements per thread, rows between them
+template <int N> constexpr bool y_col() { return N >= 256; }
+template <int N> constexpr int y_el() { return y_col<N>() ? 16 : 8; }
+template <int N> constexpr int y_st() { return N / y_el<N>(); }
+// (the plain y passes at 512: the radix-8 engine, whose 1024-thread blocks put 32 waves on a CU and whose
+// transform has no cross-lane stages: two arrays forward / inverse 344 / 307 us against 369 / 354)
+template <int N> constexpr bool yp_col() { return y_col<N>() && N != 512; }
+// The grids' forward z pass takes the column engine at 1024 (4.5 against 5.9 ms with the radix-8 engine,
+// whose tile would be 8 packed columns there) and for two grids of 256 (77 against 90 us).  One grid of 256
+// and grids of 512 want the 32 waves per CU of the radix-8 engine's 512- and 1024-thread blocks on their
+// 16-byte row segments (47 against 56 us, and 431 against 549 us for two).
+template <int N, int NA> constexpr bool zg_col() { return N == 1024 || (N == 256 && NA == 2); }
 // z tiles (one y row, 2 wz consecutive x) and tiles per block of the z iteration
-template <int N> constexpr int ztiles() { return N * (N / (2 * wz<N>())); }
+template <int N, int SPLIT = 0> constexpr int ztiles() { return N * (N / (2 * wzs<N, SPLIT>())); }
 // (the start and cross modes and the matrix-core radix variants, which hold more live state, take one
 // tile per block)
 template <int N, int MODE, int SPLIT = 0> constexpr int ztpb() {
-  return MODE == ZI_PLAIN && SPLIT == 0 ? cmin(z_tpb<N>(), ztiles<N>()) : 1;
+  return MODE == ZI_PLAIN && SPLIT == 0 && !z_col<N>() ? cmin(RECON_Z_TPB, ztiles<N>()) : 1;
 }
 
 
@@ -989,32 +1001,197 @@ __device__ __forceinline__ float los_comp(const Geo& g, int a, int i) { return f
 // value whatever the compiler hoists or contracts
 __device__ __forceinline__ float los_r2(float rx, float ry, float rz) { return fmaf(rz, rz, fmaf(ry, ry, rx * rx)); }
 
-template <int N> constexpr int ntz() { return frag_threads<N, wz<N>()>(); }
-template <int N> constexpr int nty() { return frag_threads<N, wy<N>()>(); }
+template <int N> constexpr int ntz() { return z_col<N>() ? N : frag_threads<N, wz<N>()>(); }
+template <int N, int SPLIT> constexpr int ntzs() { return SPLIT > 0 ? frag_threads<N, wzs<N, SPLIT>()>() : ntz<N>(); }
+template <int N> constexpr int nty() { return y_col<N>() ? N : frag_threads<N, wy<N>()>(); }
 template <int N> constexpr int ntx() { return frag_threads<N, wx<N>()>(); }
+
+// Column-engine z tile (one y row, 32 consecutive x as 16 packed columns, every z).
+template <int N>
+struct ZCol {
+  using G = Col<N>;
+  static constexpr int WP = 16, RT = N / 16, RL = 8;      // rows a load step apart, load steps (kz < N/2)
+  // half-spectrum rows kz = m + i RT (i < 8) of columns p and p + 16 of an array, and of row N/2 in the
+  // first 16 threads: loads that stay in flight while another array is transformed
+  struct Half {
+    float2 a[RL], b[RL], na, nb;
+  };
+  // the rows of load step i as a buffer: kz planes lie N^2 elements apart
+  __device__ __forceinline__ static PlaneBuf rows(const float2* arr, int kz, int y, int x0) {
+    return PlaneBuf(arr + ((long long)kz * N + y) * N + x0, (unsigned)((RT - 1) * N * N + 2 * WP) * 8u);
+  }
+  __device__ __forceinline__ static unsigned lane() {
+    return ((unsigned)(threadIdx.x >> 4) * (unsigned)(N * N) + (threadIdx.x & 15)) * 8u;
+  }
+  __device__ __forceinline__ static void fetch(Half& h, const float2* arr, int y, int x0) {
+    constexpr bool HINT = (RECON_STREAM & 2) != 0;
+    const unsigned l = lane();
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+      const PlaneBuf pb = rows(arr, i * RT, y, x0);
+      h.a[i] = pb.template load<HINT>(l, 0);
+      h.b[i] = pb.template load<HINT>(l, WP * 8);
+    }
+    if (threadIdx.x < 16) {
+      const PlaneBuf pb = rows(arr, N / 2, y, x0);
+      h.na = pb.template load<HINT>(l, 0);
+      h.nb = pb.template load<HINT>(l, WP * 8);
+    }
+  }
+  // the packed full-length columns Z = A + i B, extended Hermitian-wise, in natural order in the tile
+  // (the imaginary parts at k = 0 and N/2 are dropped as for a real inverse transform)
+  __device__ __forceinline__ static void put(const Half& h, float2* buf) {
+    const int m0 = threadIdx.x >> 4, p = threadIdx.x & 15;
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+      const int m = m0 + i * RT;
+      const float2 A = h.a[i], B = h.b[i];
+      if (i == 0 && m == 0) {
+        buf[G::at(0, p)] = make_float2(A.x, B.x);
+      } else {
+        buf[G::at(m, p)] = make_float2(A.x - B.y, A.y + B.x);
+        buf[G::at(N - m, p)] = make_float2(A.x + B.y, B.x - A.y);
+      }
+    }
+    if (threadIdx.x < 16) buf[G::at(N / 2, p)] = make_float2(h.na.x, h.nb.x);
+  }
+  // this thread's fragment, rows j + r N/16 of column c
+  __device__ __forceinline__ static void frag(float2* v, const float2* buf, int c, int j) {
+#pragma unroll
+    for (int r = 0; r < G::E; ++r) v[r] = buf[G::at(j + r * G::T, c)];
+  }
+  // Half spectra of the two real columns of each packed column (natural order in the tile) to memory;
+  // MULK: times i k'_z.
+  template <bool MULK>
+  __device__ __forceinline__ static void unpack(const float2* buf, float2* out, int y, int x0, float kf) {
+    constexpr bool HINT = (RECON_STREAM & 1) != 0;
+    const int m0 = threadIdx.x >> 4, p = threadIdx.x & 15;
+    const unsigned l = lane();
+    auto one = [&](int kz, const PlaneBuf& pb) {
+      const float2 Z = buf[G::at(kz, p)], M = buf[G::at((N - kz) & (N - 1), p)];
+      float2 A = make_float2(0.5f * (Z.x + M.x), 0.5f * (Z.y - M.y));
+      float2 B = make_float2(0.5f * (Z.y + M.y), 0.5f * (M.x - Z.x));
+      if (MULK) {
+        const float k = kf * deriv_mode<N>(kz);
+        A = mul_i(A) * k;
+        B = mul_i(B) * k;
+      }
+      pb.template store<HINT>(A, l, 0);
+      pb.template store<HINT>(B, l, WP * 8);
+    };
+#pragma unroll
+    for (int i = 0; i < RL; ++i) one(m0 + i * RT, rows(out, i * RT, y, x0));
+    if (threadIdx.x < 16) one(N / 2, rows(out, N / 2, y, x0));
+  }
+};
+
+// The column engine's in-flight half spectra (nothing on the radix-8 engine).
+struct ZNone {};
+template <int N, bool COL = z_col<N>()>
+struct ZHalf {
+  using type = ZNone;
+};
+template <int N>
+struct ZHalf<N, true> {
+  using type = typename ZCol<N>::Half;
+};
+
+// Fragment coordinates, transforms and stores of a z tile, on the engine of its size (COL: the column
+// engine; the tile is the same on both from 256 on).
+template <int N, bool COL = z_col<N>()>
+struct ZTile {
+  static constexpr int WP = wz<N>(), NT = COL ? N : frag_threads<N, WP>(), E = COL ? 16 : 8, ST = N / E;
+  static constexpr int SIZE = [] {
+    if constexpr (COL) return Col<N>::SIZE;
+    else return Lay<N, WP, false>::SIZE;
+  }();
+  __device__ __forceinline__ static void coords(int& c, int& j) {
+    if constexpr (COL) Col<N>::coords(c, j);
+    else frag_coords<N, WP, false>(c, j);
+  }
+  __device__ __forceinline__ static bool active() { return COL || threadIdx.x < Lay<N, WP, false>::NTF; }
+  template <bool INV>
+  __device__ __forceinline__ static void fft(float2* v, float2* buf, const float2* tw, int c, int j) {
+    if constexpr (COL) col_fft<N, INV>(v, buf, tw, c, j);
+    else fft_rr<N, WP, INV, false>(v, buf, tw);
+  }
+  template <bool INV>
+  __device__ __forceinline__ static void fft_lds(float2* v, float2* buf, const float2* tw, int c, int j) {
+    if constexpr (COL) col_fft_lds<N, INV>(v, buf, tw, c, j);
+    else fft_rl<N, WP, INV, false>(v, buf, tw);
+  }
+  template <bool MULK>
+  __device__ __forceinline__ static void unpack(const float2* buf, float2* out, int y, int x0, float kf) {
+    if constexpr (COL) ZCol<N>::template unpack<MULK>(buf, out, y, x0, kf);
+    else z_unpack_store<N, WP, NT, MULK>(buf, out, y, x0, kf);
+  }
+};
+
+// Rows z = j + r ST of a real field (elements of BYTES bytes, x fastest) at one z tile: element h (0: column
+// x0 + c, 1: x0 + c + wz) of row r, addressed as a buffer per r, so that a thread's 2 E elements share one
+// lane offset.  skip: the access is dropped (a load gives 0).
+template <int N, int BYTES, bool COL = z_col<N>()>
+struct ZField {
+  static constexpr int ST = ZTile<N, COL>::ST, WP = wz<N>();
+  const char* base;
+  unsigned lane;
+  __device__ __forceinline__ ZField(const void* f, int y, int x0, int c, int j)
+      : base((const char*)f + ((long long)y * N + x0) * BYTES), lane(((unsigned)j * (unsigned)(N * N) + c) * BYTES) {}
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows(int r) const {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base) + (long long)r * ST * N * N * BYTES, 0,
+                                             ((unsigned)(ST - 1) * (unsigned)(N * N) + 2 * WP) * BYTES, 0x00027000);
+  }
+  __device__ __forceinline__ unsigned off(bool skip) const { return skip ? 0x80000000u : lane; }
+  __device__ __forceinline__ float load(int r, int h) const {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows(r), lane, h * WP * BYTES, 0));
+  }
+  __device__ __forceinline__ void store(float v, int r, int h) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rows(r), lane, h * WP * BYTES, 0);
+  }
+  __device__ __forceinline__ unsigned char load_byte(int r, int h) const {
+    return __builtin_amdgcn_raw_buffer_load_b8(rows(r), lane, h * WP * BYTES, 0);
+  }
+  __device__ __forceinline__ long long load64(int r, int h, bool skip) const {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 t = __builtin_amdgcn_raw_buffer_load_b64(rows(r), off(skip), h * WP * BYTES, 0);
+    return (long long)(((unsigned long long)t[1] << 32) | t[0]);
+  }
+};
+
+// (float)q, rounded once as by the plain conversion, without its 64-bit shift by a register: gfx950 reads the
+// shift amount wrongly when it sits in the last VGPR of the wave's allocation (seen on a build of the 128^3
+// grid pass with 40 VGPRs: v39 read as v0 in some waves), and the compiler does not avoid that register.
+// The two words meet in FP64, exact below 2^53; above, the low 12 bits are folded into one sticky bit first,
+// far below the 24 bits that remain.
+__device__ __forceinline__ float float_of(long long q) {
+  const int hi = (int)(q >> 32);
+  unsigned lo = (unsigned)q;
+  if (hi >= (1 << 21) || hi < -(1 << 21)) lo = (lo & ~0xfffu) | ((lo & 0xfffu) ? 0x800u : 0u);
+  return (float)fma((double)hi, 4294967296.0, (double)lo);
+}
 
 // Forward z transform of int64 grids (units 2^-32) into half spectra.
 // Also writes the exact totals {sum g0, sum g1, #(g1 != 0)} of the tile to tpart[b][block].
-template <int N, int NA>
 // With tile flags (zflag != null, [NA][batch][z tiles]): a tile whose bricks are all not valid gets
 // flag 0 and its zero half spectra are not written (the forward y pass reads such rows as zeros);
 // every other tile gets flag 1.
-__global__ void __launch_bounds__(ntz<N>(), 8) k_z_fwd_grid(const long long* __restrict__ g0,
+template <int N, int NA>
+__global__ void __launch_bounds__((ZTile<N, zg_col<N, NA>()>::NT), N < 256 ? 4 : 8) k_z_fwd_grid(const long long* __restrict__ g0,
                                                          const long long* __restrict__ g1, float2* __restrict__ o0,
                                                          float2* __restrict__ o1, unsigned long long* __restrict__ tpart,
                                                          const float2* __restrict__ twg,
                                                          const unsigned char* __restrict__ v0 = nullptr,
                                                          const unsigned char* __restrict__ v1 = nullptr,
                                                          unsigned char* __restrict__ zflag = nullptr) {
-  constexpr int NT = ntz<N>(), WP = wz<N>();
-  using L = Lay<N, WP, false>;
-  __shared__ float2 buf[L::SIZE];
+  constexpr int NT = ZTile<N, zg_col<N, NA>()>::NT, WP = wz<N>();
+  using Z = ZTile<N, zg_col<N, NA>()>;
+  __shared__ float2 buf[Z::SIZE];
   __shared__ float2 tw[N];
   stage_twiddles<N, NT>(tw, twg);
   int y, x0, c, j;
   z_tile_coords<N, WP>(y, x0);
-  frag_coords<N, WP, false>(c, j);
-  const bool act = threadIdx.x < L::NTF;
+  Z::coords(c, j);
+  const bool act = Z::active();
   const long long n3 = (long long)N * N * N, cn = (long long)(N / 2 + 1) * N * N;
   const int b = blockIdx.y;
   const float unit = 2.3283064365386963e-10f;   // 2^-32
@@ -1043,22 +1220,22 @@ __global__ void __launch_bounds__(ntz<N>(), 8) k_z_fwd_grid(const long long* __r
       }
     }
     if (zflag && threadIdx.x == 0) zflag[((long long)a * gridDim.y + b) * gridDim.x + blockIdx.x] = 1;
-    float2 v[8];
+    float2 v[Z::E];
+    const ZField<N, 8, zg_col<N, NA>()> fld(gsrc, y, x0, c, j);
     if (act) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int z = j + r * (N / 8);
-        const long long base = ((long long)z * N + y) * N + x0 + c;
+      for (int r = 0; r < Z::E; ++r) {
+        const int z = j + r * Z::ST;
         const unsigned char* vz = vb ? vb + (z / kBrick) * NBS * NBS : nullptr;
         const bool ok0 = !vz || vz[(x0 + c) / kBrick], ok1 = !vz || vz[(x0 + c + WP) / kBrick];
-        const long long q0 = ok0 ? gsrc[base] : 0, q1 = ok1 ? gsrc[base + WP] : 0;
+        const long long q0 = fld.load64(r, 0, !ok0), q1 = fld.load64(r, 1, !ok1);
         sums[a] += (unsigned long long)q0 + (unsigned long long)q1;
         if (a == 1) sums[2] += (q0 != 0) + (q1 != 0);
-        v[r] = make_float2((float)q0 * unit, (float)q1 * unit);
+        v[r] = make_float2(float_of(q0) * unit, float_of(q1) * unit);
       }
     }
-    fft_rl<N, WP, false, false>(v, buf, tw);
-    z_unpack_store<N, WP, NT, false>(buf, (a == 0 ? o0 : o1) + b * cn, y, x0, 0.f);
+    Z::template fft_lds<false>(v, buf, tw, c, j);
+    Z::template unpack<false>(buf, (a == 0 ? o0 : o1) + b * cn, y, x0, 0.f);
   }
   __shared__ unsigned long long red[3][NT / 64];
 #pragma unroll
@@ -1083,26 +1260,24 @@ template <int N>
 __global__ void __launch_bounds__(ntz<N>()) k_z_fwd_real(const float* __restrict__ f, float2* __restrict__ o,
                                                          const float2* __restrict__ twg) {
   constexpr int NT = ntz<N>(), WP = wz<N>();
-  using L = Lay<N, WP, false>;
-  __shared__ float2 buf[L::SIZE];
+  using Z = ZTile<N>;
+  __shared__ float2 buf[Z::SIZE];
   __shared__ float2 tw[N];
   stage_twiddles<N, NT>(tw, twg);
   int y, x0, c, j;
   z_tile_coords<N, WP>(y, x0);
-  frag_coords<N, WP, false>(c, j);
+  Z::coords(c, j);
   const long long n3 = (long long)N * N * N, cn = (long long)(N / 2 + 1) * N * N;
   const int b = blockIdx.y;
   f += b * n3;
-  float2 v[8];
-  if (threadIdx.x < L::NTF) {
+  float2 v[Z::E];
+  const ZField<N, 4> fld(f, y, x0, c, j);
+  if (Z::active()) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const long long base = ((long long)(j + r * (N / 8)) * N + y) * N + x0 + c;
-      v[r] = make_float2(f[base], f[base + WP]);
-    }
+    for (int r = 0; r < Z::E; ++r) v[r] = make_float2(fld.load(r, 0), fld.load(r, 1));
   }
-  fft_rl<N, WP, false, false>(v, buf, tw);
-  z_unpack_store<N, WP, NT, false>(buf, o + b * cn, y, x0, 0.f);
+  Z::template fft_lds<false>(v, buf, tw, c, j);
+  Z::template unpack<false>(buf, o + b * cn, y, x0, 0.f);
 }
 
 // Inverse z transform of the smoothed galaxy (and random) densities, overdensity in
@@ -1110,27 +1285,27 @@ __global__ void __launch_bounds__(ntz<N>()) k_z_fwd_real(const float* __restrict
 //   with randoms:  delta = m (G - alpha R) / (alpha R), 0 outside the mask or where R <= 0
 //   mean density:  delta = G / rho_bar - 1
 template <int N, int NA>
-__global__ void __launch_bounds__(ntz<N>()) k_z_delta(float2* __restrict__ a0, const float2* __restrict__ a1,
+__global__ void __launch_bounds__(ntz<N>(), N == 512 ? 4 : 1) k_z_delta(float2* __restrict__ a0, const float2* __restrict__ a1,
                                                       const unsigned char* __restrict__ mask,
                                                       const DeltaScal* __restrict__ sc, float* __restrict__ delta_out,
                                                       float log_floor, double* __restrict__ partials,
                                                       const float2* __restrict__ twg,
                                                       const unsigned char* __restrict__ mflag = nullptr) {
   constexpr int NT = ntz<N>(), WP = wz<N>();
-  using L = Lay<N, WP, false>;
-  __shared__ float2 buf[L::SIZE];
+  using Z = ZTile<N>;
+  __shared__ float2 buf[Z::SIZE];
   __shared__ float2 tw[N];
   stage_twiddles<N, NT>(tw, twg);
   int y, x0, c, j;
   z_tile_coords<N, WP>(y, x0);
-  frag_coords<N, WP, false>(c, j);
-  const bool act = threadIdx.x < L::NTF;
+  Z::coords(c, j);
+  const bool act = Z::active();
   const long long n3 = (long long)N * N * N, cn = (long long)(N / 2 + 1) * N * N;
   const int b = blockIdx.y;
   a0 += b * cn;
   const DeltaScal s = sc[b];
   double lsum = 0.0;
-  float2 gv[8], v[8];
+  float2 gv[Z::E], v[Z::E];
   if constexpr (NA == 2) {
     // a tile outside the survey mask (mask-tile flag 0) has delta_s = 0 in every cell (also after the
     // lognormal transform, ln 1 = 0): its spectrum is zero and no transform is needed; it is not
@@ -1146,33 +1321,60 @@ __global__ void __launch_bounds__(ntz<N>()) k_z_delta(float2* __restrict__ a0, c
       }
       return;
     }
-    // the second array is staged in LDS by direct loads while the first is transformed
-    __shared__ float2 stage[ZStage<N, WP>::SIZE];
-    z_stage_issue<N, WP, NT>(stage, a0, y, x0);
-    z_stage_wait();
+    if constexpr (z_col<N>()) {
+      // the second array's loads run under the first one's transform
+      using C = ZCol<N>;
+      typename C::Half h;
+      C::fetch(h, a0, y, x0);
+      C::put(h, buf);
+      C::fetch(h, a1 + b * cn, y, x0);
+      __syncthreads();
+      C::frag(gv, buf, c, j);
+      Z::template fft<true>(gv, buf, tw, c, j);
+      __syncthreads();
+      C::put(h, buf);
+      __syncthreads();
+      C::frag(v, buf, c, j);
+      Z::template fft<true>(v, buf, tw, c, j);
+    } else {
+      // the second array is staged in LDS by direct loads while the first is transformed
+      __shared__ float2 stage[ZStage<N, WP>::SIZE];
+      z_stage_issue<N, WP, NT>(stage, a0, y, x0);
+      z_stage_wait();
+      __syncthreads();
+      if (act) z_pack_stage<N, WP>(gv, stage, c, j);
+      __syncthreads();
+      z_stage_issue<N, WP, NT>(stage, a1 + b * cn, y, x0);
+      fft_rr<N, WP, true, false>(gv, buf, tw);
+      z_stage_wait();
+      __syncthreads();
+      if (act) z_pack_stage<N, WP>(v, stage, c, j);
+      fft_rr<N, WP, true, false>(v, buf, tw);
+    }
+  } else if constexpr (z_col<N>()) {
+    using C = ZCol<N>;
+    typename C::Half h;
+    C::fetch(h, a0, y, x0);
+    C::put(h, buf);
     __syncthreads();
-    if (act) z_pack_stage<N, WP>(gv, stage, c, j);
-    __syncthreads();
-    z_stage_issue<N, WP, NT>(stage, a1 + b * cn, y, x0);
-    fft_rr<N, WP, true, false>(gv, buf, tw);
-    z_stage_wait();
-    __syncthreads();
-    if (act) z_pack_stage<N, WP>(v, stage, c, j);
-    fft_rr<N, WP, true, false>(v, buf, tw);
+    C::frag(gv, buf, c, j);
+    Z::template fft<true>(gv, buf, tw, c, j);
   } else {
     if (act) z_pack_frag<N, WP>(gv, a0, y, x0, c, j);
     fft_rr<N, WP, true, false>(gv, buf, tw);
   }
   if (act) {
+    const ZField<N, 1> msk(mask + b * n3, y, x0, c, j);
+    const ZField<N, 4> dout(delta_out + b * n3, y, x0, c, j);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const long long cell = ((long long)(j + r * (N / 8)) * N + y) * N + x0 + c;
+    for (int r = 0; r < Z::E; ++r) {
       float d0, d1;
       if constexpr (NA == 2) {
-        const unsigned char* m = mask + b * n3;
         const float ar0 = s.alpha * v[r].x, ar1 = s.alpha * v[r].y;
-        d0 = (m[cell] && ar0 > 0.f) ? (gv[r].x - ar0) / ar0 : 0.f;
-        d1 = (m[cell + WP] && ar1 > 0.f) ? (gv[r].y - ar1) / ar1 : 0.f;
+        const bool in0 = (msk.load_byte(r, 0) != 0) & (ar0 > 0.f), in1 = (msk.load_byte(r, 1) != 0) & (ar1 > 0.f);
+        const float q0 = (gv[r].x - ar0) / ar0, q1 = (gv[r].y - ar1) / ar1;
+        d0 = in0 ? q0 : 0.f;
+        d1 = in1 ? q1 : 0.f;
       } else {
         d0 = gv[r].x * s.inv_rhobar - 1.f;
         d1 = gv[r].y * s.inv_rhobar - 1.f;
@@ -1184,9 +1386,10 @@ __global__ void __launch_bounds__(ntz<N>()) k_z_delta(float2* __restrict__ a0, c
       }
       v[r] = make_float2(d0, d1);
       if (delta_out) {
-        delta_out[b * n3 + cell] = d0;
-        delta_out[b * n3 + cell + WP] = d1;
+        dout.store(d0, r, 0);
+        dout.store(d1, r, 1);
       }
+      if (z_col<N>() && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
   }
   if (log_floor > 0.f) {
@@ -1197,8 +1400,8 @@ __global__ void __launch_bounds__(ntz<N>()) k_z_delta(float2* __restrict__ a0, c
       partials[2 * ((long long)b * gridDim.x + blockIdx.x) + 1] = 0.0;
     }
   }
-  fft_rl<N, WP, false, false>(v, buf, tw);
-  z_unpack_store<N, WP, NT, false>(buf, a0, y, x0, 0.f);
+  Z::template fft_lds<false>(v, buf, tw, c, j);
+  Z::template unpack<false>(buf, a0, y, x0, 0.f);
 }
 
 // Lognormal option: add C = -<ln(max(1 + delta, floor))> (sums[2 b] = sum over the n^3 cells of
@@ -1224,12 +1427,12 @@ __global__ void __launch_bounds__(256) k_log_shift(float* __restrict__ delta, lo
 // a start, ZI_CROSS iterates as ZI_PLAIN and accumulates S3 = sum Delta u_1 (second entry 0), the
 // cross term of ||Psi_1 - Psi_0||^2.
 template <int N, int MODE, int SPLIT = 0>
-__global__ void __launch_bounds__(ntz<N>()) k_z_iter(float2* __restrict__ a0, float2* __restrict__ a1,
+__global__ void __launch_bounds__((ntzs<N, SPLIT>())) k_z_iter(float2* __restrict__ a0, float2* __restrict__ a1,
                                                      const float2* __restrict__ a2, Geo g, float* __restrict__ corr,
                                                      double* __restrict__ partials, const int* __restrict__ active,
                                                      const float2* __restrict__ twg,
                                                      const float* __restrict__ up_in = nullptr) {
-  constexpr int NT = ntz<N>(), WP = wz<N>(), TPB = ztpb<N, MODE, SPLIT>();
+  constexpr int NT = ntzs<N, SPLIT>(), WP = wzs<N, SPLIT>(), TPB = ztpb<N, MODE, SPLIT>();
   using L = Lay<N, WP, false>;
   const int b = blockIdx.y;
   if (active && !active[b]) return;
@@ -1252,9 +1455,9 @@ __global__ void __launch_bounds__(ntz<N>()) k_z_iter(float2* __restrict__ a0, fl
   // py < 0: nothing deferred
   constexpr bool DEFER = RECON_Z_DEFER && MODE != ZI_LEARNED;
   int py = -1, px0 = 0;
-  if (MODE != ZI_LEARNED && tile < ztiles<N>()) z_stage_issue<N, WP, NT>(stage, a0, y, x0);
+  if (MODE != ZI_LEARNED && tile < (ztiles<N, SPLIT>())) z_stage_issue<N, WP, NT>(stage, a0, y, x0);
 #pragma unroll 1
-  for (int t = 0; t < TPB && tile < ztiles<N>(); ++t) {     // block-uniform bound
+  for (int t = 0; t < TPB && tile < (ztiles<N, SPLIT>()); ++t) {     // block-uniform bound
     int c, j;
     frag_coords<N, WP, false>(c, j);
     const float ry = los_comp(g, 1, y);
@@ -1273,7 +1476,7 @@ __global__ void __launch_bounds__(ntz<N>()) k_z_iter(float2* __restrict__ a0, fl
       z_stage_wait();
       __syncthreads();
       if (act) z_pack_stage<N, WP>(v, stage, c, j);
-      if (t + 1 < TPB && next < ztiles<N>()) {
+      if (t + 1 < TPB && next < (ztiles<N, SPLIT>())) {
         __syncthreads();
         z_tile_at<N, WP>(next, ny, nx0);
         z_stage_issue<N, WP, NT>(stage, a0, ny, nx0);
@@ -1342,235 +1545,191 @@ __global__ void __launch_bounds__(ntz<N>()) k_z_iter(float2* __restrict__ a0, fl
   }
 }
 
-// The plain z iteration of k_z_iter with wave-local transforms (N = 512): the wave of packed column
-// c transforms that column in its own LDS region, so the only block barriers of a tile are those
-// of the staging and of the stores (6 per tile instead of about 22).  The staged tile is skewed: row
-// m's 16-byte piece p sits in slot (p - m) mod 16 of the row, so that a wave reading one column down
-// 64 consecutive rows spreads over every bank; the per-wave regions are 577 float2 apart, so that the
-// stores, which read one row of 16 columns at a time, do too.
-template <int N, int WP>
-__device__ __forceinline__ void z_stage_issue_skew(float2* stage, const float2* __restrict__ a, int y, int x0) {
-  using S = ZStage<N, WP>;
-  static_assert(S::LPR == 16, "skewed staging takes rows of 16 pieces");
-  constexpr int NT = 1024;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int q = wave; q < S::NCH; q += NT / 64) {
-    const int m = q * S::RPC + lane / S::LPR;
-    const long long e = ((long long)m * N + y) * N + x0 + 2 * (((lane % S::LPR) + m) & 15);
-    if (m < S::ROWS && in_bounds(e + 1, (long long)(N / 2 + 1) * N * N)) {
-      __builtin_amdgcn_global_load_lds((const void*)(a + e),
-                                       (__attribute__((address_space(3))) void*)(stage + q * 128), 16, 0,
-                                       kStageCachePolicy);
-    }
-  }
-}
-
-template <int N, int WP>
-__device__ __forceinline__ float2 z_stage_at_skew(const float2* stage, int m, int col) {
-  return stage[m * 2 * WP + 2 * (((col >> 1) - m) & 15) + (col & 1)];
-}
-
-// z_pack_stage for the wave layout: column c, rows j + 64 r
-template <int N, int WP>
-__device__ __forceinline__ void z_pack_stage_w(float2* v, const float2* stage, int c, int j) {
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const int k = j + r * (N / 8);
-    const int m = k <= N / 2 ? k : N - k;
-    const float2 A = z_stage_at_skew<N, WP>(stage, m, c), B = z_stage_at_skew<N, WP>(stage, m, c + WP);
-    if (k == 0 || k == N / 2) v[r] = make_float2(A.x, B.x);
-    else if (k < N / 2) v[r] = make_float2(A.x - B.y, A.y + B.x);
-    else v[r] = make_float2(A.x + B.y, B.x - A.y);
-  }
-}
-
-constexpr int kWaveRegion = 512 + 512 / 8 + 1;   // float2 per wave region
-
-// z_unpack_store from the per-wave regions (column p in region p, natural order)
-template <int N, int WP, int NT, bool MULK>
-__device__ __forceinline__ void z_unpack_store_w(const float2* wreg, float2* __restrict__ out, int y, int x0,
-                                                 float kf) {
-  for (int e = threadIdx.x; e < (N / 2 + 1) * WP; e += NT) {
-    const int p = e % WP, kz = e / WP;
-    const float2 Z = wreg[p * kWaveRegion + wat(kz)];
-    const float2 M = wreg[p * kWaveRegion + wat((N - kz) & (N - 1))];
-    float2 A = make_float2(0.5f * (Z.x + M.x), 0.5f * (Z.y - M.y));
-    float2 B = make_float2(0.5f * (Z.y + M.y), 0.5f * (M.x - Z.x));
-    if (MULK) {
-      const float k = kf * deriv_mode<N>(kz);
-      A = mul_i(A) * k;
-      B = mul_i(B) * k;
-    }
-    const long long base = ((long long)kz * N + y) * N + x0 + p;
-    constexpr long long CN = (long long)(N / 2 + 1) * N * N;
-    if (in_bounds(base, CN)) st_stream(out + base, A);
-    if (in_bounds(base + WP, CN)) st_stream(out + base + WP, B);
-  }
-}
-
-template <int N>
-__global__ void __launch_bounds__(1024) k_z_iter_w(float2* __restrict__ a0, float2* __restrict__ a1,
-                                                   const float2* __restrict__ a2, Geo g,
-                                                   const int* __restrict__ active, const float2* __restrict__ twg) {
-  static_assert(N == 512, "wave-local z iteration: one radix-8 fragment per lane of a 64-lane wave");
-  constexpr int WP = wz<N>(), NT = 1024, TPB = ztpb<N, ZI_PLAIN>();
-  static_assert(WP == 16 && (N / 8) * WP == NT, "one wave per packed column");
+// The z iteration of k_z_iter on the column engine, one tile per block.  It moves 4 spectrum passes (2.15 GB
+// at 512^3, 0.34 ms at the chip's streaming rate); what bounds it is the latency of a block's own chain of
+// loads, three transforms and stores, so the blocks are small (N threads) and two or more share a CU, one
+// loading or storing while another transforms.  512^3 0.556 -> 0.462 ms (1024-thread blocks of the radix-8
+// engine with wave-local transforms before), 256^3 69 -> 56 us, 1024^3 8.4 -> 6.3 ms.
+template <int N, int MODE>
+__global__ void __launch_bounds__(N, N == 512 ? 4 : 1) k_z_iter_c(float2* __restrict__ a0, float2* __restrict__ a1,
+                                                  const float2* __restrict__ a2, Geo g, float* __restrict__ corr,
+                                                  double* __restrict__ partials, const int* __restrict__ active,
+                                                  const float2* __restrict__ twg,
+                                                  const float* __restrict__ up_in = nullptr) {
+  using C = ZCol<N>;
+  using G = Col<N>;
+  constexpr int WP = C::WP;
   const int b = blockIdx.y;
   if (active && !active[b]) return;
-  __shared__ float2 wreg[WP * kWaveRegion];
+  __shared__ float2 buf[G::SIZE];
   __shared__ float2 tw[N];
-  __shared__ float2 stage[ZStage<N, WP>::SIZE];
-  stage_twiddles<N, NT>(tw, twg);
-  const long long cn = (long long)(N / 2 + 1) * N * N;
+  stage_twiddles<N, N>(tw, twg);
+  const long long n3 = (long long)N * N * N, cn = (long long)(N / 2 + 1) * N * N;
   a0 += b * cn; a1 += b * cn; a2 += b * cn;
-  int tile = blockIdx.x, y, x0;
-  z_tile_at<N, WP>(tile, y, x0);
-  if (tile < ztiles<N>()) z_stage_issue_skew<N, WP>(stage, a0, y, x0);
-  z_stage_wait();
-  __syncthreads();                                     // first tile staged
-  // Waits: the staging waits (vmcnt(0)) also wait for every store a wave has issued.  The next tile's
-  // first array is therefore waited for after the inverse transform of v, not at the top of the loop:
-  // the stores of Z[q] have drained under that transform, and the stores of Z[r_z q], issued after
-  // the wait, drain under the next tile's packing and first transform.
-#pragma unroll 1
-  for (int t = 0; t < TPB && tile < ztiles<N>(); ++t) {   // block-uniform bound
-    // the lane's row and column are taken afresh in every tile: the addresses and line-of-sight
-    // components derived from them are recomputed (a few integer and FMA operations) instead of
-    // being held in registers across the loop, which would spill
-    int j = threadIdx.x & 63, c = threadIdx.x >> 6;
-    asm volatile("" : "+v"(j), "+v"(c));
-    float2* reg = wreg + c * kWaveRegion;
-    const float ry = los_comp(g, 1, y);
-    const float rx0 = los_comp(g, 0, x0 + c), rx1 = los_comp(g, 0, x0 + c + WP);
-    const int next = tile + gridDim.x;
-    int ny = y, nx0 = x0;
-    float2 s[8], v[8];
-    z_pack_stage_w<N, WP>(s, stage, c, j);
-    __syncthreads();                                   // every wave has read the staged tile
-    z_stage_issue_skew<N, WP>(stage, a2, y, x0);
-    wfft_rr<true>(s, reg, tw, j);
-    z_stage_wait();
+  int y, x0, c, j;
+  z_tile_coords<N, WP>(y, x0);
+  G::coords(c, j);
+  float2 s[16], v[16];
+  if constexpr (MODE != ZI_LEARNED) {
+    // Psi_z's loads run under the transverse part's transform
+    typename C::Half h;
+    C::fetch(h, a0, y, x0);
+    C::put(h, buf);
+    C::fetch(h, a2, y, x0);
     __syncthreads();
-    z_pack_stage_w<N, WP>(v, stage, c, j);
+    C::frag(s, buf, c, j);
+    col_fft<N, true>(s, buf, tw, c, j);
     __syncthreads();
-    if (t + 1 < TPB && next < ztiles<N>()) {
-      z_tile_at<N, WP>(next, ny, nx0);
-      z_stage_issue_skew<N, WP>(stage, a0, ny, nx0);
-    }
-    wfft_rr<true>(v, reg, tw, j);
-    // s = Psi . r (two columns packed as .x / .y) -> q = u / |r|, so that V_j = q r_j
+    C::put(h, buf);
+    __syncthreads();
+    C::frag(v, buf, c, j);
+    col_fft<N, true>(v, buf, tw, c, j);
+  } else {
+    __syncthreads();                                    // the twiddle factors
+  }
+  // s = Psi . r (two columns packed as .x / .y) -> q = u_0 / |r|, so that V_j = q r_j
+  float acc1 = 0.f, acc2 = 0.f;          // 32 terms per thread; block and grid sums in FP64
+  const float ry = los_comp(g, 1, y);
+  const float rx0 = los_comp(g, 0, x0 + c), rx1 = los_comp(g, 0, x0 + c + WP);
+  const ZField<N, 4> cf(corr + b * n3, y, x0, c, j), uf(up_in + b * n3, y, x0, c, j);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const float rz = los_comp(g, 2, j + r * (N / 8));
-      s[r] = make_float2(fmaf(rz, v[r].x, s[r].x), fmaf(rz, v[r].y, s[r].y));
+  for (int r = 0; r < 16; ++r) {
+    const int z = j + r * G::T;
+    const float rz = los_comp(g, 2, z);
+    if (MODE != ZI_LEARNED) s[r] = make_float2(fmaf(rz, v[r].x, s[r].x), fmaf(rz, v[r].y, s[r].y));
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const float r2 = los_r2(h ? rx1 : rx0, ry, rz);
-        const float ir = r2 > 0.f ? rsqrtf(r2) : 0.f;
-        const float q = ((h ? s[r].y : s[r].x) * ir) * ir;
-        if (h) s[r].y = q; else s[r].x = q;
+    for (int h = 0; h < 2; ++h) {
+      const float rx = h ? rx1 : rx0;
+      const float r2 = los_r2(rx, ry, rz);
+      const float ir = r2 > 0.f ? rsqrtf(r2) : 0.f;
+      // u_p = Psi . r_hat
+      const float up = MODE == ZI_LEARNED ? uf.load(r, h) : (h ? s[r].y : s[r].x) * ir;
+      float u0 = up;
+      if (MODE != ZI_PLAIN) {
+        float dlt;
+        if (MODE == ZI_FFTA) {
+          u0 = g.start_scale * up;
+          dlt = u0 - up;
+          cf.store(dlt, r, h);
+        } else {
+          const float in = cf.load(r, h);
+          dlt = r2 > 0.f ? in : 0.f;
+          if (MODE == ZI_LEARNED) u0 = up + dlt;
+        }
+        acc1 = fmaf(dlt, up, acc1);
+        if (MODE != ZI_CROSS) acc2 = fmaf(dlt, dlt, acc2);
       }
-      v[r] = s[r] * rz;
+      const float q = u0 * ir;
+      if (h) s[r].y = q; else s[r].x = q;
     }
-    wfft_rl<false>(s, reg, tw, j);
-    __syncthreads();                                   // every column of Z[q] is in its region
-    z_unpack_store_w<N, WP, NT, false>(wreg, a0, y, x0, g.kf);
-    __syncthreads();                                   // the regions are free
-    wfft_rl<false>(v, reg, tw, j);
-    z_stage_wait();
-    __syncthreads();                                   // Z[r_z q] in the regions; the next tile staged
-    z_unpack_store_w<N, WP, NT, true>(wreg, a1, y, x0, g.kf);
-    // (the barrier after the next tile's packing orders these reads of the regions before its transforms)
-    tile = next; y = ny; x0 = nx0;
+    v[r] = s[r] * rz;
+    if (MODE != ZI_PLAIN && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // few loads in flight at a time
+  }
+  // Z[q] -> a0 and i k'_z Z[r_z q] -> a1
+  col_fft_lds<N, false>(s, buf, tw, c, j);
+  C::template unpack<false>(buf, a0, y, x0, g.kf);
+  col_fft_lds<N, false>(v, buf, tw, c, j);
+  C::template unpack<true>(buf, a1, y, x0, g.kf);
+  if (MODE != ZI_PLAIN) {
+    double t1, t2;
+    block_sum2<N>((double)acc1, (double)acc2, &t1, &t2);
+    if (threadIdx.x == 0) {
+      const long long nb = gridDim.x;
+      partials[2 * (b * nb + blockIdx.x) + 0] = t1;
+      partials[2 * (b * nb + blockIdx.x) + 1] = t2;
+    }
   }
 }
 
-// Inverse z of the displacement spectra.  Full state (COMB = false, a0..a2 = Psi_x, Psi_y, Psi_z):
-// writes Psi (planar [b][3][N^3], when psi != null), u = Psi . r_hat (when u_out != null) and accumulates
-// S3 = sum corr * u (when corr != null).  Combined state (COMB = true, a0 = r_x Psi_x + r_y Psi_y,
-// a2 = Psi_z): writes u only (psi and corr must be null).
-template <int N, bool COMB>
-__global__ void __launch_bounds__(ntz<N>()) k_z_final(const float2* __restrict__ a0, const float2* __restrict__ a1,
+// Inverse z of the displacement spectra.
+//   ZF_PSI:   full state (a0..a2 = Psi_x, Psi_y, Psi_z): writes Psi (planar [b][3][N^3])
+//   ZF_CROSS: the same, and the block's partial sum of corr * u with u = Psi . r_hat
+//   ZF_U:     combined state (a0 = r_x Psi_x + r_y Psi_y, a2 = Psi_z): writes u to u_out
+// One component is transformed and written at a time; only the running Psi . r is held beside it.
+enum ZFinalKind { ZF_PSI = 0, ZF_CROSS = 1, ZF_U = 2 };
+template <int N, int KIND>
+__global__ void __launch_bounds__(ntz<N>(), N == 512 ? 4 : 1) k_z_final(const float2* __restrict__ a0, const float2* __restrict__ a1,
                                                       const float2* __restrict__ a2, Geo g, float* __restrict__ psi,
                                                       float* __restrict__ u_out, const float* __restrict__ corr,
                                                       double* __restrict__ partials, const int* __restrict__ active,
                                                       const float2* __restrict__ twg) {
   constexpr int NT = ntz<N>(), WP = wz<N>();
-  using L = Lay<N, WP, false>;
+  using Z = ZTile<N>;
   const int b = blockIdx.y;
   if (active && !active[b]) return;
-  __shared__ float2 buf[L::SIZE];
+  __shared__ float2 buf[Z::SIZE];
   __shared__ float2 tw[N];
+  __shared__ float2 stage[z_col<N>() ? 1 : ZStage<N, WP>::SIZE];   // radix-8 engine only
   stage_twiddles<N, NT>(tw, twg);
   int y, x0, c, j;
   z_tile_coords<N, WP>(y, x0);
-  frag_coords<N, WP, false>(c, j);
-  const bool act = threadIdx.x < L::NTF;
+  Z::coords(c, j);
+  const bool act = Z::active();
   const long long n3 = (long long)N * N * N, cn = (long long)(N / 2 + 1) * N * N;
-  a0 += b * cn; a1 += b * cn; a2 += b * cn;
-  // each array is staged in LDS by direct loads while the previous one is transformed
-  __shared__ float2 stage[ZStage<N, WP>::SIZE];
-  z_stage_issue<N, WP, NT>(stage, a0, y, x0);
-  z_stage_wait();
-  __syncthreads();
-  float2 px[8], py[8], v[8];
-  if (act) z_pack_stage<N, WP>(px, stage, c, j);
-  __syncthreads();
-  if (!COMB) {
-    z_stage_issue<N, WP, NT>(stage, a1, y, x0);
-    fft_rr<N, WP, true, false>(px, buf, tw);
-    z_stage_wait();
-    __syncthreads();
-    if (act) z_pack_stage<N, WP>(py, stage, c, j);
-    __syncthreads();
-  }
-  z_stage_issue<N, WP, NT>(stage, a2, y, x0);
-  fft_rr<N, WP, true, false>(COMB ? px : py, buf, tw);
-  z_stage_wait();
-  __syncthreads();
-  if (act) z_pack_stage<N, WP>(v, stage, c, j);
-  fft_rr<N, WP, true, false>(v, buf, tw);
+  const float2* src[3] = {a0 + b * cn, (KIND == ZF_U ? a2 : a1) + b * cn, a2 + b * cn};
+  constexpr int NC = KIND == ZF_U ? 2 : 3;
   const float ry = los_comp(g, 1, y);
   const float rx0 = los_comp(g, 0, x0 + c), rx1 = los_comp(g, 0, x0 + c + WP);
-  double acc = 0.0;
-  if (act) {
+  typename ZHalf<N>::type h;
+  if constexpr (z_col<N>()) ZCol<N>::fetch(h, src[0], y, x0);
+  else z_stage_issue<N, WP, NT>(stage, src[0], y, x0);
+  float2 v[Z::E], s[Z::E];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int z = j + r * (N / 8);
-      const long long cell = b * n3 + ((long long)z * N + y) * N + x0 + c;
-      if (!COMB && psi) {
-        float* pb = psi + 3 * b * n3;
-        const long long c0 = cell - b * n3, c1 = c0 + WP;
-        if (in_bounds(c1, n3)) {
-          pb[c0] = px[r].x;
-          pb[c1] = px[r].y;
-          pb[n3 + c0] = py[r].x;
-          pb[n3 + c1] = py[r].y;
-          pb[2 * n3 + c0] = v[r].x;
-          pb[2 * n3 + c1] = v[r].y;
-        }
-      }
-      if (u_out || (!COMB && corr)) {
-        const float rz = los_comp(g, 2, z);
+  for (int k = 0; k < NC; ++k) {
+    // the next array's loads run under this one's transform
+    if constexpr (z_col<N>()) {
+      if (k) __syncthreads();
+      ZCol<N>::put(h, buf);
+      if (k + 1 < NC) ZCol<N>::fetch(h, src[k + 1], y, x0);
+      __syncthreads();
+      ZCol<N>::frag(v, buf, c, j);
+    } else {
+      z_stage_wait();
+      __syncthreads();
+      if (act) z_pack_stage<N, WP>(v, stage, c, j);
+      __syncthreads();
+      if (k + 1 < NC) z_stage_issue<N, WP, NT>(stage, src[k + 1], y, x0);
+    }
+    Z::template fft<true>(v, buf, tw, c, j);
+    if (!act) continue;
+    if (KIND != ZF_U) {
+      const ZField<N, 4> f(psi + (3 * b + k) * n3, y, x0, c, j);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const float rx = h ? rx1 : rx0;
-          const float r2 = los_r2(rx, ry, rz);
-          const float ir = r2 > 0.f ? rsqrtf(r2) : 0.f;
-          float u;
-          if (COMB) {
-            u = fmaf(rz, h ? v[r].y : v[r].x, h ? px[r].y : px[r].x) * ir;
-          } else {
-            const float sx = h ? px[r].y : px[r].x, sy = h ? py[r].y : py[r].x, sz = h ? v[r].y : v[r].x;
-            u = (rx * sx + ry * sy + rz * sz) * ir;
-          }
-          if (u_out) u_out[cell + h * WP] = u;
-          if (!COMB && corr) acc += (double)corr[cell + h * WP] * (double)u;
+      for (int r = 0; r < Z::E; ++r) {
+        if (in_bounds(((long long)(j + r * Z::ST) * N + y) * N + x0 + c + WP, n3)) {
+          f.store(v[r].x, r, 0);
+          f.store(v[r].y, r, 1);
         }
       }
     }
+    if (KIND == ZF_PSI) continue;
+#pragma unroll
+    for (int r = 0; r < Z::E; ++r) {
+      const float rz = los_comp(g, 2, j + r * Z::ST);
+      if (k == 0) s[r] = KIND == ZF_U ? v[r] : make_float2(rx0 * v[r].x, rx1 * v[r].y);
+      else if (KIND == ZF_CROSS && k == 1) s[r] = make_float2(fmaf(ry, v[r].x, s[r].x), fmaf(ry, v[r].y, s[r].y));
+      else s[r] = make_float2(fmaf(rz, v[r].x, s[r].x), fmaf(rz, v[r].y, s[r].y));
+    }
   }
-  if (!COMB && corr) {
+  if (KIND == ZF_PSI) return;
+  double acc = 0.0;
+  if (act) {
+    const ZField<N, 4> f(KIND == ZF_U ? u_out + b * n3 : corr + b * n3, y, x0, c, j);
+#pragma unroll
+    for (int r = 0; r < Z::E; ++r) {
+      const float rz = los_comp(g, 2, j + r * Z::ST);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const float r2 = los_r2(q ? rx1 : rx0, ry, rz);
+        const float ir = r2 > 0.f ? rsqrtf(r2) : 0.f;
+        const float u = (q ? s[r].y : s[r].x) * ir;
+        if (KIND == ZF_U) f.store(u, r, q);
+        else acc += (double)f.load(r, q) * (double)u;
+      }
+      if (z_col<N>() && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (KIND == ZF_CROSS) {
     double t1, t2;
     block_sum2<NT>(acc, 0.0, &t1, &t2);
     if (threadIdx.x == 0) {
@@ -1633,25 +1792,47 @@ __device__ __forceinline__ void y_tile_coords(int& p, int& x0) {
   x0 = (blockIdx.x % (N / W)) * W;
 }
 
-// Non-temporal loads in the y passes only where a tile row is a whole 128-byte line (16 columns).
-template <int N> constexpr bool y_hint() { return wy<N>() >= 16; }
+// Tile, fragment coordinates and transform of a y pass, on the engine of its size (COL: the column engine;
+// the tile is the same on both).
+template <int N, bool COL = y_col<N>()>
+struct YTile {
+  static constexpr int W = wy<N>(), E = COL ? 16 : 8, ST = N / E, NT = COL ? N : frag_threads<N, W>();
+  static constexpr int SIZE = [] {
+    if constexpr (COL) return Col<N>::SIZE;
+    else return Lay<N, W, false>::SIZE;
+  }();
+  __device__ __forceinline__ static void coords(int& c, int& j) {
+    if constexpr (COL) Col<N>::coords(c, j);
+    else frag_coords<N, W, false>(c, j);
+  }
+  __device__ __forceinline__ static bool active() { return COL || threadIdx.x < Lay<N, W, false>::NTF; }
+  template <bool INV>
+  __device__ __forceinline__ static void fft(float2* v, float2* buf, const float2* tw, int c, int j) {
+    if constexpr (COL) col_fft<N, INV>(v, buf, tw, c, j);
+    else fft_rr<N, W, INV, false>(v, buf, tw);
+  }
+};
 
+// Element r of a fragment is row j + r ST of plane p.
 template <int N>
 __device__ __forceinline__ void y_load(float2* v, const float2* __restrict__ a, int p, int x0, int c, int j) {
+  const PlaneBuf pl(a + (long long)p * N * N, (unsigned)N * N * 8);
+  const unsigned lane = ((unsigned)j * N + x0 + c) * 8;
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const long long e = ((long long)p * N + j + r * (N / 8)) * N + x0 + c;
-    v[r] = in_bounds(e, (long long)(N / 2 + 1) * N * N) ? ld_stream<y_hint<N>()>(a + e) : float2{};
-  }
+  for (int r = 0; r < y_el<N>(); ++r)
+    v[r] = in_bounds((long long)p * N * N + lane / 8 + r * y_st<N>() * N, (long long)(N / 2 + 1) * N * N)
+               ? pl.template load<(RECON_STREAM & 2) != 0>(lane, r * y_st<N>() * N * 8)
+               : float2{};
 }
 
 template <int N>
 __device__ __forceinline__ void y_store(const float2* v, float2* __restrict__ a, int p, int x0, int c, int j) {
+  const PlaneBuf pl(a + (long long)p * N * N, (unsigned)N * N * 8);
+  const unsigned lane = ((unsigned)j * N + x0 + c) * 8;
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const long long e = ((long long)p * N + j + r * (N / 8)) * N + x0 + c;
-    if (in_bounds(e, (long long)(N / 2 + 1) * N * N)) st_stream(a + e, v[r]);
-  }
+  for (int r = 0; r < y_el<N>(); ++r)
+    if (in_bounds((long long)p * N * N + lane / 8 + r * y_st<N>() * N, (long long)(N / 2 + 1) * N * N))
+      pl.template store<(RECON_STREAM & 1) != 0>(v[r], lane, r * y_st<N>() * N * 8);
 }
 
 // Row flags (flag != null): one byte per z tile (one y row, 2 wz consecutive x), [NA][batch][z tiles]
@@ -1660,21 +1841,21 @@ __device__ __forceinline__ void y_store(const float2* v, float2* __restrict__ a,
 // such rows are not stored (the z pass that follows does not read them).
 
 template <int N, int NA, bool INV>
-__global__ void __launch_bounds__(nty<N>()) k_y_plain(float2* __restrict__ a0, float2* __restrict__ a1,
+__global__ void __launch_bounds__((YTile<N, yp_col<N>()>::NT)) k_y_plain(float2* __restrict__ a0, float2* __restrict__ a1,
                                                       const float2* __restrict__ twg,
                                                       const unsigned char* __restrict__ flag = nullptr) {
-  constexpr int NT = nty<N>(), W = wy<N>(), NZT = N / (2 * wz<N>());
+  using Y = YTile<N, yp_col<N>()>;
+  constexpr int NT = Y::NT, W = Y::W, NZT = N / (2 * wz<N>());
   static_assert((2 * wz<N>()) % W == 0, "a y tile lies inside one z tile");
   constexpr int NF = INV ? 1 : NA;                     // flag sets: per array (forward) or shared (inverse)
-  using L = Lay<N, W, false>;
-  __shared__ float2 buf[L::SIZE];
+  __shared__ float2 buf[Y::SIZE];
   __shared__ float2 tw[N];
   __shared__ unsigned char live[NF][N];                // the tile's row flags, staged with the twiddles
   stage_twiddles<N, NT>(tw, twg);
   int p, x0, c, j;
   y_tile_coords<N, W>(p, x0);
-  frag_coords<N, W, false>(c, j);
-  const bool act = threadIdx.x < L::NTF;
+  Y::coords(c, j);
+  const bool act = Y::active();
   const long long cn = (long long)(N / 2 + 1) * N * N;
   const int b = blockIdx.y;
   if (flag) {
@@ -1686,25 +1867,25 @@ __global__ void __launch_bounds__(nty<N>()) k_y_plain(float2* __restrict__ a0, f
   }
 #pragma unroll
   for (int a = 0; a < NA; ++a) {
-    float2* arr = (a == 0 ? a0 : a1) + b * cn;
+    const PlaneBuf pl((a == 0 ? a0 : a1) + b * cn + (long long)p * N * N, (unsigned)N * N * 8);
     const unsigned char* lv = live[INV ? 0 : a];
-    float2 v[8];
+    const unsigned lane = ((unsigned)j * N + x0 + c) * 8;
+    // a row that is not live is read as zero (forward) or not stored (inverse): its lane offset lies past
+    // the plane's end
+    auto at = [&](int r, bool skip) {
+      const bool out = (skip && flag && !lv[j + r * Y::ST]) ||
+                       !in_bounds((long long)p * N * N + lane / 8 + r * Y::ST * N, cn);
+      return out ? 0x80000000u : lane;
+    };
+    float2 v[Y::E];
     if (act) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int yy = j + r * (N / 8);
-        const long long e = ((long long)p * N + yy) * N + x0 + c;
-        v[r] = (in_bounds(e, cn) && (INV || !flag || lv[yy])) ? ld_stream<y_hint<N>()>(arr + e) : float2{};
-      }
+      for (int r = 0; r < Y::E; ++r) v[r] = pl.template load<(RECON_STREAM & 2) != 0>(at(r, !INV), r * Y::ST * N * 8);
     }
-    fft_rr<N, W, INV, false>(v, buf, tw);
+    Y::template fft<INV>(v, buf, tw, c, j);
     if (act) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int yy = j + r * (N / 8);
-        const long long e = ((long long)p * N + yy) * N + x0 + c;
-        if (in_bounds(e, cn) && (!INV || !flag || lv[yy])) st_stream(arr + e, v[r]);
-      }
+      for (int r = 0; r < Y::E; ++r) pl.template store<(RECON_STREAM & 1) != 0>(v[r], at(r, INV), r * Y::ST * N * 8);
     }
   }
 }
@@ -1719,51 +1900,51 @@ __global__ void __launch_bounds__(nty<N>()) k_y_plain(float2* __restrict__ a0, f
 // the z transform:
 //   a0 <- r_x Y^-1[a0] + r_y Y^-1[i k'_y a1],   a2 <- i k'_z Y^-1[a1]   (a1 is left as it was)
 template <int N, bool COMB>
-__global__ void __launch_bounds__(nty<N>()) k_y_fanout(float2* __restrict__ a0, float2* __restrict__ a1,
+__global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanout(float2* __restrict__ a0, float2* __restrict__ a1,
                                                        float2* __restrict__ a2, Geo g, const int* __restrict__ active,
                                                        const float2* __restrict__ twg) {
   constexpr int NT = nty<N>(), W = wy<N>();
-  using L = Lay<N, W, false>;
+  using Y = YTile<N>;
   const int b = blockIdx.y;
   if (active && !active[b]) return;
-  __shared__ float2 buf[L::SIZE];
+  __shared__ float2 buf[Y::SIZE];
   __shared__ float2 tw[N];
   stage_twiddles<N, NT>(tw, twg);
   int p, x0, c, j;
   y_tile_coords<N, W>(p, x0);
-  frag_coords<N, W, false>(c, j);
-  const bool act = threadIdx.x < L::NTF;
+  Y::coords(c, j);
+  const bool act = Y::active();
   const long long cn = (long long)(N / 2 + 1) * N * N;
   a0 += b * cn; a1 += b * cn; a2 += b * cn;
   // a1 first: once its z component is stored only w is live, so a0 is loaded while w is transformed
   // and no transform runs with more than two arrays live (97 VGPRs; holding a0 and a1 through the
   // first transform needs 119)
-  float2 v[8], w[8];
+  float2 v[Y::E], w[Y::E];
   {
-    float2 keep[8];
+    float2 keep[Y::E];
     if (act) {
       y_load<N>(keep, a1, p, x0, c, j);
 #pragma unroll
-      for (int r = 0; r < 8; ++r) w[r] = mul_i(keep[r]) * (g.kf * deriv_mode<N>(j + r * (N / 8)));
+      for (int r = 0; r < Y::E; ++r) w[r] = mul_i(keep[r]) * (g.kf * deriv_mode<N>(j + r * Y::ST));
     }
-    fft_rr<N, W, true, false>(keep, buf, tw);
+    Y::template fft<true>(keep, buf, tw, c, j);
     if (act) {
       const float kz = g.kf * deriv_mode<N>(p);     // p in [0, N/2]; N/2 is the Nyquist plane
 #pragma unroll
-      for (int r = 0; r < 8; ++r) keep[r] = mul_i(keep[r]) * kz;
+      for (int r = 0; r < Y::E; ++r) keep[r] = mul_i(keep[r]) * kz;
       y_store<N>(keep, a2, p, x0, c, j);
       y_load<N>(v, a0, p, x0, c, j);               // in flight during the transform of w
     }
   }
-  fft_rr<N, W, true, false>(w, buf, tw);
+  Y::template fft<true>(w, buf, tw, c, j);
   if (!COMB && act) y_store<N>(w, a1, p, x0, c, j);
-  fft_rr<N, W, true, false>(v, buf, tw);
+  Y::template fft<true>(v, buf, tw, c, j);
   if (act) {
     if (COMB) {
       const float rx = los_comp(g, 0, x0 + c);
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const float ry = los_comp(g, 1, j + r * (N / 8));
+      for (int r = 0; r < Y::E; ++r) {
+        const float ry = los_comp(g, 1, j + r * Y::ST);
         const float2 t = v[r] * rx;
         v[r] = make_float2(fmaf(ry, w[r].x, t.x), fmaf(ry, w[r].y, t.y));
       }
@@ -1793,44 +1974,44 @@ __global__ void __launch_bounds__(256) k_y_combine(float2* __restrict__ a0, cons
 //   a0 <- r_x Y[a0]                   (x component Y Z[V_x]; i k'_x applied in the x pass)
 //   a1 <- i k'_y Y[r_y a0] + Y[a1]    (y component plus the z component)
 template <int N>
-__global__ void __launch_bounds__(nty<N>()) k_y_fanin(float2* __restrict__ a0, float2* __restrict__ a1, Geo g,
+__global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanin(float2* __restrict__ a0, float2* __restrict__ a1, Geo g,
                                                       const int* __restrict__ active, const float2* __restrict__ twg) {
   constexpr int NT = nty<N>(), W = wy<N>();
-  using L = Lay<N, W, false>;
+  using Y = YTile<N>;
   const int b = blockIdx.y;
   if (active && !active[b]) return;
-  __shared__ float2 buf[L::SIZE];
+  __shared__ float2 buf[Y::SIZE];
   __shared__ float2 tw[N];
   stage_twiddles<N, NT>(tw, twg);
   int p, x0, c, j;
   y_tile_coords<N, W>(p, x0);
-  frag_coords<N, W, false>(c, j);
-  const bool act = threadIdx.x < L::NTF;
+  Y::coords(c, j);
+  const bool act = Y::active();
   const long long cn = (long long)(N / 2 + 1) * N * N;
   a0 += b * cn; a1 += b * cn;
-  float2 v[8], keep[8];
+  float2 v[Y::E], keep[Y::E];
   if (act) {
     y_load<N>(v, a0, p, x0, c, j);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) keep[r] = v[r] * los_comp(g, 1, j + r * (N / 8));
+    for (int r = 0; r < Y::E; ++r) keep[r] = v[r] * los_comp(g, 1, j + r * Y::ST);
   }
-  fft_rr<N, W, false, false>(v, buf, tw);
+  Y::template fft<false>(v, buf, tw, c, j);
   if (act) {
     const float rx = los_comp(g, 0, x0 + c);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) v[r] = v[r] * rx;
+    for (int r = 0; r < Y::E; ++r) v[r] = v[r] * rx;
     y_store<N>(v, a0, p, x0, c, j);
     y_load<N>(v, a1, p, x0, c, j);                  // in flight during the next transform
   }
-  fft_rr<N, W, false, false>(keep, buf, tw);
+  Y::template fft<false>(keep, buf, tw, c, j);
   if (act) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) keep[r] = mul_i(keep[r]) * (g.kf * deriv_mode<N>(j + r * (N / 8)));
+    for (int r = 0; r < Y::E; ++r) keep[r] = mul_i(keep[r]) * (g.kf * deriv_mode<N>(j + r * Y::ST));
   }
-  fft_rr<N, W, false, false>(v, buf, tw);
+  Y::template fft<false>(v, buf, tw, c, j);
   if (act) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) v[r] = v[r] + keep[r];
+    for (int r = 0; r < Y::E; ++r) v[r] = v[r] + keep[r];
     y_store<N>(v, a1, p, x0, c, j);
   }
 }
@@ -1860,8 +2041,8 @@ __device__ __forceinline__ void x_store(const float2* v, float2* __restrict__ a,
 template <int N>
 __device__ __forceinline__ void x_wavenumbers(long long row, int kx, float kf, float& k2, float& dx, float& dy,
                                               float& dz, int& kzi) {
-  const int ky = (int)(row % N);
-  kzi = (int)(row / N);
+  const int ky = (int)row % N;
+  kzi = (int)row / N;
   const float mx = signed_mode<N>(kx), my = signed_mode<N>(ky), mz = (float)kzi;
   k2 = kf * kf * (mx * mx + my * my + mz * mz);
   dx = kf * deriv_mode<N>(kx);

@@ -313,3 +313,95 @@ def test_work_queued_ahead_of_the_convergence_test_changes_nothing(gpu_lib, star
         assert p[0] == passes[b] and torch.equal(one.psi()[0], psi[b])
     one.close()
     both.close()
+
+
+def field_reference(delta, box, obs, b, f, passes, start, relax):
+    """The pass iteration in 64 bits with torch's transforms; yields the three components of Psi."""
+    n = delta.shape[-1]
+    m = torch.arange(n, device=delta.device, dtype=torch.float64)
+    k = torch.where(m < n // 2, m, m - n) * (2 * np.pi / box)
+    dk = torch.where(m == n // 2, torch.zeros_like(k), k)
+    kv = (k.view(n, 1, 1), k.view(1, n, 1), k[:n // 2 + 1].abs().view(1, 1, -1))
+    d = (dk[:n // 2 + 1].view(1, 1, -1), dk.view(1, n, 1), dk.view(n, 1, 1))          # x, y, z
+    k2 = kv[0] ** 2 + kv[1] ** 2 + kv[2] ** 2
+    k2[0, 0, 0] = 1.0
+    x = m * (box / n)
+    r = [(x - obs[0]).view(1, 1, n), (x - obs[1]).view(1, n, 1), (x - obs[2]).view(n, 1, 1)]
+    dist = torch.sqrt(r[0] ** 2 + r[1] ** 2 + r[2] ** 2)
+    spec = lambda a: torch.fft.rfftn(a)                                               # noqa: E731
+    comp = lambda s, j: torch.fft.irfftn(1j * d[j] * s / (b * k2), s=(n, n, n))       # noqa: E731
+    ds = spec(delta.double())
+    ds[0, 0, 0] = 0
+    cur = ds
+
+    def along(s):
+        u = torch.zeros_like(dist)
+        for j in range(3):
+            u += comp(s, j) * (r[j] / dist)
+        return u
+
+    for p in range(passes):
+        u = along(cur)
+        if p == 0 and start == 2:                                                    # FFTA-2: u (1 - c)
+            u *= 1.0 - 3.0 * (f / b) / (7.0 + 3.0 * (f / b))
+        new = ds.clone()
+        for j in range(3):
+            new += f * 1j * d[j] * spec(u * (r[j] / dist))
+        new[0, 0, 0] = 0
+        w = 1.0 if relax is None or (p == 0 and start != 0) else relax
+        cur = w * new + (1.0 - w) * cur
+        del new, u
+    for j in range(3):
+        yield comp(cur, j)
+
+
+@pytest.mark.parametrize("n,start,relaxed", [(128, 0, False), (256, 0, False), (256, 0, True), (256, 2, False),
+                                             (512, 0, False), (512, 2, True), (1024, 0, False)])
+def test_passes_of_a_white_field_against_64_bits(gpu_lib, n, start, relaxed):
+    # every mode up to the Nyquist planes through both transform engines (below and from 256) and each form
+    # of the z step.  Tolerance: a transform of 2^30 points in FP32 is off by about 6e-8 sqrt(30) = 3e-7,
+    # two passes are five of them in a row, and the line of sight adds its own rounding: 1e-5 with a margin
+    # as the plane-wave test at 1024 takes.
+    from paper_1504_02591_amd import native
+    box, obs, b, f = 10.0 * n, (-3.0 * n, 4.0 * n + 3.0, 7.0 * n), 1.8, 0.8
+    g = torch.Generator(device=dev()).manual_seed(n + start)
+    delta = torch.randn((n, n, n), generator=g, device=dev(), dtype=torch.float32)
+    delta -= delta.mean()
+    plan = native.Plan(n, box, obs, b, f, 0.0, randoms=False, relaxed=relaxed,
+                       start_buffers=start != 0)
+    plan.set_delta(delta)
+    plan.solve(start)
+    plan.iterate(2, 0.0)
+    psi = plan.psi()[0]
+    plan.close()
+    num = den = 0.0
+    w = 2.0 / (2.0 + f / b) if relaxed else None
+    for j, want in enumerate(field_reference(delta, box, obs, b, f, 2, start, w)):
+        num += float(((psi[j].double() - want) ** 2).sum())
+        den += float((want ** 2).sum())
+    print(f"{n}^3 start {start} relaxed {relaxed}: rel L2 {(num / den) ** 0.5:.2e}", flush=True)
+    assert num <= 1e-10 * den
+
+
+@pytest.mark.parametrize("n", [16, 128, 256])
+def test_grid_cells_round_once_to_floats(gpu_lib, n):
+    # one object on a node of the 16^3-brick lattice per brick, weights over the whole range a cell can hold
+    # (below and above 2^53 units of 2^-32): without smoothing delta_s + 1 is the grid over its mean, to the
+    # transforms' rounding, 1e-6 of the largest cell
+    from paper_1504_02591_amd import native
+    m = (n // 16) ** 3
+    rng = np.random.default_rng(n)
+    cell = np.stack(np.meshgrid(*[np.arange(n // 16)] * 3, indexing="ij"), -1).reshape(m, 3) * 16 + 5
+    w = (2.0 ** rng.uniform(-2, 5.9, m)).astype(np.float32)
+    heavy = np.repeat(np.arange(min(m, 8)), 40000)               # 40,000 objects of weight 63 on one node each
+    for more in (heavy[:0], heavy):
+        pos = np.concatenate([cell, cell[more]]).astype(np.float32)
+        wt = np.concatenate([w, np.full(len(more), 63, np.float32)])
+        plan = native.Plan(n, float(n), (-3.0 * n, 0.0, 0.0), 1.0, 0.5, 0.0, randoms=False, keep_delta=True)
+        plan.paint(native.GAL, torch.from_numpy(pos).to(dev()), torch.from_numpy(wt).to(dev()))
+        plan.solve()
+        d = plan.delta()[0].double()
+        g = plan.grid(native.GAL)[0].double()
+        plan.close()
+        want = g / g.mean() - 1.0
+        assert float((d - want).abs().max()) <= 1e-6 * float(want.abs().max())
