@@ -347,6 +347,7 @@ struct recon_plan_s {
   PinnedDoubles host;
   double *h_red = nullptr, *h_red2 = nullptr, *h_stat = nullptr;
   double *hd_red = nullptr, *hd_red2 = nullptr, *hd_stat = nullptr;   // as kernels address them, or null
+  double *h_part = nullptr, *hd_part = nullptr;   // plane passes: the planes' partial sums, added up by the host; or null
   hipEvent_t ev = nullptr;     // what the host waits for, so that work queued behind it is not waited for
   std::string msg;
   Profiler prof;
@@ -448,6 +449,10 @@ int wait_read(recon_plan_t* pl) {
 // ---------------------------------------------------------------------------
 // Per-size launchers
 // ---------------------------------------------------------------------------
+// Up to this many pairs of partial sums, a plane pass writes them to pinned memory for the host to add up,
+// instead of a launch that does (4 us a pass; 1024 pairs take the host 1 us).
+constexpr size_t kHostParts = 1024;
+
 struct Ops {
   int (*setup)(recon_plan_t*);             // z/y/x/y/z/y/x chain from the painted grids to D_s and state X
   int (*setup_delta)(recon_plan_t*, const float*);
@@ -455,11 +460,14 @@ struct Ops {
   int (*combine)(recon_plan_t*, const int*);              // full state Y -> combined state Y
   int (*ziter)(recon_plan_t*, int mode, const int*);
   int (*fanin)(recon_plan_t*, const int*);
-  int (*xiter)(recon_plan_t*, bool first, const int*, float omega);
+  // fan: fan-out (a state Y, or SY_NONE) of the realisations marked in fan_act, where plane is set; there it
+  // holds the fan-in as well
+  int (*xiter)(recon_plan_t*, bool first, const int*, float omega, int fan, const int* fan_act);
   int (*zfinal)(recon_plan_t*, float* psi, float* u, bool cross, const int*, bool comb);
   int (*refan)(recon_plan_t*, const int*, const float2* d);  // state X again from the spectrum d
   int (*helm)(recon_plan_t*, const float*);  // fan-out of the Helmholtz projection of a real field
   int nb_x, nb_z;
+  bool plane;                              // the plane kernels: fan-in, x iteration and fan-out in one launch
 };
 
 // Brick validity of a grid for its readers: null while the grid is dense.
@@ -553,7 +561,37 @@ struct SizeOps {
     return dim3(ztiles<N, SPLIT>() / tpb, pl->batch);
   }
   static dim3 gy(const recon_plan_t* pl) { return dim3((N / 2 + 1) * (N / WY), pl->batch); }
+  static dim3 gp(const recon_plan_t* pl) { return dim3(N / 2 + 1, pl->batch); }
   static dim3 gx(const recon_plan_t* pl) { return dim3((N / 2 + 1) * N / WX, pl->batch); }
+
+  // y and x forward of the painted grids' z spectra, smoothing, x and y inverse.  zflag / mflag (may be
+  // null): z tiles whose rows were not written, and whose rows nothing reads afterwards
+  template <int NA>
+  static int smooth(recon_plan_t* pl, const unsigned char* zflag, const unsigned char* mflag) {
+    hipStream_t s = pl->stream;
+    if constexpr (N <= kPlaneN) {
+      PROF(pl, KP_X_SMOOTH);
+      k_plane_smooth<N><<<dim3(N / 2 + 1, pl->batch, NA), dim3(Plane<N, 1>::NT), 0, s>>>(pl->w0, pl->w1, pl->geo, pl->tw,
+                                                                                     zflag, mflag);
+      return check_launch(pl, "plane smooth");
+    } else {
+      {
+        PROF(pl, KP_Y_FWD);
+        k_y_plain<N, NA, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, NA == 2 ? pl->w1 : nullptr, pl->tw, zflag);
+      }
+      RECON_TRY(check_launch(pl, "y forward"));
+      {
+        PROF(pl, KP_X_SMOOTH);
+        k_x_smooth<N, NA><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, NA == 2 ? pl->w1 : nullptr, pl->geo, pl->tw);
+      }
+      RECON_TRY(check_launch(pl, "x smooth"));
+      {
+        PROF(pl, KP_Y_INV);
+        k_y_plain<N, NA, true><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, NA == 2 ? pl->w1 : nullptr, pl->tw, mflag);
+      }
+      return check_launch(pl, "y inverse");
+    }
+  }
 
   static int setup(recon_plan_t* pl) {
     hipStream_t s = pl->stream;
@@ -567,21 +605,7 @@ struct SizeOps {
       // the mask (from the random grid and the totals) and its tile flags come first, so that the
       // inverse y pass can skip the rows the overdensity step will not read
       RECON_TRY(scalars_and_mask(pl, (int)gz(pl).x, 2 * WZ));
-      {
-        PROF(pl, KP_Y_FWD);
-        k_y_plain<N, 2, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, pl->w1, pl->tw, pl->zflag);
-      }
-      RECON_TRY(check_launch(pl, "y forward"));
-      {
-        PROF(pl, KP_X_SMOOTH);
-        k_x_smooth<N, 2><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->geo, pl->tw);
-      }
-      RECON_TRY(check_launch(pl, "x smooth"));
-      {
-        PROF(pl, KP_Y_INV);
-        k_y_plain<N, 2, true><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, pl->w1, pl->tw, pl->mflag);
-      }
-      RECON_TRY(check_launch(pl, "y inverse"));
+      RECON_TRY(smooth<2>(pl, pl->zflag, pl->mflag));
       {
         PROF(pl, KP_Z_DELTA);
         k_z_delta<N, 2><<<gz(pl), dim3(TZ), 0, s>>>(pl->w0, pl->w1, pl->mask, pl->dscal, pl->delta,
@@ -597,21 +621,7 @@ struct SizeOps {
                                                        valid_of(pl, RECON_GAL), nullptr, pl->zflag);
       }
       RECON_TRY(check_launch(pl, "z forward (grid)"));
-      {
-        PROF(pl, KP_Y_FWD);
-        k_y_plain<N, 1, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, nullptr, pl->tw, pl->zflag);
-      }
-      RECON_TRY(check_launch(pl, "y forward"));
-      {
-        PROF(pl, KP_X_SMOOTH);
-        k_x_smooth<N, 1><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, nullptr, pl->geo, pl->tw);
-      }
-      RECON_TRY(check_launch(pl, "x smooth"));
-      {
-        PROF(pl, KP_Y_INV);
-        k_y_plain<N, 1, true><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, nullptr, pl->tw);
-      }
-      RECON_TRY(check_launch(pl, "y inverse"));
+      RECON_TRY(smooth<1>(pl, pl->zflag, nullptr));
       RECON_TRY(scalars_and_mask(pl, (int)gz(pl).x, 2 * WZ));
       {
         PROF(pl, KP_Z_DELTA);
@@ -625,19 +635,26 @@ struct SizeOps {
   }
 
   // y and x forward of the overdensity's z spectrum (rows of the z tiles flagged 0 in mflag, when
-  // given, were not written and are zero), D_s, and the fan-out state X of the plain start
+  // given, were not written and are zero), D_s, and the fan-out state X of the plain start (plane kernels: its
+  // combined state Y)
   static int finish_start(recon_plan_t* pl, const unsigned char* mflag) {
     hipStream_t s = pl->stream;
-    {
-      PROF(pl, KP_Y_FWD);
-      k_y_plain<N, 1, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, nullptr, pl->tw, mflag);
-    }
-    RECON_TRY(check_launch(pl, "y forward (delta)"));
-    {
+    if constexpr (N <= kPlaneN) {
       PROF(pl, KP_X_START);
-      k_x_start<N><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->ds, pl->geo, pl->tw);
+      k_plane_start<N><<<gp(pl), dim3(Plane<N, 2>::NT), 0, s>>>(pl->w0, pl->w2, pl->ds, pl->geo, pl->tw, mflag);
+      return check_launch(pl, "plane start");
+    } else {
+      {
+        PROF(pl, KP_Y_FWD);
+        k_y_plain<N, 1, false><<<gy(pl), dim3(TYP), 0, s>>>(pl->w0, nullptr, pl->tw, mflag);
+      }
+      RECON_TRY(check_launch(pl, "y forward (delta)"));
+      {
+        PROF(pl, KP_X_START);
+        k_x_start<N><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->ds, pl->geo, pl->tw);
+      }
+      return check_launch(pl, "x start");
     }
-    return check_launch(pl, "x start");
   }
 
   static int setup_delta(recon_plan_t* pl, const float* d) {
@@ -733,24 +750,38 @@ struct SizeOps {
   }
 
   static int fanin(recon_plan_t* pl, const int* act) {
-    {
+    if constexpr (N > kPlaneN) {
       PROF(pl, KP_Y_FANIN);
       k_y_fanin<N><<<gy(pl), dim3(TY), 0, pl->stream>>>(pl->w0, pl->w1, pl->geo, act, pl->tw);
+      return check_launch(pl, "y fan-in");
     }
-    return check_launch(pl, "y fan-in");
+    return RECON_OK;
   }
 
-  static int xiter(recon_plan_t* pl, bool first, const int* act, float omega) {
+  static int xiter(recon_plan_t* pl, bool first, const int* act, float omega, int fan, const int* fan_act) {
     hipStream_t s = pl->stream;
+    const float2* prev = first ? pl->ds : pl->dn;
     {
       PROF(pl, KP_X_ITER);
-      k_x_iter<N><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->ds, first ? pl->ds : pl->dn, pl->dn,
-                                                     pl->geo, pl->partials, act, pl->tw, omega);
+      if constexpr (N <= kPlaneN) {
+        auto go = [&](auto kernel) {
+          kernel<<<gp(pl), dim3(Plane<N, 2>::NT), 0, s>>>(pl->w0, pl->w1, pl->w2, pl->ds, prev, pl->dn, pl->geo,
+                                                          pl->hd_part ? pl->hd_part : pl->partials, act, fan_act, pl->tw, omega);
+        };
+        if (fan == SY_COMB) go(k_plane_iter<N, PF_COMB>);
+        else if (fan == SY_FULL) go(k_plane_iter<N, PF_FULL>);
+        else go(k_plane_iter<N, PF_NONE>);
+      } else {
+        k_x_iter<N><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->ds, prev, pl->dn, pl->geo, pl->partials, act, pl->tw,
+                                                omega);
+      }
     }
     RECON_TRY(check_launch(pl, "x iteration"));
+    if (pl->hd_part) return RECON_OK;
     {
       PROF(pl, KP_REDUCE);
-      k_reduce_pairs<<<pl->batch, 1024, 0, s>>>(pl->partials, (int)gx(pl).x, pl->red, pl->hd_red);
+      k_reduce_pairs<<<pl->batch, 1024, 0, s>>>(pl->partials, N <= kPlaneN ? N / 2 + 1 : (int)gx(pl).x, pl->red,
+                                                pl->hd_red);
     }
     return check_launch(pl, "reduce (norm)");
   }
@@ -781,7 +812,7 @@ struct SizeOps {
 
   static const Ops* table() {
     static const Ops ops = {setup, setup_delta, fanout, combine, ziter, fanin, xiter, zfinal, refan, helm,
-                            (int)((N / 2 + 1) * N / WX), (int)(N * (N / (2 * WZ)))};
+                            (int)((N / 2 + 1) * N / WX), (int)(N * (N / (2 * WZ))), N <= kPlaneN};
     return &ops;
   }
 };
@@ -960,7 +991,8 @@ int pass_graph_launch(recon_plan_t* pl, const Ops* ops) {
     }
     rc = ops->ziter(pl, ZI_PLAIN, pl->act_it);
     if (rc == RECON_OK) rc = ops->fanin(pl, pl->act_it);
-    if (rc == RECON_OK) rc = ops->xiter(pl, false, pl->act_it, relax_weight(pl));
+    // (where the x step holds the fan-out: the combined one, of the realisations marked for it at the time)
+    if (rc == RECON_OK) rc = ops->xiter(pl, false, pl->act_it, relax_weight(pl), SY_COMB, pl->act_fan);
     const hipError_t ec = hipStreamEndCapture(pl->cap_stream, &graph);
     pl->stream = keep;
     if (rc != RECON_OK) {
@@ -1134,7 +1166,9 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
   pl->h_fan.assign(pl->batch, 0);
   pl->h_fin.assign(pl->batch, 0);
   pl->h_it.assign(pl->batch, 0);
-  if (!pl->host.assign(7 * (size_t)pl->batch + 2, 0.0, pinned) ||
+  const size_t parts = (size_t)pl->batch * (n / 2 + 1);
+  const bool host_parts = ops_for(n) && ops_for(n)->plane && parts <= kHostParts;
+  if (!pl->host.assign(7 * (size_t)pl->batch + 2 + (host_parts ? 2 * parts : 0), 0.0, pinned) ||
       (pinned && hipEventCreateWithFlags(&pl->ev, hipEventDisableTiming) != hipSuccess)) {
     delete pl;
     return RECON_EDEVICE;
@@ -1146,6 +1180,11 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
     pl->hd_red = pl->host.dev;
     pl->hd_red2 = pl->hd_red + 4 * pl->batch;
     pl->hd_stat = pl->hd_red2 + 2 * pl->batch;
+    if (host_parts) {
+      const size_t at = 7 * (size_t)pl->batch + 2;
+      pl->h_part = pl->host.p + at;
+      pl->hd_part = pl->host.dev + at;
+    }
   }
 
   {
@@ -1398,7 +1437,7 @@ int recon_solve(recon_plan_t* pl, int start, const void* net) {
     pl->passes[b] = 0;
     pl->done[b] = 0;
     pl->psi_valid[b] = 0;
-    pl->st_y[b] = SY_NONE;
+    pl->st_y[b] = ops->plane ? SY_COMB : SY_NONE;
     pl->pending1[b] = 0;
     pl->diverged[b] = 0;
     pl->stale_x[b] = 0;
@@ -1409,7 +1448,7 @@ int recon_solve(recon_plan_t* pl, int start, const void* net) {
   if (start == RECON_START_LEARNED) {
     Marker mark("a7/a11 learned start (u_p, network)");
     // u_p = Psi_p . r_hat from the fanned-out start, then Delta u = network(delta_s, u_p) into corr
-    RECON_TRY(ops->fanout(pl, nullptr, true));
+    if (!ops->plane) RECON_TRY(ops->fanout(pl, nullptr, true));
     RECON_TRY(ops->zfinal(pl, nullptr, pl->upbuf, false, nullptr, true));
     if (pl->dh) {
       // network on the (n/4)^3 grid: two restrictions (both fields per pass), one trilinear
@@ -1460,6 +1499,15 @@ double expect_eps(const recon_plan_t* pl, int b, double beta) {
   return h.back() * rate;
 }
 
+// Sum of every second of 2 count values (count <= 64), in k_reduce_pairs' order: halves of 64 folded together.
+double plane_sum(const double* v, int count) {
+  double a[64] = {};
+  for (int i = 0; i < count; ++i) a[i] = v[2 * i];
+  for (int off = 32; off > 0; off >>= 1)
+    for (int i = 0; i < off; ++i) a[i] += a[i + off];
+  return a[0];
+}
+
 int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out, double* eps_out) {
   CHECK_PLAN(pl);
   if (pl->state != ST_SOLVED) return fail(pl, RECON_ESTATE, "solve must precede iterate");
@@ -1467,6 +1515,7 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
   const Ops* ops = ops_for(pl->n);
   const int B = pl->batch;
   const bool fixed = !(tol > 0.0);
+  const int planes = pl->n / 2 + 1;
   const double norm_k = 1.0 / (pl->p.bias * pl->p.bias * (double)pl->n3);   // Parseval + 1/b^2
   const double beta = pl->p.growth / pl->p.bias;
   std::vector<std::vector<double>> call_eps(B);
@@ -1593,6 +1642,8 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
     return RECON_OK;
   };
 
+  const bool graphs = (pl->p.flags & RECON_PASS_GRAPHS) && !pl->prof.on;
+  std::vector<int> z_done(B, 0);                     // realisations whose next z step has run ahead
   for (int it = 0; it < max_iter; ++it) {
     Marker mark("a8 correction pass");
     bool any = false;
@@ -1629,8 +1680,9 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
     const bool need_y = mode != ZI_LEARNED;
     bool any_comb = false, any_fan = false;
     for (int b = 0; b < B; ++b) {
-      pl->h_fan[b] = (need_y && pl->h_it[b] && pl->st_y[b] == SY_NONE) ? 1 : 0;
-      pl->h_fin[b] = (need_y && pl->h_it[b] && pl->st_y[b] == SY_FULL) ? 1 : 0;   // combined in place
+      const bool want_y = need_y && pl->h_it[b] && !z_done[b];
+      pl->h_fan[b] = want_y && pl->st_y[b] == SY_NONE ? 1 : 0;
+      pl->h_fin[b] = want_y && pl->st_y[b] == SY_FULL ? 1 : 0;   // combined in place
       any_comb = any_comb || pl->h_fin[b];
       any_fan = any_fan || pl->h_fan[b];
     }
@@ -1643,10 +1695,18 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
       RECON_TRY(upload_mask(pl, pl->act_fan, pl->h_fan));
       RECON_TRY(ops->fanout(pl, pl->act_fan, true));
     }
-    const bool steady = mode == ZI_PLAIN && !first;
-    const bool graph = steady && (pl->p.flags & RECON_PASS_GRAPHS) && !pl->prof.on;
-    if (graph) RECON_TRY(pass_graph_launch(pl, ops));
-    else RECON_TRY(ops->ziter(pl, mode, pl->act_it));
+    const bool graph = graphs && mode == ZI_PLAIN && !first;
+    if (!graph) {
+      bool some = false, rest = false;               // realisations whose z step has run, or has not
+      for (int b = 0; b < B; ++b) {
+        pl->h_fan[b] = pl->h_it[b] && !z_done[b];
+        some = some || (pl->h_it[b] && z_done[b]);
+        rest = rest || pl->h_fan[b];
+        z_done[b] = 0;
+      }
+      if (some && rest) RECON_TRY(upload_mask(pl, pl->act_fan, pl->h_fan));
+      if (rest) RECON_TRY(ops->ziter(pl, mode, some ? pl->act_fan : pl->act_it));
+    }
     if (cross) {
       // the fan-in is queued before the wait: a realisation that drops out of the pass here is rebuilt
       // from D_1 or D_s, so what it leaves in W0 and W1 is not read
@@ -1674,18 +1734,11 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
       if (!rest) continue;
       RECON_TRY(upload_mask(pl, pl->act_it, pl->h_it));
     }
-    // relaxed passes mix with D_n; the first pass after a non-gradient start has no D_0 and is plain
-    if (!graph) {
-      if (!cross) RECON_TRY(ops->fanin(pl, pl->act_it));
-      RECON_TRY(ops->xiter(pl, first, pl->act_it, start_pass ? 1.f : relax_weight(pl)));
-    }
-    // the start pass also reads S1, S2 (red[2B..4B)): both halves together
-    RECON_TRY(queue_read(pl, pl->h_red, pl->red, (start_pass ? 4 : 2) * B));
-    // While the host waits for the norm and decides, the fan-out that the realisations need next is already
-    // running: the combined one for those sure to go on (passes left in this call, and eps expected well
-    // above the tolerance), the full one when all are sure to stop.  Which of them ran is the
-    // realisation's state Y, so a wrong guess costs its time and nothing else; where it is not clear,
-    // nothing is run ahead.  (Waiting first left the GPU idle for 15 us a pass: a fifth of a 64^3 pass.)
+    // While the host waits for the norm and decides, what the realisations need next is already running: the
+    // combined fan-out for those sure to go on (passes left in this call, and eps expected well above the
+    // tolerance), the full one when all are sure to stop.  Which of them ran is the realisation's state Y, so
+    // a wrong guess costs its time and nothing else; where it is not clear, nothing is run ahead.  (Waiting
+    // first left the GPU idle for 15 us a pass: a fifth of a 64^3 pass.)
     bool go_on = false, all_stop = true;
     for (int b = 0; b < B; ++b) {
       pl->h_fan[b] = 0;
@@ -1698,9 +1751,32 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
     }
     const int ahead = go_on ? SY_COMB : (all_stop ? SY_FULL : SY_NONE);
     if (ahead == SY_FULL) pl->h_fan = pl->h_it;
-    if (ahead != SY_NONE) {
+    // (a plane pass recorded as a graph holds the combined fan-out of the realisations marked when it runs)
+    const bool graph_fan = graph && ops->plane, late_fan = ahead != SY_NONE && (!ops->plane || (graph && ahead == SY_FULL));
+    if (graph_fan && ahead != SY_COMB) {
+      pl->h_fin.assign(B, 0);
+      RECON_TRY(upload_mask(pl, pl->act_fan, pl->h_fin));
+    } else if (ahead != SY_NONE) {
+      RECON_TRY(upload_mask(pl, pl->act_fan, pl->h_fan));
+    }
+    if (graph) RECON_TRY(pass_graph_launch(pl, ops));
+    // relaxed passes mix with D_n; the first pass after a non-gradient start has no D_0 and is plain
+    if (!graph) {
+      if (!cross) RECON_TRY(ops->fanin(pl, pl->act_it));
+      RECON_TRY(ops->xiter(pl, first, pl->act_it, start_pass ? 1.f : relax_weight(pl), ahead, pl->act_fan));
+    }
+    // the start pass also reads S1, S2 (red[2B..4B)): both halves together
+    RECON_TRY(queue_read(pl, pl->h_red, pl->red, (start_pass ? 4 : 2) * B));
+    if (late_fan) {
       RECON_TRY(upload_mask(pl, pl->act_fan, pl->h_fan));
       RECON_TRY(ops->fanout(pl, pl->act_fan, ahead == SY_COMB));
+    }
+    // Plane kernels: the z step that follows the fan-out too (a realisation that stops here after all is
+    // rebuilt from D_n); the pass after a non-gradient start's first needs its sums, and is left.
+    std::vector<int> z_next;
+    if (ops->plane && !graphs && ahead == SY_COMB && !start_pass) {
+      z_next = pl->h_fan;
+      RECON_TRY(ops->ziter(pl, ZI_PLAIN, pl->act_fan));
     }
     RECON_TRY(wait_read(pl));
     for (int b = 0; b < B; ++b) {
@@ -1709,7 +1785,11 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
       pl->psi_valid[b] = 0;
       const bool was_start = pl->passes[b] == 0 && pl->start_b[b] != RECON_START_PLAIN;
       pl->passes[b] += 1;
-      const double num = pl->h_red[2 * b], den = pl->h_red[2 * b + 1];
+      double num = pl->h_red[2 * b], den = pl->h_red[2 * b + 1];
+      if (pl->hd_part) {
+        num = plane_sum(pl->h_part + (size_t)2 * b * planes, planes);
+        den = plane_sum(pl->h_part + (size_t)2 * b * planes + 1, planes);
+      }
       if (was_start) {
         pl->num0[b] = num * norm_k;
         pl->den0[b] = den * norm_k;
@@ -1718,6 +1798,12 @@ int recon_iterate(recon_plan_t* pl, int max_iter, double tol, int32_t* iters_out
         pl->pending1[b] = 1;
       } else {
         RECON_TRY(record(b, den > 0 ? std::sqrt(num / den) : 0.0, den * norm_k));
+      }
+      if (!z_next.empty() && z_next[b]) {
+        // its state Y went into the z step: the next pass takes it from there, the final displacement does not
+        pl->st_y[b] = SY_NONE;
+        if (pl->done[b]) pl->stale_x[b] = 1;
+        else if (!pl->stale_x[b]) z_done[b] = 1;     // (a realisation that fell back starts over)
       }
     }
   }

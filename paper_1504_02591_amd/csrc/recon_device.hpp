@@ -175,16 +175,17 @@ __device__ __forceinline__ void bfly_coords(int b, int& c, int& j) {
   else { c = b % W; j = b / W; }
 }
 
-// Fragment coordinates of this thread (valid when threadIdx.x < NTF).
+// Fragment coordinates of this thread (valid when t < NTF).  Here and below, t is the thread's index among
+// those of its tile: the block's own, unless a block holds several tiles; threads with t >= NTF take part in
+// the barriers only.
 template <int N, int W, bool JF>
-__device__ __forceinline__ void frag_coords(int& c, int& j) { bfly_coords<N, W, 8, JF>(threadIdx.x, c, j); }
+__device__ __forceinline__ void frag_coords(int& c, int& j, int t = threadIdx.x) { bfly_coords<N, W, 8, JF>(t, c, j); }
 
 // Generic LDS-to-LDS Stockham pass (radix R, completed sub-transform length NS).
 template <int N, int W, int R, int NS, bool INV, bool JF>
-__device__ __forceinline__ void lds_pass(float2* buf, const float2* tw) {
+__device__ __forceinline__ void lds_pass(float2* buf, const float2* tw, int t = threadIdx.x) {
   using L = Lay<N, W, JF>;
   constexpr int Q = 8 / R;
-  const int t = threadIdx.x;
   float2 v[Q][R];
   if (t < L::NTF) {
 #pragma unroll
@@ -222,12 +223,12 @@ __device__ __forceinline__ void lds_pass(float2* buf, const float2* tw) {
 // First radix-8 pass from the register fragment into LDS (preceded by a barrier that
 // protects earlier readers of the tile).
 template <int N, int W, bool INV, bool JF>
-__device__ __forceinline__ void first_pass(float2* v, float2* buf) {
+__device__ __forceinline__ void first_pass(float2* v, float2* buf, int t = threadIdx.x) {
   using L = Lay<N, W, JF>;
   __syncthreads();
-  if (threadIdx.x < L::NTF) {
+  if (t < L::NTF) {
     int c, j;
-    frag_coords<N, W, JF>(c, j);
+    frag_coords<N, W, JF>(c, j, t);
     dft8<INV>(v);
 #pragma unroll
     for (int r = 0; r < 8; ++r) buf[L::at(j * 8 + r, c)] = v[r];
@@ -237,11 +238,11 @@ __device__ __forceinline__ void first_pass(float2* v, float2* buf) {
 
 // Last radix-8 pass (NS = N/8) from LDS into the register fragment.
 template <int N, int W, bool INV, bool JF>
-__device__ __forceinline__ void last_pass(float2* v, const float2* buf, const float2* tw) {
+__device__ __forceinline__ void last_pass(float2* v, const float2* buf, const float2* tw, int t = threadIdx.x) {
   using L = Lay<N, W, JF>;
-  if (threadIdx.x < L::NTF) {
+  if (t < L::NTF) {
     int c, j;
-    frag_coords<N, W, JF>(c, j);
+    frag_coords<N, W, JF>(c, j, t);
 #pragma unroll
     for (int r = 0; r < 8; ++r) v[r] = buf[L::at(j + r * (N / 8), c)];
 #pragma unroll
@@ -258,29 +259,29 @@ __device__ __forceinline__ void last_pass(float2* v, const float2* buf, const fl
 // 1024 is a tuning knob (RECON_MID_512: 0 = 8, 1 = 2 x 4, 2 = 4 x 2; RECON_MID_1024: 0 = 4 x 4,
 // 1 = 2 x 8, 2 = 8 x 2), chosen by the autotuner (autotune.py).
 template <int N, int W, bool INV, bool JF>
-__device__ __forceinline__ void middle_passes(float2* buf, const float2* tw) {
-  if constexpr (N == 128) lds_pass<N, W, 2, 8, INV, JF>(buf, tw);
-  else if constexpr (N == 256) lds_pass<N, W, 4, 8, INV, JF>(buf, tw);
+__device__ __forceinline__ void middle_passes(float2* buf, const float2* tw, int t = threadIdx.x) {
+  if constexpr (N == 128) lds_pass<N, W, 2, 8, INV, JF>(buf, tw, t);
+  else if constexpr (N == 256) lds_pass<N, W, 4, 8, INV, JF>(buf, tw, t);
   else if constexpr (N == 512) {
     if constexpr (RECON_MID_512 == 1) {
-      lds_pass<N, W, 2, 8, INV, JF>(buf, tw);
-      lds_pass<N, W, 4, 16, INV, JF>(buf, tw);
+      lds_pass<N, W, 2, 8, INV, JF>(buf, tw, t);
+      lds_pass<N, W, 4, 16, INV, JF>(buf, tw, t);
     } else if constexpr (RECON_MID_512 == 2) {
-      lds_pass<N, W, 4, 8, INV, JF>(buf, tw);
-      lds_pass<N, W, 2, 32, INV, JF>(buf, tw);
+      lds_pass<N, W, 4, 8, INV, JF>(buf, tw, t);
+      lds_pass<N, W, 2, 32, INV, JF>(buf, tw, t);
     } else {
-      lds_pass<N, W, 8, 8, INV, JF>(buf, tw);
+      lds_pass<N, W, 8, 8, INV, JF>(buf, tw, t);
     }
   } else if constexpr (N == 1024) {
     if constexpr (RECON_MID_1024 == 1) {
-      lds_pass<N, W, 2, 8, INV, JF>(buf, tw);
-      lds_pass<N, W, 8, 16, INV, JF>(buf, tw);
+      lds_pass<N, W, 2, 8, INV, JF>(buf, tw, t);
+      lds_pass<N, W, 8, 16, INV, JF>(buf, tw, t);
     } else if constexpr (RECON_MID_1024 == 2) {
-      lds_pass<N, W, 8, 8, INV, JF>(buf, tw);
-      lds_pass<N, W, 2, 64, INV, JF>(buf, tw);
+      lds_pass<N, W, 8, 8, INV, JF>(buf, tw, t);
+      lds_pass<N, W, 2, 64, INV, JF>(buf, tw, t);
     } else {
-      lds_pass<N, W, 4, 8, INV, JF>(buf, tw);
-      lds_pass<N, W, 4, 32, INV, JF>(buf, tw);
+      lds_pass<N, W, 4, 8, INV, JF>(buf, tw, t);
+      lds_pass<N, W, 4, 32, INV, JF>(buf, tw, t);
     }
   }
 }
@@ -401,33 +402,33 @@ __device__ __forceinline__ void lds_pass_r8_mfma(float2* buf, const float2* tw) 
 // barrier before its next write to the tile.  SPLIT > 0 (N >= 64): the last radix-8 stage runs on
 // the matrix cores with SPLIT bfloat16 terms per operand (lds_pass_r8_mfma).
 template <int N, int W, bool INV, bool JF, int SPLIT = 0>
-__device__ __forceinline__ void fft_rr(float2* v, float2* buf, const float2* tw) {
+__device__ __forceinline__ void fft_rr(float2* v, float2* buf, const float2* tw, int t = threadIdx.x) {
   using L = Lay<N, W, JF>;
   if constexpr (N == 8) {
-    if (threadIdx.x < L::NTF) dft8<INV>(v);
+    if (t < L::NTF) dft8<INV>(v);
   } else if constexpr (N < 64) {
-    first_pass<N, W, INV, JF>(v, buf);
-    lds_pass<N, W, N / 8, 8, INV, JF>(buf, tw);
-    if (threadIdx.x < L::NTF) {
+    first_pass<N, W, INV, JF>(v, buf, t);
+    lds_pass<N, W, N / 8, 8, INV, JF>(buf, tw, t);
+    if (t < L::NTF) {
       int c, j;
-      frag_coords<N, W, JF>(c, j);
+      frag_coords<N, W, JF>(c, j, t);
 #pragma unroll
       for (int r = 0; r < 8; ++r) v[r] = buf[L::at(j + r * (N / 8), c)];
     }
   } else if constexpr (SPLIT > 0) {
-    first_pass<N, W, INV, JF>(v, buf);
-    middle_passes<N, W, INV, JF>(buf, tw);
+    first_pass<N, W, INV, JF>(v, buf, t);
+    middle_passes<N, W, INV, JF>(buf, tw, t);
     lds_pass_r8_mfma<N, W, N / 8, INV, JF, SPLIT>(buf, tw);
-    if (threadIdx.x < L::NTF) {
+    if (t < L::NTF) {
       int c, j;
-      frag_coords<N, W, JF>(c, j);
+      frag_coords<N, W, JF>(c, j, t);
 #pragma unroll
       for (int r = 0; r < 8; ++r) v[r] = buf[L::at(j + r * (N / 8), c)];
     }
   } else {
-    first_pass<N, W, INV, JF>(v, buf);
-    middle_passes<N, W, INV, JF>(buf, tw);
-    last_pass<N, W, INV, JF>(v, buf, tw);
+    first_pass<N, W, INV, JF>(v, buf, t);
+    middle_passes<N, W, INV, JF>(buf, tw, t);
+    last_pass<N, W, INV, JF>(v, buf, tw, t);
   }
 }
 

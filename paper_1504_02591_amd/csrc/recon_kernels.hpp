@@ -75,6 +75,8 @@ template <int N> constexpr bool yp_col() { return y_col<N>() && N != 512; }
 // and grids of 512 want the 32 waves per CU of the radix-8 engine's 512- and 1024-thread blocks on their
 // 16-byte row segments (47 against 56 us, and 431 against 549 us for two).
 template <int N, int NA> constexpr bool zg_col() { return N == 1024 || (N == 256 && NA == 2); }
+// Grids up to this size run the y and x steps of a plane in one kernel (k_plane_*).
+constexpr int kPlaneN = 64;
 // z tiles (one y row, 2 wz consecutive x) and tiles per block of the z iteration
 template <int N, int SPLIT = 0> constexpr int ztiles() { return N * (N / (2 * wzs<N, SPLIT>())); }
 // (the start and cross modes and the matrix-core radix variants, which hold more live state, take one
@@ -2261,6 +2263,332 @@ __global__ void RECON_X_ITER_BOUNDS(N) k_x_iter(float2* __restrict__ a0, float2*
   if (act) x_store<N>(xa, a0, row, j);
   fft_rr<N, W, true, true>(v, buf, tw);
   if (act) x_store<N>(v, a1, row, j);
+}
+
+// ---------------------------------------------------------------------------
+// Plane kernels (N <= kPlaneN): one block holds a whole kz plane of a spectrum, N x N, and runs the y and x
+// transforms of a step back to back, so a step that was three launches over global memory is one.  What
+// bounds these sizes is the latency of a launch's own chain (each of the three took 5 to 8 us at 32^3 and
+// 64^3 for 0.1 to 1 us of memory traffic), not bandwidth; a larger plane's arrays do not fit the LDS.
+// The chain is kept short: loads are issued before anything is waited for, and the two arrays of a step run
+// side by side in two groups of N^2/8 threads, one exchange tile each.  Fan-in to fan-out at 32^3: 10.8 us
+// (12.4 with one group; 4.8 + 8.1 + 4.9 as three launches), at 64^3 17.7 us (17.3; 5.1 + 8.5 + 5.4), where
+// the transforms of a plane fill the vector units of its one CU.  Eight passes, us, three launches against
+// one: 32^3 291 / 202, 64^3 310 / 267, 256 grids of 32^3 1814 / 1195, 128 of 64^3 4637 / 3678.
+// Fragments: y form (column x = c, rows y = j + r N/8) and x form (row y = cx, columns x = jx + r N/8), turned
+// into each other through the exchange tile.
+// ---------------------------------------------------------------------------
+// a or b, by value (?: of two array elements would select between addresses and put the array in memory)
+__device__ __forceinline__ float2 pick(bool first, float2 a, float2 b) {
+  return make_float2(first ? a.x : b.x, first ? a.y : b.y);
+}
+
+template <int N, int GROUPS>
+struct Plane {
+  using LY = Lay<N, N, false>;
+  using LX = Lay<N, N, true>;
+  static constexpr int NTF = N * N / 8, NT = GROUPS * NTF < 64 ? 64 : GROUPS * NTF;
+  static constexpr int TILE = LY::SIZE > LX::SIZE ? LY::SIZE : LX::SIZE;
+  static constexpr int SIZE = GROUPS == 1 ? TILE : 3 * TILE;   // (two groups: and a tile to hand values over)
+  static_assert(TILE >= 8 * NTF, "a tile holds every fragment");
+  float2 *buf, *mid;
+  const float2* tw;
+  int g, t, c, j, cx, jx;
+  bool on;
+  __device__ __forceinline__ Plane(float2* b, const float2* w) : tw(w) {
+    const int i = threadIdx.x / NTF;
+    on = i < GROUPS;
+    g = on ? i : 0;
+    t = on ? threadIdx.x - i * NTF : NTF;
+    buf = b + g * TILE;
+    mid = b + 2 * TILE;
+    frag_coords<N, N, false>(c, j, t);
+    frag_coords<N, N, true>(cx, jx, t);
+  }
+  __device__ __forceinline__ int row(int r) const { return j + r * (N / 8); }                // y of element r, y form
+  __device__ __forceinline__ int at_y(int r) const { return row(r) * N + c; }                // element r, in the plane
+  __device__ __forceinline__ int at_x(int r) const { return cx * N + jx + r * (N / 8); }
+  __device__ __forceinline__ void put_y(const float2* v, float2* b) const {                   // to a tile, by (y, x)
+#pragma unroll
+    for (int r = 0; r < 8; ++r) b[LX::at(c, row(r))] = v[r];
+  }
+  __device__ __forceinline__ void get_x(float2* v, const float2* b) const {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = b[LX::at(jx + r * (N / 8), cx)];
+  }
+  __device__ __forceinline__ void y_to_x(float2* v) const {
+    __syncthreads();
+    if (on) put_y(v, buf);
+    __syncthreads();
+    if (on) get_x(v, buf);
+  }
+  __device__ __forceinline__ void x_to_y(float2* v) const {
+    __syncthreads();
+    if (on) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) buf[LX::at(jx + r * (N / 8), cx)] = v[r];
+    }
+    __syncthreads();
+    if (on) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) v[r] = buf[LX::at(c, row(r))];
+    }
+  }
+  // transforms of the groups for which run is set
+  template <bool INV>
+  __device__ __forceinline__ void fft_y(float2* v, bool run = true) const {
+    fft_rr<N, N, INV, false>(v, buf, tw, run ? t : NTF);
+  }
+  template <bool INV>
+  __device__ __forceinline__ void fft_x(float2* v, bool run = true) const {
+    fft_rr<N, N, INV, true>(v, buf, tw, run ? t : NTF);
+  }
+  // Two groups.  From P in x form to the fan-out, as k_y_fanout does it: group 0 takes v = i k'_x P, group 1
+  // v = P.  STORE_X: state X, no fan-out.
+  template <bool COMB>
+  __device__ __forceinline__ void tail(float2* v, const Geo& geo, int p, bool state_x, float2* a0, float2* a1,
+                                       float2* a2) const {
+    fft_x<true>(v);
+    if (state_x) {
+      if (on) {
+        float2* a = g == 0 ? a0 : a1;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) a[at_x(r)] = v[r];
+      }
+      return;
+    }
+    x_to_y(v);
+    float2 w[8];                                       // what the first round transforms
+#pragma unroll
+    for (int r = 0; r < 8; ++r) w[r] = pick(g == 0, v[r], mul_i(v[r]) * (geo.kf * deriv_mode<N>(row(r))));
+    fft_y<true>(w);
+    if (COMB) {
+      if (on && g == 1) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) mid[r * NTF + t] = w[r];
+      }
+      __syncthreads();
+      if (on && g == 0) {
+        const float rx = los_comp(geo, 0, c);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const float ry = los_comp(geo, 1, row(r));
+          const float2 s = w[r] * rx, u = mid[r * NTF + t];
+          a0[at_y(r)] = make_float2(fmaf(ry, u.x, s.x), fmaf(ry, u.y, s.y));
+        }
+      }
+    } else if (on) {
+      float2* a = g == 0 ? a0 : a1;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) a[at_y(r)] = w[r];
+    }
+    fft_y<true>(v, g == 1);
+    if (on && g == 1) {
+      const float kz = geo.kf * deriv_mode<N>(p);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) a2[at_y(r)] = mul_i(v[r]) * kz;
+    }
+  }
+};
+
+// y forward, x forward, smoothing, x inverse, y inverse of one array (blockIdx.z): k_y_plain, k_x_smooth and
+// k_y_plain in one.  in_flag [arrays][batch][z tiles]: rows of z tiles flagged 0 are zero and are not read;
+// out_flag [batch][z tiles]: such rows are not stored (null: every row).
+template <int N>
+__global__ void __launch_bounds__((Plane<N, 1>::NT)) k_plane_smooth(float2* __restrict__ a0, float2* __restrict__ a1,
+                                                                    Geo g, const float2* __restrict__ twg,
+                                                                    const unsigned char* __restrict__ in_flag,
+                                                                    const unsigned char* __restrict__ out_flag) {
+  using P = Plane<N, 1>;
+  __shared__ float2 buf[P::SIZE];
+  __shared__ float2 tw[N];
+  const P pl(buf, tw);
+  constexpr int NZT = N / (2 * wz<N>());
+  const int p = blockIdx.x, b = blockIdx.y, a = blockIdx.z;
+  float2* arr = (a == 0 ? a0 : a1) + ((long long)b * (N / 2 + 1) + p) * N * N;
+  if (in_flag) in_flag += ((long long)a * gridDim.y + b) * N * NZT + pl.c / (2 * wz<N>());
+  if (out_flag) out_flag += (long long)b * N * NZT + pl.c / (2 * wz<N>());
+  float2 v[8];
+  if (pl.on) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      v[r] = !in_flag || in_flag[pl.row(r) * NZT] ? arr[pl.at_y(r)] : make_float2(0.f, 0.f);
+  }
+  stage_twiddles<N, P::NT>(tw, twg);
+  pl.template fft_y<false>(v);
+  pl.y_to_x(v);
+  pl.template fft_x<false>(v);
+  if (pl.on) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      float k2, dx, dy, dz;
+      int kzi;
+      x_wavenumbers<N>((long long)p * N + pl.cx, pl.jx + r * (N / 8), g.kf, k2, dx, dy, dz, kzi);
+      v[r] = v[r] * (expf(-k2 * g.smooth_c) * g.inv_n3);
+    }
+  }
+  pl.template fft_x<true>(v);
+  pl.x_to_y(v);
+  pl.template fft_y<true>(v);
+  if (pl.on) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (!out_flag || out_flag[pl.row(r) * NZT]) arr[pl.at_y(r)] = v[r];
+  }
+}
+
+// y forward and x forward of the overdensity, D_s, and the combined fan-out of the plain start: k_y_plain,
+// k_x_start and k_y_fanout in one (state X is not stored).
+template <int N>
+__global__ void __launch_bounds__((Plane<N, 2>::NT)) k_plane_start(float2* __restrict__ a0, float2* __restrict__ a2,
+                                                                   float2* __restrict__ ds, Geo g,
+                                                                   const float2* __restrict__ twg,
+                                                                   const unsigned char* __restrict__ in_flag) {
+  using P = Plane<N, 2>;
+  __shared__ float2 buf[P::SIZE];
+  __shared__ float2 tw[N];
+  const P pl(buf, tw);
+  constexpr int NZT = N / (2 * wz<N>());
+  const int p = blockIdx.x, b = blockIdx.y;
+  const long long off = ((long long)b * (N / 2 + 1) + p) * N * N;
+  a0 += off; a2 += off; ds += off;
+  if (in_flag) in_flag += (long long)b * N * NZT + pl.c / (2 * wz<N>());
+  float2 v[8];
+  if (pl.on && pl.g == 0) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      v[r] = !in_flag || in_flag[pl.row(r) * NZT] ? a0[pl.at_y(r)] : make_float2(0.f, 0.f);
+  }
+  stage_twiddles<N, P::NT>(tw, twg);
+  pl.template fft_y<false>(v, pl.g == 0);
+  pl.y_to_x(v);
+  pl.template fft_x<false>(v, pl.g == 0);
+  if (pl.on && pl.g == 0) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      ds[pl.at_x(r)] = v[r];
+      float k2, dx, dy, dz;
+      int kzi;
+      x_wavenumbers<N>((long long)p * N + pl.cx, pl.jx + r * (N / 8), g.kf, k2, dx, dy, dz, kzi);
+      v[r] = k2 > 0.f ? v[r] * (g.inv_bn3 / k2) : make_float2(0.f, 0.f);
+      pl.mid[r * P::NTF + pl.t] = v[r];
+      v[r] = mul_i(v[r]) * dx;
+    }
+  }
+  __syncthreads();
+  if (pl.on && pl.g == 1) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = pl.mid[r * P::NTF + pl.t];
+  }
+  pl.template tail<true>(v, g, p, false, a0, nullptr, a2);
+}
+
+// A pass from the z step's output to the next fan-out: k_y_fanin, k_x_iter and k_y_fanout in one.  FAN: the
+// fan-out of the realisations marked in fan (PF_COMB: combined, PF_FULL: full); the others' state X is stored.
+// Group 0 carries a0, group 1 a1; each takes half of the k-space step's elements.
+enum PlaneFan { PF_NONE = 0, PF_COMB = 1, PF_FULL = 2 };
+template <int N, int FAN>
+__global__ void __launch_bounds__((Plane<N, 2>::NT)) k_plane_iter(float2* __restrict__ a0, float2* __restrict__ a1,
+                                                                  float2* __restrict__ a2,
+                                                                  const float2* __restrict__ ds, const float2* dprev,
+                                                                  float2* dnext, Geo g, double* __restrict__ partials,
+                                                                  const int* __restrict__ active,
+                                                                  const int* __restrict__ fan,
+                                                                  const float2* __restrict__ twg, float omega) {
+  using P = Plane<N, 2>;
+  __shared__ float2 buf[P::SIZE];
+  __shared__ float2 tw[N];
+  const P pl(buf, tw);
+  const int p = blockIdx.x, b = blockIdx.y;
+  const long long off = ((long long)b * (N / 2 + 1) + p) * N * N;
+  a0 += off; a1 += off; a2 += off; ds += off; dprev += off; dnext += off;
+  float2 v[8], keep[8], dsv[4], dp[4];
+  const int r0 = 4 * pl.g;                              // the k-space step's elements of this thread
+  if (pl.on) {
+    const float2* a = pl.g == 0 ? a0 : a1;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = a[pl.at_y(r)];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) { dsv[r] = ds[pl.at_x(r0 + r)]; dp[r] = dprev[pl.at_x(r0 + r)]; }
+  }
+  if (!active[b]) return;
+  stage_twiddles<N, P::NT>(tw, twg);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) keep[r] = v[r] * los_comp(g, 1, pl.row(r));
+  pl.template fft_y<false>(v);
+  pl.template fft_y<false>(keep, pl.g == 0);
+  if (pl.on && pl.g == 0) {
+    const float rx = los_comp(g, 0, pl.c);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      v[r] = v[r] * rx;
+      keep[r] = mul_i(keep[r]) * (g.kf * deriv_mode<N>(pl.row(r)));
+    }
+  }
+  __syncthreads();
+  if (pl.on) {
+    pl.put_y(v, pl.buf);
+    if (pl.g == 0) pl.put_y(keep, pl.mid);
+  }
+  __syncthreads();
+  if (pl.on) {
+    pl.get_x(v, pl.buf);
+    if (pl.g == 1) {
+      pl.get_x(keep, pl.mid);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) v[r] = v[r] + keep[r];
+    }
+  }
+  pl.template fft_x<false>(v);
+  // the other group's value of this thread's elements; slot r holds element r of the thread pair
+  if (pl.on) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) pl.mid[(4 - r0 + r) * P::NTF + pl.t] = pick(pl.g == 0, v[4 + r], v[r]);
+  }
+  __syncthreads();
+  double num = 0.0, den = 0.0;
+  if (pl.on) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float2 mine = pick(pl.g == 0, v[r], v[4 + r]), other = pl.mid[(r0 + r) * P::NTF + pl.t];
+      const float2 xa = pick(pl.g == 0, mine, other), ya = pick(pl.g == 0, other, mine);
+      float k2, dx, dy, dz;
+      int kzi;
+      x_wavenumbers<N>((long long)p * N + pl.cx, pl.jx + (r0 + r) * (N / 8), g.kf, k2, dx, dy, dz, kzi);
+      const float2 div = mul_i(xa) * dx + ya;
+      float2 dn = make_float2(fmaf(g.growth, div.x, dsv[r].x), fmaf(g.growth, div.y, dsv[r].y));
+      if (omega != 1.f) dn = make_float2(fmaf(omega, dn.x - dp[r].x, dp[r].x), fmaf(omega, dn.y - dp[r].y, dp[r].y));
+      dnext[pl.at_x(r0 + r)] = dn;
+      float2 pot = make_float2(0.f, 0.f);
+      if (k2 > 0.f) {
+        const float wgt = (kzi == 0 || kzi == N / 2) ? 1.f : 2.f;
+        const float kd2 = dx * dx + dy * dy + dz * dz;
+        const float f = wgt * kd2 / (k2 * k2);
+        const float ex = dn.x - dp[r].x, ey = dn.y - dp[r].y;
+        num += (double)(f * (ex * ex + ey * ey));
+        den += (double)(f * (dn.x * dn.x + dn.y * dn.y));
+        pot = dn * (g.inv_bn3 / k2);
+      }
+      pl.mid[(r0 + r) * P::NTF + pl.t] = pot;          // (the slot this thread has just read)
+    }
+  }
+  __syncthreads();
+  if (pl.on) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      v[r] = pl.mid[r * P::NTF + pl.t];
+      if (pl.g == 0) v[r] = mul_i(v[r]) * (g.kf * deriv_mode<N>(pl.jx + r * (N / 8)));
+    }
+  }
+  {
+    double t1, t2;
+    block_sum2<P::NT>(num, den, &t1, &t2);
+    if (threadIdx.x == 0) {
+      partials[2 * ((long long)b * gridDim.x + p) + 0] = t1;
+      partials[2 * ((long long)b * gridDim.x + p) + 1] = t2;
+    }
+  }
+  pl.template tail<FAN == PF_COMB>(v, g, p, FAN == PF_NONE || !fan[b], a0, a1, a2);
 }
 
 // Fixed-order reduction of per-block partial pairs: out[b] = sum over blocks, also written to the host's

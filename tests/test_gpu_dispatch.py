@@ -405,3 +405,59 @@ def test_grid_cells_round_once_to_floats(gpu_lib, n):
         plan.close()
         want = g / g.mean() - 1.0
         assert float((d - want).abs().max()) <= 1e-6 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("n", [8, 16, 32, 64])
+@pytest.mark.parametrize("start,relaxed", [(0, False), (0, True), (2, False)])
+def test_plane_passes_against_64_bits(gpu_lib, n, start, relaxed):
+    # the sizes whose y and x steps run per plane; tolerance as in the white-field test above
+    from paper_1504_02591_amd import native
+    box, obs, b, f = 10.0 * n, (-3.0 * n, 4.0 * n + 3.0, 7.0 * n), 1.8, 0.8
+    g = torch.Generator(device=dev()).manual_seed(n + start)
+    delta = torch.randn((n, n, n), generator=g, device=dev(), dtype=torch.float32)
+    delta -= delta.mean()
+    w = 2.0 / (2.0 + f / b) if relaxed else None
+    want = torch.stack(list(field_reference(delta, box, obs, b, f, 3, start, w)))
+    for graphs in (False, True):
+        plan = native.Plan(n, box, obs, b, f, 0.0, randoms=False, relaxed=relaxed, start_buffers=start != 0,
+                           graphs=graphs)
+        plan.set_delta(delta)
+        plan.solve(start)
+        plan.iterate(2, 0.0)
+        plan.iterate(1, 0.0)
+        psi = plan.psi()[0].double()
+        plan.close()
+        assert float((psi - want).norm()) <= 1e-5 * float(want.norm())
+
+
+@pytest.mark.parametrize("n,batch", [(16, 5), (32, 70), (64, 4), (64, 33)])
+def test_plane_passes_of_a_batch_that_stops_at_different_passes(gpu_lib, n, batch):
+    # work queued ahead for realisations that go on, and taken back for one that stops: each ends as it does
+    # alone, bit for bit, also where the sums of a batch go through the reduction kernel
+    from paper_1504_02591_amd import native
+    kw = dict(box_len=10.0 * n, observer=(4.0 * n, -2.0 * n, 3.0 * n), bias=1.1, growth=0.9, smooth_r=0.0, randoms=False)
+    # smooth and rough fields converge at different rates
+    fields = []
+    for i in range(batch):
+        f = torch.fft.rfftn(field(n, 300 + i))
+        k = torch.fft.fftfreq(n, device=dev()) * n
+        k2 = k.view(-1, 1, 1) ** 2 + k.view(1, -1, 1) ** 2 + k[:n // 2 + 1].view(1, 1, -1) ** 2
+        fields.append(torch.fft.irfftn(f * torch.exp(-k2 * (0.02 * (i % 7))), s=(n, n, n)).float().contiguous())
+    many = native.Plan(n, batch=batch, **kw)
+    many.set_delta(torch.stack(fields))
+    many.solve()
+    _, iters, eps = many.iterate(12, 0.02)
+    psi = many.psi()
+    many.close()
+    one = native.Plan(n, **kw)
+    seen = set()
+    for i in range(0, batch, max(1, batch // 8)):
+        one.set_delta(fields[i])
+        one.solve()
+        _, it1, e1 = one.iterate(12, 0.02)
+        seen.add(int(it1[0]))
+        assert it1[0] == iters[i]
+        assert torch.equal(one.psi()[0], psi[i])
+        assert e1[0] == eps[i]
+    one.close()
+    print(n, batch, sorted(seen), flush=True)
