@@ -16,6 +16,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/recon.h"
@@ -452,6 +453,8 @@ int wait_read(recon_plan_t* pl) {
 // Up to this many pairs of partial sums, a plane pass writes them to pinned memory for the host to add up,
 // instead of a launch that does (4 us a pass; 1024 pairs take the host 1 us).
 constexpr size_t kHostParts = 1024;
+// Sizes of a spectrum between which a pass uses plain accesses (SizeOps::hinted).
+constexpr size_t kPlainMin = 12u << 20, kPlainMax = 96u << 20;
 
 struct Ops {
   int (*setup)(recon_plan_t*);             // z/y/x/y/z/y/x chain from the painted grids to D_s and state X
@@ -563,6 +566,20 @@ struct SizeOps {
   static dim3 gy(const recon_plan_t* pl) { return dim3((N / 2 + 1) * (N / WY), pl->batch); }
   static dim3 gp(const recon_plan_t* pl) { return dim3(N / 2 + 1, pl->batch); }
   static dim3 gx(const recon_plan_t* pl) { return dim3((N / 2 + 1) * N / WX, pl->batch); }
+
+  // Runs f with the non-temporal choice of a pass's kernels (H).  Without the hint the five spectra of a pass
+  // stay in the 256 MB memory-side cache from one kernel to the next: taken where a spectrum is too large for
+  // the L2s to hold (there the hint's early write-out is the faster) and five are about that cache.  Eight
+  // passes, us, hint / plain: 128^3 465 / 527, 2 of 128^3 652 / 633, 4: 1162 / 1040, 8: 2180 / 1989, 16: 4194
+  // / 4290; 256^3 2113 / 1961, 2 of 256^3 3947 / 4128, 4: 8053 / 8788; 512^3 17150 / 18330.
+  template <class F>
+  static void hinted(const recon_plan_t* pl, F f) {
+    if constexpr (N == 128 || N == 256) {
+      const size_t bytes = sizeof(float2) * pl->cn * pl->batch;
+      if (bytes >= kPlainMin && bytes <= kPlainMax) return f(std::integral_constant<int, 0>());
+    }
+    f(std::integral_constant<int, stream_of<N>()>());
+  }
 
   // y and x forward of the painted grids' z spectra, smoothing, x and y inverse.  zflag / mflag (may be
   // null): z tiles whose rows were not written, and whose rows nothing reads afterwards
@@ -689,10 +706,10 @@ struct SizeOps {
   static int fanout(recon_plan_t* pl, const int* act, bool comb) {
     {
       PROF(pl, KP_Y_FANOUT);
-      if (comb)
-        k_y_fanout<N, true><<<gy(pl), dim3(TY), 0, pl->stream>>>(pl->w0, pl->w1, pl->w2, pl->geo, act, pl->tw);
-      else
-        k_y_fanout<N, false><<<gy(pl), dim3(TY), 0, pl->stream>>>(pl->w0, pl->w1, pl->w2, pl->geo, act, pl->tw);
+      hinted(pl, [&](auto h) {
+        auto kernel = comb ? k_y_fanout<N, true, h()> : k_y_fanout<N, false, h()>;
+        kernel<<<gy(pl), dim3(TY), 0, pl->stream>>>(pl->w0, pl->w1, pl->w2, pl->geo, act, pl->tw);
+      });
     }
     return check_launch(pl, "y fan-out");
   }
@@ -710,12 +727,13 @@ struct SizeOps {
     float* corr = MODE == ZI_PLAIN ? nullptr : pl->corr;
     double* part = MODE == ZI_PLAIN ? nullptr : pl->partials;
     const float* up = MODE == ZI_LEARNED ? pl->upbuf : nullptr;
-    if constexpr (z_col<N>())
-      k_z_iter_c<N, MODE><<<gzi<MODE>(pl), dim3(TZ), 0, pl->stream>>>(pl->w0, pl->w1, pl->w2, pl->geo, corr, part, act,
-                                                                     pl->tw, up);
-    else
-      k_z_iter<N, MODE><<<gzi<MODE>(pl), dim3(TZ), 0, pl->stream>>>(pl->w0, pl->w1, pl->w2, pl->geo, corr, part, act,
-                                                                   pl->tw, up);
+    auto go = [&](auto kernel) {
+      kernel<<<gzi<MODE>(pl), dim3(TZ), 0, pl->stream>>>(pl->w0, pl->w1, pl->w2, pl->geo, corr, part, act, pl->tw, up);
+    };
+    hinted(pl, [&](auto h) {
+      if constexpr (z_col<N>()) go(k_z_iter_c<N, MODE, h()>);
+      else go(k_z_iter<N, MODE, 0, h()>);
+    });
   }
 
   template <int TERMS>
@@ -752,7 +770,9 @@ struct SizeOps {
   static int fanin(recon_plan_t* pl, const int* act) {
     if constexpr (N > kPlaneN) {
       PROF(pl, KP_Y_FANIN);
-      k_y_fanin<N><<<gy(pl), dim3(TY), 0, pl->stream>>>(pl->w0, pl->w1, pl->geo, act, pl->tw);
+      hinted(pl, [&](auto h) {
+        k_y_fanin<N, h()><<<gy(pl), dim3(TY), 0, pl->stream>>>(pl->w0, pl->w1, pl->geo, act, pl->tw);
+      });
       return check_launch(pl, "y fan-in");
     }
     return RECON_OK;
@@ -772,8 +792,10 @@ struct SizeOps {
         else if (fan == SY_FULL) go(k_plane_iter<N, PF_FULL>);
         else go(k_plane_iter<N, PF_NONE>);
       } else {
-        k_x_iter<N><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->ds, prev, pl->dn, pl->geo, pl->partials, act, pl->tw,
-                                                omega);
+        hinted(pl, [&](auto h) {
+          k_x_iter<N, h()><<<gx(pl), dim3(TX), 0, s>>>(pl->w0, pl->w1, pl->ds, prev, pl->dn, pl->geo, pl->partials, act,
+                                                       pl->tw, omega);
+        });
       }
     }
     RECON_TRY(check_launch(pl, "x iteration"));

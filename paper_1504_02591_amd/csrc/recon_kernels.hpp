@@ -943,7 +943,7 @@ struct ZStage {
   static constexpr int SIZE = NCH * 128;              // float2 elements
 };
 
-template <int N, int WP, int NT>
+template <int N, int WP, int NT, int H = stream_of<N>()>
 __device__ __forceinline__ void z_stage_issue(float2* stage, const float2* __restrict__ a, int y, int x0) {
   using S = ZStage<N, WP>;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -953,7 +953,7 @@ __device__ __forceinline__ void z_stage_issue(float2* stage, const float2* __res
     if (m < S::ROWS && in_bounds(e + 1, (long long)(N / 2 + 1) * N * N)) {
       const float2* g = a + e;
       __builtin_amdgcn_global_load_lds((const void*)g, (__attribute__((address_space(3))) void*)(stage + q * 128),
-                                       16, 0, kStageCachePolicy);
+                                       16, 0, (H & 2) ? 2 : 0 /* the nt bit */);
     }
   }
 }
@@ -976,7 +976,7 @@ __device__ __forceinline__ void z_pack_stage(float2* v, const float2* stage, int
 
 // Split a transformed packed tile (natural order in LDS) into the half spectra of its
 // two real columns and store them.  MULK: multiply by i k'_z.
-template <int N, int WP, int NT, bool MULK>
+template <int N, int WP, int NT, bool MULK, int H = stream_of<N>()>
 __device__ __forceinline__ void z_unpack_store(const float2* buf, float2* __restrict__ out, int y, int x0, float kf) {
   using L = Lay<N, WP, false>;
   for (int e = threadIdx.x; e < (N / 2 + 1) * WP; e += NT) {
@@ -992,8 +992,8 @@ __device__ __forceinline__ void z_unpack_store(const float2* buf, float2* __rest
     }
     const long long base = ((long long)kz * N + y) * N + x0 + p;
     constexpr long long CN = (long long)(N / 2 + 1) * N * N;
-    if (in_bounds(base, CN)) st_stream(out + base, A);
-    if (in_bounds(base + WP, CN)) st_stream(out + base + WP, B);
+    if (in_bounds(base, CN)) st_stream<H>(out + base, A);
+    if (in_bounds(base + WP, CN)) st_stream<H>(out + base + WP, B);
   }
 }
 
@@ -1025,8 +1025,9 @@ struct ZCol {
   __device__ __forceinline__ static unsigned lane() {
     return ((unsigned)(threadIdx.x >> 4) * (unsigned)(N * N) + (threadIdx.x & 15)) * 8u;
   }
+  template <int H = stream_of<N>()>
   __device__ __forceinline__ static void fetch(Half& h, const float2* arr, int y, int x0) {
-    constexpr bool HINT = (RECON_STREAM & 2) != 0;
+    constexpr bool HINT = (H & 2) != 0;
     const unsigned l = lane();
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
@@ -1064,9 +1065,9 @@ struct ZCol {
   }
   // Half spectra of the two real columns of each packed column (natural order in the tile) to memory;
   // MULK: times i k'_z.
-  template <bool MULK>
+  template <bool MULK, int H = stream_of<N>()>
   __device__ __forceinline__ static void unpack(const float2* buf, float2* out, int y, int x0, float kf) {
-    constexpr bool HINT = (RECON_STREAM & 1) != 0;
+    constexpr bool HINT = (H & 1) != 0;
     const int m0 = threadIdx.x >> 4, p = threadIdx.x & 15;
     const unsigned l = lane();
     auto one = [&](int kz, const PlaneBuf& pb) {
@@ -1428,7 +1429,7 @@ __global__ void __launch_bounds__(256) k_log_shift(float* __restrict__ delta, lo
 // and both accumulate S1 = sum Delta u_p, S2 = sum Delta^2 into partials.  On the pass after such
 // a start, ZI_CROSS iterates as ZI_PLAIN and accumulates S3 = sum Delta u_1 (second entry 0), the
 // cross term of ||Psi_1 - Psi_0||^2.
-template <int N, int MODE, int SPLIT = 0>
+template <int N, int MODE, int SPLIT = 0, int H = stream_of<N>()>
 __global__ void __launch_bounds__((ntzs<N, SPLIT>())) k_z_iter(float2* __restrict__ a0, float2* __restrict__ a1,
                                                      const float2* __restrict__ a2, Geo g, float* __restrict__ corr,
                                                      double* __restrict__ partials, const int* __restrict__ active,
@@ -1457,7 +1458,7 @@ __global__ void __launch_bounds__((ntzs<N, SPLIT>())) k_z_iter(float2* __restric
   // py < 0: nothing deferred
   constexpr bool DEFER = RECON_Z_DEFER && MODE != ZI_LEARNED;
   int py = -1, px0 = 0;
-  if (MODE != ZI_LEARNED && tile < (ztiles<N, SPLIT>())) z_stage_issue<N, WP, NT>(stage, a0, y, x0);
+  if (MODE != ZI_LEARNED && tile < (ztiles<N, SPLIT>())) z_stage_issue<N, WP, NT, H>(stage, a0, y, x0);
 #pragma unroll 1
   for (int t = 0; t < TPB && tile < (ztiles<N, SPLIT>()); ++t) {     // block-uniform bound
     int c, j;
@@ -1472,8 +1473,8 @@ __global__ void __launch_bounds__((ntzs<N, SPLIT>())) k_z_iter(float2* __restric
       __syncthreads();
       if (act) z_pack_stage<N, WP>(s, stage, c, j);
       __syncthreads();                                // every thread has read the staged tile
-      if (DEFER && py >= 0) z_unpack_store<N, WP, NT, true>(buf, a1, py, px0, g.kf);
-      z_stage_issue<N, WP, NT>(stage, a2, y, x0);
+      if (DEFER && py >= 0) z_unpack_store<N, WP, NT, true, H>(buf, a1, py, px0, g.kf);
+      z_stage_issue<N, WP, NT, H>(stage, a2, y, x0);
       fft_rr<N, WP, true, false, SPLIT>(s, buf, tw);        // (its first barrier ends the reads of buf above)
       z_stage_wait();
       __syncthreads();
@@ -1481,7 +1482,7 @@ __global__ void __launch_bounds__((ntzs<N, SPLIT>())) k_z_iter(float2* __restric
       if (t + 1 < TPB && next < (ztiles<N, SPLIT>())) {
         __syncthreads();
         z_tile_at<N, WP>(next, ny, nx0);
-        z_stage_issue<N, WP, NT>(stage, a0, ny, nx0);
+        z_stage_issue<N, WP, NT, H>(stage, a0, ny, nx0);
       }
       fft_rr<N, WP, true, false, SPLIT>(v, buf, tw);
     }
@@ -1525,17 +1526,17 @@ __global__ void __launch_bounds__((ntzs<N, SPLIT>())) k_z_iter(float2* __restric
     // Z[q] -> a0 and i k'_z Z[r_z q] -> a1; Z[V_x] = r_x Z[q] and Z[V_y] = r_y Z[q] are formed in
     // the y pass
     fft_rl<N, WP, false, false, SPLIT>(s, buf, tw);
-    z_unpack_store<N, WP, NT, false>(buf, a0, y, x0, g.kf);
+    z_unpack_store<N, WP, NT, false, H>(buf, a0, y, x0, g.kf);
     fft_rl<N, WP, false, false, SPLIT>(v, buf, tw);
     if (DEFER) {
       py = y;
       px0 = x0;
     } else {
-      z_unpack_store<N, WP, NT, true>(buf, a1, y, x0, g.kf);
+      z_unpack_store<N, WP, NT, true, H>(buf, a1, y, x0, g.kf);
     }
     tile = next; y = ny; x0 = nx0;
   }
-  if (DEFER && py >= 0) z_unpack_store<N, WP, NT, true>(buf, a1, py, px0, g.kf);
+  if (DEFER && py >= 0) z_unpack_store<N, WP, NT, true, H>(buf, a1, py, px0, g.kf);
   if (MODE != ZI_PLAIN) {
     double t1, t2;
     block_sum2<NT>((double)acc1, (double)acc2, &t1, &t2);
@@ -1552,7 +1553,7 @@ __global__ void __launch_bounds__((ntzs<N, SPLIT>())) k_z_iter(float2* __restric
 // loads, three transforms and stores, so the blocks are small (N threads) and two or more share a CU, one
 // loading or storing while another transforms.  512^3 0.556 -> 0.462 ms (1024-thread blocks of the radix-8
 // engine with wave-local transforms before), 256^3 69 -> 56 us, 1024^3 8.4 -> 6.3 ms.
-template <int N, int MODE>
+template <int N, int MODE, int H = stream_of<N>()>
 __global__ void __launch_bounds__(N, N == 512 ? 4 : 1) k_z_iter_c(float2* __restrict__ a0, float2* __restrict__ a1,
                                                   const float2* __restrict__ a2, Geo g, float* __restrict__ corr,
                                                   double* __restrict__ partials, const int* __restrict__ active,
@@ -1575,9 +1576,9 @@ __global__ void __launch_bounds__(N, N == 512 ? 4 : 1) k_z_iter_c(float2* __rest
   if constexpr (MODE != ZI_LEARNED) {
     // Psi_z's loads run under the transverse part's transform
     typename C::Half h;
-    C::fetch(h, a0, y, x0);
+    C::template fetch<H>(h, a0, y, x0);
     C::put(h, buf);
-    C::fetch(h, a2, y, x0);
+    C::template fetch<H>(h, a2, y, x0);
     __syncthreads();
     C::frag(s, buf, c, j);
     col_fft<N, true>(s, buf, tw, c, j);
@@ -1629,9 +1630,9 @@ __global__ void __launch_bounds__(N, N == 512 ? 4 : 1) k_z_iter_c(float2* __rest
   }
   // Z[q] -> a0 and i k'_z Z[r_z q] -> a1
   col_fft_lds<N, false>(s, buf, tw, c, j);
-  C::template unpack<false>(buf, a0, y, x0, g.kf);
+  C::template unpack<false, H>(buf, a0, y, x0, g.kf);
   col_fft_lds<N, false>(v, buf, tw, c, j);
-  C::template unpack<true>(buf, a1, y, x0, g.kf);
+  C::template unpack<true, H>(buf, a1, y, x0, g.kf);
   if (MODE != ZI_PLAIN) {
     double t1, t2;
     block_sum2<N>((double)acc1, (double)acc2, &t1, &t2);
@@ -1816,25 +1817,25 @@ struct YTile {
 };
 
 // Element r of a fragment is row j + r ST of plane p.
-template <int N>
+template <int N, int H = stream_of<N>()>
 __device__ __forceinline__ void y_load(float2* v, const float2* __restrict__ a, int p, int x0, int c, int j) {
   const PlaneBuf pl(a + (long long)p * N * N, (unsigned)N * N * 8);
   const unsigned lane = ((unsigned)j * N + x0 + c) * 8;
 #pragma unroll
   for (int r = 0; r < y_el<N>(); ++r)
     v[r] = in_bounds((long long)p * N * N + lane / 8 + r * y_st<N>() * N, (long long)(N / 2 + 1) * N * N)
-               ? pl.template load<(RECON_STREAM & 2) != 0>(lane, r * y_st<N>() * N * 8)
+               ? pl.template load<(H & 2) != 0>(lane, r * y_st<N>() * N * 8)
                : float2{};
 }
 
-template <int N>
+template <int N, int H = stream_of<N>()>
 __device__ __forceinline__ void y_store(const float2* v, float2* __restrict__ a, int p, int x0, int c, int j) {
   const PlaneBuf pl(a + (long long)p * N * N, (unsigned)N * N * 8);
   const unsigned lane = ((unsigned)j * N + x0 + c) * 8;
 #pragma unroll
   for (int r = 0; r < y_el<N>(); ++r)
     if (in_bounds((long long)p * N * N + lane / 8 + r * y_st<N>() * N, (long long)(N / 2 + 1) * N * N))
-      pl.template store<(RECON_STREAM & 1) != 0>(v[r], lane, r * y_st<N>() * N * 8);
+      pl.template store<(H & 1) != 0>(v[r], lane, r * y_st<N>() * N * 8);
 }
 
 // Row flags (flag != null): one byte per z tile (one y row, 2 wz consecutive x), [NA][batch][z tiles]
@@ -1882,12 +1883,12 @@ __global__ void __launch_bounds__((YTile<N, yp_col<N>()>::NT)) k_y_plain(float2*
     float2 v[Y::E];
     if (act) {
 #pragma unroll
-      for (int r = 0; r < Y::E; ++r) v[r] = pl.template load<(RECON_STREAM & 2) != 0>(at(r, !INV), r * Y::ST * N * 8);
+      for (int r = 0; r < Y::E; ++r) v[r] = pl.template load<(stream_of<N>() & 2) != 0>(at(r, !INV), r * Y::ST * N * 8);
     }
     Y::template fft<INV>(v, buf, tw, c, j);
     if (act) {
 #pragma unroll
-      for (int r = 0; r < Y::E; ++r) pl.template store<(RECON_STREAM & 1) != 0>(v[r], at(r, INV), r * Y::ST * N * 8);
+      for (int r = 0; r < Y::E; ++r) pl.template store<(stream_of<N>() & 1) != 0>(v[r], at(r, INV), r * Y::ST * N * 8);
     }
   }
 }
@@ -1901,7 +1902,7 @@ __global__ void __launch_bounds__((YTile<N, yp_col<N>()>::NT)) k_y_plain(float2*
 // and r_y are constant along a z column, so the transverse part of Psi . r is formed here, before
 // the z transform:
 //   a0 <- r_x Y^-1[a0] + r_y Y^-1[i k'_y a1],   a2 <- i k'_z Y^-1[a1]   (a1 is left as it was)
-template <int N, bool COMB>
+template <int N, bool COMB, int H = stream_of<N>()>
 __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanout(float2* __restrict__ a0, float2* __restrict__ a1,
                                                        float2* __restrict__ a2, Geo g, const int* __restrict__ active,
                                                        const float2* __restrict__ twg) {
@@ -1925,7 +1926,7 @@ __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanout(float2*
   {
     float2 keep[Y::E];
     if (act) {
-      y_load<N>(keep, a1, p, x0, c, j);
+      y_load<N, H>(keep, a1, p, x0, c, j);
 #pragma unroll
       for (int r = 0; r < Y::E; ++r) w[r] = mul_i(keep[r]) * (g.kf * deriv_mode<N>(j + r * Y::ST));
     }
@@ -1934,12 +1935,12 @@ __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanout(float2*
       const float kz = g.kf * deriv_mode<N>(p);     // p in [0, N/2]; N/2 is the Nyquist plane
 #pragma unroll
       for (int r = 0; r < Y::E; ++r) keep[r] = mul_i(keep[r]) * kz;
-      y_store<N>(keep, a2, p, x0, c, j);
-      y_load<N>(v, a0, p, x0, c, j);               // in flight during the transform of w
+      y_store<N, H>(keep, a2, p, x0, c, j);
+      y_load<N, H>(v, a0, p, x0, c, j);               // in flight during the transform of w
     }
   }
   Y::template fft<true>(w, buf, tw, c, j);
-  if (!COMB && act) y_store<N>(w, a1, p, x0, c, j);
+  if (!COMB && act) y_store<N, H>(w, a1, p, x0, c, j);
   Y::template fft<true>(v, buf, tw, c, j);
   if (act) {
     if (COMB) {
@@ -1951,7 +1952,7 @@ __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanout(float2*
         v[r] = make_float2(fmaf(ry, w[r].x, t.x), fmaf(ry, w[r].y, t.y));
       }
     }
-    y_store<N>(v, a0, p, x0, c, j);
+    y_store<N, H>(v, a0, p, x0, c, j);
   }
 }
 
@@ -1975,7 +1976,7 @@ __global__ void __launch_bounds__(256) k_y_combine(float2* __restrict__ a0, cons
 // iteration's q = u / |r| with r the scaled line of sight, so that V_j = q r_j):
 //   a0 <- r_x Y[a0]                   (x component Y Z[V_x]; i k'_x applied in the x pass)
 //   a1 <- i k'_y Y[r_y a0] + Y[a1]    (y component plus the z component)
-template <int N>
+template <int N, int H = stream_of<N>()>
 __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanin(float2* __restrict__ a0, float2* __restrict__ a1, Geo g,
                                                       const int* __restrict__ active, const float2* __restrict__ twg) {
   constexpr int NT = nty<N>(), W = wy<N>();
@@ -1993,7 +1994,7 @@ __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanin(float2* 
   a0 += b * cn; a1 += b * cn;
   float2 v[Y::E], keep[Y::E];
   if (act) {
-    y_load<N>(v, a0, p, x0, c, j);
+    y_load<N, H>(v, a0, p, x0, c, j);
 #pragma unroll
     for (int r = 0; r < Y::E; ++r) keep[r] = v[r] * los_comp(g, 1, j + r * Y::ST);
   }
@@ -2002,8 +2003,8 @@ __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanin(float2* 
     const float rx = los_comp(g, 0, x0 + c);
 #pragma unroll
     for (int r = 0; r < Y::E; ++r) v[r] = v[r] * rx;
-    y_store<N>(v, a0, p, x0, c, j);
-    y_load<N>(v, a1, p, x0, c, j);                  // in flight during the next transform
+    y_store<N, H>(v, a0, p, x0, c, j);
+    y_load<N, H>(v, a1, p, x0, c, j);                  // in flight during the next transform
   }
   Y::template fft<false>(keep, buf, tw, c, j);
   if (act) {
@@ -2014,28 +2015,28 @@ __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanin(float2* 
   if (act) {
 #pragma unroll
     for (int r = 0; r < Y::E; ++r) v[r] = v[r] + keep[r];
-    y_store<N>(v, a1, p, x0, c, j);
+    y_store<N, H>(v, a1, p, x0, c, j);
   }
 }
 
 // ---------------------------------------------------------------------------
 // x passes.  Tile: W consecutive rows (row = kz * N + ky), all N x; row-fast fragments.
 // ---------------------------------------------------------------------------
-template <int N>
+template <int N, int H = stream_of<N>()>
 __device__ __forceinline__ void x_load(float2* v, const float2* __restrict__ a, long long row, int j) {
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const long long e = row * N + j + r * (N / 8);
-    v[r] = in_bounds(e, (long long)(N / 2 + 1) * N * N) ? ld_stream(a + e) : float2{};
+    v[r] = in_bounds(e, (long long)(N / 2 + 1) * N * N) ? ld_stream<H>(a + e) : float2{};
   }
 }
 
-template <int N>
+template <int N, int H = stream_of<N>()>
 __device__ __forceinline__ void x_store(const float2* v, float2* __restrict__ a, long long row, int j) {
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const long long e = row * N + j + r * (N / 8);
-    if (in_bounds(e, (long long)(N / 2 + 1) * N * N)) st_stream(a + e, v[r]);
+    if (in_bounds(e, (long long)(N / 2 + 1) * N * N)) st_stream<H>(a + e, v[r]);
   }
 }
 
@@ -2198,7 +2199,7 @@ __global__ void __launch_bounds__(256) k_helm_out(const float* __restrict__ psi,
 #else
 #define RECON_X_ITER_BOUNDS(N) __launch_bounds__(ntx<N>())
 #endif
-template <int N>
+template <int N, int H = stream_of<N>()>
 __global__ void RECON_X_ITER_BOUNDS(N) k_x_iter(float2* __restrict__ a0, float2* __restrict__ a1,
                                                      const float2* __restrict__ ds, const float2* dprev,
                                                      float2* dnext, Geo g, double* __restrict__ partials,
@@ -2218,9 +2219,9 @@ __global__ void RECON_X_ITER_BOUNDS(N) k_x_iter(float2* __restrict__ a0, float2*
   const long long row = (long long)blockIdx.x * W + c;
   a0 += b * cn; a1 += b * cn; ds += b * cn; dprev += b * cn; dnext += b * cn;
   float2 xa[8], v[8];
-  if (act) x_load<N>(xa, a0, row, j);
+  if (act) x_load<N, H>(xa, a0, row, j);
   fft_rr<N, W, false, true>(xa, buf, tw);
-  if (act) x_load<N>(v, a1, row, j);
+  if (act) x_load<N, H>(v, a1, row, j);
   fft_rr<N, W, false, true>(v, buf, tw);
   double num = 0.0, den = 0.0;
   if (act) {
@@ -2260,9 +2261,9 @@ __global__ void RECON_X_ITER_BOUNDS(N) k_x_iter(float2* __restrict__ a0, float2*
     }
   }
   fft_rr<N, W, true, true>(xa, buf, tw);
-  if (act) x_store<N>(xa, a0, row, j);
+  if (act) x_store<N, H>(xa, a0, row, j);
   fft_rr<N, W, true, true>(v, buf, tw);
-  if (act) x_store<N>(v, a1, row, j);
+  if (act) x_store<N, H>(v, a1, row, j);
 }
 
 // ---------------------------------------------------------------------------

@@ -461,3 +461,9 @@ def test_plane_passes_of_a_batch_that_stops_at_different_passes(gpu_lib, n, batc
         assert e1[0] == eps[i]
     one.close()
     print(n, batch, sorted(seen), flush=True)
+
+
+@pytest.mark.parametrize("n,batch", [(128, 2), (256, 2)])
+def test_non_temporal_choice_does_not_change_the_result(gpu_lib, n, batch):
+    # one of 128^3 and two of 256^3 run hinted, two of 128^3 and one of 256^3 plain: the same bits
+    test_z_tiles_per_block_do_not_change_the_result(gpu_lib, n, batch)
