@@ -1920,8 +1920,7 @@ __global__ void __launch_bounds__(nty<N>(), N == 512 ? 4 : 1) k_y_fanout(float2*
   const long long cn = (long long)(N / 2 + 1) * N * N;
   a0 += b * cn; a1 += b * cn; a2 += b * cn;
   // a1 first: once its z component is stored only w is live, so a0 is loaded while w is transformed
-  // and no transform runs with more than two arrays live (97 VGPRs; holding a0 and a1 through the
-  // first transform needs 119)
+  // and no transform runs with more than two arrays live (a third would not fit the registers)
   float2 v[Y::E], w[Y::E];
   {
     float2 keep[Y::E];

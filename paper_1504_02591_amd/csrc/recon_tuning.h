@@ -51,8 +51,8 @@
 //   reorder after the brick-order shift, chunks of one block (shift stage, both catalogues)
 //     per_x apart: 1.096   adjacent (one trip per block), 2 / 4 / 8 chunks: 0.980 / 0.983 / 0.980
 // Non-temporal hint on the transform passes' spectrum accesses (bit 0 stores, bit 1 loads), timed on
-// the 512^3 survey reconstruction (plain start, 6 passes, ms per reconstruction): 0: 20.30 / 20.46,
-// 1: 19.71, 2: 19.96, 3: 19.41 / 19.45 (two runs; Psi bit-identical).  The same hint on the deposit's
+// the 512^3 survey reconstruction (plain start, 6 passes, ms per reconstruction): 0: 19.69, 1: 19.10,
+// 2: 19.24, 3: 18.69 (Psi bit-identical).  The same hint on the deposit's
 // scattered brick-ordered copy made the binning 2.4x slower (0.79 -> 1.92 ms) and is not used.
 // At 1024^3 the z and x passes gained likewise (8.80 -> 8.32, 6.09 -> 5.95 ms).
 // Binning above 512^3 (more bricks than one LDS histogram holds): per-block windows of the LDS
