@@ -336,6 +336,10 @@ __global__ void __launch_bounds__(256) k_loss(const float* __restrict__ y, const
 // one row of partial sums per block; k_reduce_parts adds the rows in FP64 in a fixed order, so a step
 // is deterministic for a given grid and batch.
 // ---------------------------------------------------------------------------
+// 16 bytes as a vector: arrays of the struct uint4 held across a barrier are put in scratch memory (the weight
+// gradients took 120 and 52 us with it, 58 and 35 us as below).
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+
 constexpr int kBwdBlocks = 1024;   // most blocks (rows of partial sums) of a backward launch
 
 // Output-layer backward: d2[p][i] = bf16((sum_t W3[t][i] dy[p - d_t]) * [a2[p][i] > 0]),
@@ -380,14 +384,14 @@ __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ 
     const int x0 = (tt % nbx) * FX, y0 = ((tt / nbx) % nby) * FY, z0 = (tt / (nbx * nby)) * FZ;
     constexpr int PD = (GCELLS + 255) / 256, PA = CELLS * 2 / 256;
     float dv[PD];
-    uint4 av[PA];
+    u4 av[PA];
 #pragma unroll
     for (int k = 0; k < PD; ++k) {
       const int c0 = threadIdx.x + k * 256, c = c0 < GCELLS ? c0 : GCELLS - 1;
       const int hx = c % GX, hy = (c / GX) % GY, hz = c / (GX * GY);
       dv[k] = dy[b * n3 + ((long long)((z0 - 1 + hz) & msk) * n + ((y0 - 1 + hy) & msk)) * n + ((x0 - 1 + hx) & msk)];
     }
-    const uint4* a128 = (const uint4*)a2;
+    const u4* a128 = (const u4*)a2;
 #pragma unroll
     for (int k = 0; k < PA; ++k) {
       const int e = threadIdx.x + k * 256, cell = e >> 1;
@@ -399,7 +403,7 @@ __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ 
     for (int k = 0; k < PD; ++k)
       if (threadIdx.x + k * 256 < GCELLS) dyt[threadIdx.x + k * 256] = dv[k];
 #pragma unroll
-    for (int k = 0; k < PA; ++k) ((uint4*)tile)[threadIdx.x + k * 256] = av[k];
+    for (int k = 0; k < PA; ++k) ((u4*)tile)[threadIdx.x + k * 256] = av[k];
     __syncthreads();
     for (int c = threadIdx.x; c < CELLS; c += 256)
       bacc += dyt[((c / (FX * FY) + 1) * GY + (c / FX) % FY + 1) * GX + c % FX + 1];
@@ -459,8 +463,9 @@ __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ 
 // tap is only an address offset and nothing is gathered element by element.  A group of lanes reads 128
 // contiguous bytes, free of bank conflicts.  The four waves split the column tiles; a block takes
 // several tiles of 16 x 4 x 8 positions and writes one partial [16][KP + 1] (bias in the last column).
-// Bound by the LDS reads of the x operand (1 KB per product).  On a 128^3 network grid 119 us (layer 2)
-// and 52 us (layer 1); with element-by-element gathers of the operand, 225 and 201 us.
+// Bound by the staging of a tile before its products (with a wave taking two z planes and all taps, a third
+// of the LDS reads, 56 us instead of 58).  On a 128^3 network grid 58 us (layer 2) and 35 us (layer 1); with
+// element-by-element gathers of the operand, 225 and 201 us.
 constexpr int VX = 16, VY = 4, VZ = 8, UX = VX + 2, UY = VY + 2, UZ = VZ + 2, UCELLS = UX * UY * UZ;
 constexpr int VCELLS = VX * VY * VZ;
 
@@ -506,25 +511,25 @@ __global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict_
       return b * n3 + ((long long)((z0 - 1 + hz) & msk) * n + ((y0 - 1 + hy) & msk)) * n + ((x0 - 1 + hx) & msk);
     };
     constexpr int PD = VCELLS * 2 / 256;
-    uint4 dv[PD];
+    u4 dv[PD];
 #pragma unroll
     for (int k = 0; k < PD; ++k) {
       const int e = threadIdx.x + k * 256, cell = e >> 1;
       const int lx = cell % VX, ly = (cell / VX) % VY, lz = cell / (VX * VY);
-      dv[k] = ((const uint4*)dpre)[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)];
+      dv[k] = ((const u4*)dpre)[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)];
     }
     if constexpr (SRC == 0) {
       constexpr int CPC = C / 8, TOTAL = UCELLS * CPC, PER = (TOTAL + 255) / 256;
-      uint4 v[PER];
+      u4 v[PER];
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         const int e0 = threadIdx.x + k * 256, e = e0 < TOTAL ? e0 : TOTAL - 1;
-        v[k] = *(const uint4*)(in + halo(e / CPC) * C + 8 * (e % CPC));
+        v[k] = *(const u4*)(in + halo(e / CPC) * C + 8 * (e % CPC));
       }
       __syncthreads();                        // every wave is done with the last tile
 #pragma unroll
       for (int k = 0; k < PER; ++k)
-        if (threadIdx.x + k * 256 < TOTAL) ((uint4*)xt)[threadIdx.x + k * 256] = v[k];
+        if (threadIdx.x + k * 256 < TOTAL) ((u4*)xt)[threadIdx.x + k * 256] = v[k];
     } else {
       constexpr int PER = (UCELLS + 255) / 256;
       float fd[PER], fu[PER];
@@ -546,7 +551,7 @@ __global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict_
       }
     }
 #pragma unroll
-    for (int k = 0; k < PD; ++k) ((uint4*)dt)[threadIdx.x + k * 256] = dv[k];
+    for (int k = 0; k < PD; ++k) ((u4*)dt)[threadIdx.x + k * 256] = dv[k];
     __syncthreads();
     const int da = (4 * q + r) * CH + 4 * c;  // dpre element of this lane in a row
 #pragma unroll 2
