@@ -613,6 +613,7 @@ __device__ __forceinline__ void brick_prepare(const unsigned* __restrict__ count
     }
   }
   const bool was = valid[key] != 0;
+  __syncthreads();                                       // every thread has read the flag that thread 0 replaces
   const bool clear = mode == 0 ? touched : (mode == 1 ? (touched && !was) : !was);
   if (clear) {
     // 16-byte stores, two cells each (a brick row starts at an even cell, the grid on 16 bytes)
