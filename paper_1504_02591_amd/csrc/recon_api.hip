@@ -487,7 +487,6 @@ int scalars_and_mask(recon_plan_t* pl, int nblk_z, int tw) {
   k_scalars<<<pl->batch, 256, 0, pl->stream>>>(pl->tpart, nblk_z, pl->n3, pl->p.mask_tau, pl->randoms ? 1 : 0,
                                                pl->totals, pl->dscal, pl->thr, pl->status, pl->err, pl->hd_stat);
   RECON_TRY(check_launch(pl, "scalars"));
-  if (pl->hd_stat) HIP_TRY(pl, hipEventRecord(pl->ev, pl->stream));    // recon_solve waits for this much
   if (pl->randoms) {
     const unsigned char* v = valid_of(pl, RECON_RAN);
     if (v && tw % kBrick == 0) {
@@ -1425,20 +1424,19 @@ int recon_solve(recon_plan_t* pl, int start, const void* net) {
     if (pl->randoms && !pl->painted_r) return fail(pl, RECON_ESTATE, "randoms were not painted");
     Marker mark("a2-a6 totals, smoothing, mask, overdensity, D_s");
     RECON_TRY(ops->setup(pl));
-    // one read-back: invalid-object counters and the totals status of every realisation.  They are known
-    // once the totals are, right after the forward z pass: the rest of the setup runs on while the caller
-    // goes on.
+    // one read-back: invalid-object counters and the totals status of every realisation, once the whole
+    // setup is done (the call is a synchronisation point: it leaves nothing of the setup queued).
     std::vector<int> st(pl->batch, 0);
     int errs[2] = {0, 0};
+    if (!pl->hd_stat) {
+      HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, 2 * sizeof(int), hipMemcpyDeviceToHost, pl->stream));
+      HIP_TRY(pl, hipMemcpyAsync(st.data(), pl->status, sizeof(int) * pl->batch, hipMemcpyDeviceToHost, pl->stream));
+    }
+    HIP_TRY(pl, hipStreamSynchronize(pl->stream));
     if (pl->hd_stat) {
-      RECON_TRY(wait_read(pl));
       errs[0] = (int)pl->h_stat[0];
       errs[1] = (int)pl->h_stat[1];
       for (int b = 0; b < pl->batch; ++b) st[b] = (int)pl->h_stat[2 + b];
-    } else {
-      HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, 2 * sizeof(int), hipMemcpyDeviceToHost, pl->stream));
-      HIP_TRY(pl, hipMemcpyAsync(st.data(), pl->status, sizeof(int) * pl->batch, hipMemcpyDeviceToHost, pl->stream));
-      HIP_TRY(pl, hipStreamSynchronize(pl->stream));
     }
     const int errcount = errs[0] + (pl->randoms ? errs[1] : 0);
     if (errcount) return fail(pl, RECON_EINVAL, std::to_string(errcount) + " objects had invalid positions or weights");
