@@ -1014,6 +1014,11 @@ template <int N>
 struct ZCol {
   using G = Col<N>;
   static constexpr int WP = 16, RT = N / 16, RL = 8;      // rows a load step apart, load steps (kz < N/2)
+  // whether column x of row (kz, y) lies in the spectrum (debug build), from its own index: a buffer access
+  // that leaves its rows would be dropped without a trace
+  __device__ __forceinline__ static bool inside(int kz, int y, int x) {
+    return in_bounds(((long long)kz * N + y) * N + x, (long long)(N / 2 + 1) * N * N);
+  }
   // half-spectrum rows kz = m + i RT (i < 8) of columns p and p + 16 of an array, and of row N/2 in the
   // first 16 threads: loads that stay in flight while another array is transformed
   struct Half {
@@ -1030,16 +1035,17 @@ struct ZCol {
   __device__ __forceinline__ static void fetch(Half& h, const float2* arr, int y, int x0) {
     constexpr bool HINT = (H & 2) != 0;
     const unsigned l = lane();
+    const int m0 = threadIdx.x >> 4, x = x0 + (threadIdx.x & 15);
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
       const PlaneBuf pb = rows(arr, i * RT, y, x0);
-      h.a[i] = pb.template load<HINT>(l, 0);
-      h.b[i] = pb.template load<HINT>(l, WP * 8);
+      h.a[i] = inside(m0 + i * RT, y, x) ? pb.template load<HINT>(l, 0) : float2{};
+      h.b[i] = inside(m0 + i * RT, y, x + WP) ? pb.template load<HINT>(l, WP * 8) : float2{};
     }
     if (threadIdx.x < 16) {
       const PlaneBuf pb = rows(arr, N / 2, y, x0);
-      h.na = pb.template load<HINT>(l, 0);
-      h.nb = pb.template load<HINT>(l, WP * 8);
+      h.na = inside(N / 2, y, x) ? pb.template load<HINT>(l, 0) : float2{};
+      h.nb = inside(N / 2, y, x + WP) ? pb.template load<HINT>(l, WP * 8) : float2{};
     }
   }
   // the packed full-length columns Z = A + i B, extended Hermitian-wise, in natural order in the tile
@@ -1080,8 +1086,8 @@ struct ZCol {
         A = mul_i(A) * k;
         B = mul_i(B) * k;
       }
-      pb.template store<HINT>(A, l, 0);
-      pb.template store<HINT>(B, l, WP * 8);
+      if (inside(kz, y, x0 + p)) pb.template store<HINT>(A, l, 0);
+      if (inside(kz, y, x0 + p + WP)) pb.template store<HINT>(B, l, WP * 8);
     };
 #pragma unroll
     for (int i = 0; i < RL; ++i) one(m0 + i * RT, rows(out, i * RT, y, x0));
@@ -1139,25 +1145,34 @@ struct ZField {
   static constexpr int ST = ZTile<N, COL>::ST, WP = wz<N>();
   const char* base;
   unsigned lane;
+  long long first;                                       // element (r, h) = (0, 0), in the field
   __device__ __forceinline__ ZField(const void* f, int y, int x0, int c, int j)
-      : base((const char*)f + ((long long)y * N + x0) * BYTES), lane(((unsigned)j * (unsigned)(N * N) + c) * BYTES) {}
+      : base((const char*)f + ((long long)y * N + x0) * BYTES), lane(((unsigned)j * (unsigned)(N * N) + c) * BYTES),
+        first(((long long)j * N + y) * N + x0 + c) {}
+  // whether element (r, h) lies in the field (debug build)
+  __device__ __forceinline__ bool inside(int r, int h) const {
+    return in_bounds(first + (long long)r * ST * N * N + h * WP, (long long)N * N * N);
+  }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows(int r) const {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base) + (long long)r * ST * N * N * BYTES, 0,
                                              ((unsigned)(ST - 1) * (unsigned)(N * N) + 2 * WP) * BYTES, 0x00027000);
   }
   __device__ __forceinline__ unsigned off(bool skip) const { return skip ? 0x80000000u : lane; }
   __device__ __forceinline__ float load(int r, int h) const {
+    if (!inside(r, h)) return 0.f;
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows(r), lane, h * WP * BYTES, 0));
   }
   __device__ __forceinline__ void store(float v, int r, int h) const {
+    if (!inside(r, h)) return;
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rows(r), lane, h * WP * BYTES, 0);
   }
   __device__ __forceinline__ unsigned char load_byte(int r, int h) const {
+    if (!inside(r, h)) return 0;
     return __builtin_amdgcn_raw_buffer_load_b8(rows(r), lane, h * WP * BYTES, 0);
   }
   __device__ __forceinline__ long long load64(int r, int h, bool skip) const {
     typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 t = __builtin_amdgcn_raw_buffer_load_b64(rows(r), off(skip), h * WP * BYTES, 0);
+    const u2 t = __builtin_amdgcn_raw_buffer_load_b64(rows(r), off(skip || !inside(r, h)), h * WP * BYTES, 0);
     return (long long)(((unsigned long long)t[1] << 32) | t[0]);
   }
 };
@@ -1700,10 +1715,8 @@ __global__ void __launch_bounds__(ntz<N>(), N == 512 ? 4 : 1) k_z_final(const fl
       const ZField<N, 4> f(psi + (3 * b + k) * n3, y, x0, c, j);
 #pragma unroll
       for (int r = 0; r < Z::E; ++r) {
-        if (in_bounds(((long long)(j + r * Z::ST) * N + y) * N + x0 + c + WP, n3)) {
-          f.store(v[r].x, r, 0);
-          f.store(v[r].y, r, 1);
-        }
+        f.store(v[r].x, r, 0);
+        f.store(v[r].y, r, 1);
       }
     }
     if (KIND == ZF_PSI) continue;
@@ -2309,6 +2322,16 @@ struct Plane {
   __device__ __forceinline__ int row(int r) const { return j + r * (N / 8); }                // y of element r, y form
   __device__ __forceinline__ int at_y(int r) const { return row(r) * N + c; }                // element r, in the plane
   __device__ __forceinline__ int at_x(int r) const { return cx * N + jx + r * (N / 8); }
+  // element `at` of plane p of a spectrum (debug build: checked against the whole spectrum, not read outside it)
+  __device__ __forceinline__ static bool inside(int p, int at) {
+    return in_bounds((long long)p * N * N + at, (long long)(N / 2 + 1) * N * N);
+  }
+  __device__ __forceinline__ static float2 get(const float2* a, int p, int at) {
+    return inside(p, at) ? a[at] : make_float2(0.f, 0.f);
+  }
+  __device__ __forceinline__ static void set(float2* a, int p, int at, float2 v) {
+    if (inside(p, at)) a[at] = v;
+  }
   __device__ __forceinline__ void put_y(const float2* v, float2* b) const {                   // to a tile, by (y, x)
 #pragma unroll
     for (int r = 0; r < 8; ++r) b[LX::at(c, row(r))] = v[r];
@@ -2354,7 +2377,7 @@ struct Plane {
       if (on) {
         float2* a = g == 0 ? a0 : a1;
 #pragma unroll
-        for (int r = 0; r < 8; ++r) a[at_x(r)] = v[r];
+        for (int r = 0; r < 8; ++r) set(a, p, at_x(r), v[r]);
       }
       return;
     }
@@ -2375,19 +2398,19 @@ struct Plane {
         for (int r = 0; r < 8; ++r) {
           const float ry = los_comp(geo, 1, row(r));
           const float2 s = w[r] * rx, u = mid[r * NTF + t];
-          a0[at_y(r)] = make_float2(fmaf(ry, u.x, s.x), fmaf(ry, u.y, s.y));
+          set(a0, p, at_y(r), make_float2(fmaf(ry, u.x, s.x), fmaf(ry, u.y, s.y)));
         }
       }
     } else if (on) {
       float2* a = g == 0 ? a0 : a1;
 #pragma unroll
-      for (int r = 0; r < 8; ++r) a[at_y(r)] = w[r];
+      for (int r = 0; r < 8; ++r) set(a, p, at_y(r), w[r]);
     }
     fft_y<true>(v, g == 1);
     if (on && g == 1) {
       const float kz = geo.kf * deriv_mode<N>(p);
 #pragma unroll
-      for (int r = 0; r < 8; ++r) a2[at_y(r)] = mul_i(v[r]) * kz;
+      for (int r = 0; r < 8; ++r) set(a2, p, at_y(r), mul_i(v[r]) * kz);
     }
   }
 };
@@ -2413,7 +2436,7 @@ __global__ void __launch_bounds__((Plane<N, 1>::NT)) k_plane_smooth(float2* __re
   if (pl.on) {
 #pragma unroll
     for (int r = 0; r < 8; ++r)
-      v[r] = !in_flag || in_flag[pl.row(r) * NZT] ? arr[pl.at_y(r)] : make_float2(0.f, 0.f);
+      v[r] = !in_flag || in_flag[pl.row(r) * NZT] ? P::get(arr, p, pl.at_y(r)) : make_float2(0.f, 0.f);
   }
   stage_twiddles<N, P::NT>(tw, twg);
   pl.template fft_y<false>(v);
@@ -2434,7 +2457,7 @@ __global__ void __launch_bounds__((Plane<N, 1>::NT)) k_plane_smooth(float2* __re
   if (pl.on) {
 #pragma unroll
     for (int r = 0; r < 8; ++r)
-      if (!out_flag || out_flag[pl.row(r) * NZT]) arr[pl.at_y(r)] = v[r];
+      if (!out_flag || out_flag[pl.row(r) * NZT]) P::set(arr, p, pl.at_y(r), v[r]);
   }
 }
 
@@ -2458,7 +2481,7 @@ __global__ void __launch_bounds__((Plane<N, 2>::NT)) k_plane_start(float2* __res
   if (pl.on && pl.g == 0) {
 #pragma unroll
     for (int r = 0; r < 8; ++r)
-      v[r] = !in_flag || in_flag[pl.row(r) * NZT] ? a0[pl.at_y(r)] : make_float2(0.f, 0.f);
+      v[r] = !in_flag || in_flag[pl.row(r) * NZT] ? P::get(a0, p, pl.at_y(r)) : make_float2(0.f, 0.f);
   }
   stage_twiddles<N, P::NT>(tw, twg);
   pl.template fft_y<false>(v, pl.g == 0);
@@ -2467,7 +2490,7 @@ __global__ void __launch_bounds__((Plane<N, 2>::NT)) k_plane_start(float2* __res
   if (pl.on && pl.g == 0) {
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-      ds[pl.at_x(r)] = v[r];
+      P::set(ds, p, pl.at_x(r), v[r]);
       float k2, dx, dy, dz;
       int kzi;
       x_wavenumbers<N>((long long)p * N + pl.cx, pl.jx + r * (N / 8), g.kf, k2, dx, dy, dz, kzi);
@@ -2508,9 +2531,12 @@ __global__ void __launch_bounds__((Plane<N, 2>::NT)) k_plane_iter(float2* __rest
   if (pl.on) {
     const float2* a = pl.g == 0 ? a0 : a1;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) v[r] = a[pl.at_y(r)];
+    for (int r = 0; r < 8; ++r) v[r] = P::get(a, p, pl.at_y(r));
 #pragma unroll
-    for (int r = 0; r < 4; ++r) { dsv[r] = ds[pl.at_x(r0 + r)]; dp[r] = dprev[pl.at_x(r0 + r)]; }
+    for (int r = 0; r < 4; ++r) {
+      dsv[r] = P::get(ds, p, pl.at_x(r0 + r));
+      dp[r] = P::get(dprev, p, pl.at_x(r0 + r));
+    }
   }
   if (!active[b]) return;
   stage_twiddles<N, P::NT>(tw, twg);
@@ -2559,7 +2585,7 @@ __global__ void __launch_bounds__((Plane<N, 2>::NT)) k_plane_iter(float2* __rest
       const float2 div = mul_i(xa) * dx + ya;
       float2 dn = make_float2(fmaf(g.growth, div.x, dsv[r].x), fmaf(g.growth, div.y, dsv[r].y));
       if (omega != 1.f) dn = make_float2(fmaf(omega, dn.x - dp[r].x, dp[r].x), fmaf(omega, dn.y - dp[r].y, dp[r].y));
-      dnext[pl.at_x(r0 + r)] = dn;
+      P::set(dnext, p, pl.at_x(r0 + r), dn);
       float2 pot = make_float2(0.f, 0.f);
       if (k2 > 0.f) {
         const float wgt = (kzi == 0 || kzi == N / 2) ? 1.f : 2.f;
