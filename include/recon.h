@@ -199,7 +199,7 @@ int recon_tile_counts(recon_plan_t* plan, int64_t* out);
  * shift then runs on the deposit's brick-ordered copy of the positions and puts the results back in
  * input order, bit-identical to the direct shift; EINVAL when which, pos, n or offsets differ from
  * that paint's.  Without the flag the positions are read from pos.  Objects the deposit rejected get
- * a zero displacement. */
+ * a zero displacement, and their own position in pos_out. */
 int recon_shift(recon_plan_t* plan, int which, const float* pos, int64_t n, const int64_t* offsets,
                 float* disp_out, float* pos_out);
 

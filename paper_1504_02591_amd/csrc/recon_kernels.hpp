@@ -2741,6 +2741,11 @@ __global__ void __launch_bounds__(256) k_shift(const float* __restrict__ pos, lo
     if (!shift_coords(px, py, pz, cg, uu)) {
 #pragma unroll
       for (int a = 0; a < 3; ++a) disp[3 * i + a] = 0.f;
+      if (pos_out) {                                         // where it was, as k_shift_unpermute leaves it
+        pos_out[3 * i] = __fadd_rn(px, 0.f);
+        pos_out[3 * i + 1] = __fadd_rn(py, 0.f);
+        pos_out[3 * i + 2] = __fadd_rn(pz, 0.f);
+      }
       continue;
     }
     const int b = off ? find_realisation(off, batch, i) : 0;
