@@ -863,11 +863,23 @@ int launch_fill_u64(recon_plan_t* pl, void* p, long long count, int* zero_too) {
   return check_launch(pl, "fill");
 }
 
-// Blocks per brick of the launches that walk a brick's objects: small grids have too few bricks to fill the
-// chip (8 at 32^3, 64 at 64^3), so theirs are split (brick_part; at most 16 parts).
-unsigned brick_parts(long long nbins) {
-  const long long p = 4096 / nbins;
-  return (unsigned)(p < 1 ? 1 : (p > 16 ? 16 : p));
+// Blocks per brick of the launches that walk a brick's objects, and objects per block (brick_part): small
+// grids have too few bricks to fill the chip (8 at 32^3, 64 at 64^3), so theirs are split (at most 16 parts).
+// A part pays for the brick's footprint (17^3 atomics in a deposit, 59 KB of loads in a shift), so the
+// more bricks fill the chip already, the more objects a part has to have: `unit` per brick, up to 256 units.
+// us with 1,024 objects a part at every size / with 64 a brick in the deposit and 128 in the shift (in one
+// block per brick): deposit of 3e6 objects at 128^3 171 / 93 (93), 64^3 97 / 88 (125), 16 x 64^3 162 / 100
+// (100), 32^3 83 / 83 (611); shift of 1e7 at 128^3 215 / 180 (179), 64^3 166 / 165 (289).  A clump of 3e6 in
+// a few bricks of 128^3 980 / 980 (4593).
+struct BrickParts {
+  unsigned count, least;
+};
+BrickParts brick_parts(long long nbins, long long n, long long unit) {
+  BrickParts p;
+  p.least = (unsigned)std::max<long long>(1024, unit * std::min<long long>(nbins, 256));
+  const long long most = std::min<long long>({16, 4096 / nbins, (n + p.least - 1) / p.least});
+  p.count = (unsigned)std::max<long long>(1, most);
+  return p;
 }
 
 template <int BINS>
@@ -1365,13 +1377,14 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
     if (prep >= 0) sparse = true;
     {
       PROF(pl, KP_PAINT);
-      const dim3 blocks((unsigned)nb, brick_parts(nb));
+      const BrickParts parts = brick_parts(nb, n, 64);
+      const dim3 blocks((unsigned)nb, parts.count);
       if (ngp)
         k_brick_deposit<RECON_BRICK_NT, true><<<blocks, RECON_BRICK_NT, 0, pl->stream>>>(
-            pl->sorted, pl->bstart, pl->cic, (unsigned long long*)grid);
+            pl->sorted, pl->bstart, pl->cic, (unsigned long long*)grid, parts.least);
       else
         k_brick_deposit<RECON_BRICK_NT, false><<<blocks, RECON_BRICK_NT, 0, pl->stream>>>(
-            pl->sorted, pl->bstart, pl->cic, (unsigned long long*)grid);
+            pl->sorted, pl->bstart, pl->cic, (unsigned long long*)grid, parts.least);
     }
     RECON_TRY(check_launch(pl, "brick deposit"));
     if (!ngp) {
@@ -1927,9 +1940,10 @@ int recon_shift(recon_plan_t* pl, int which_flags, const float* pos, int64_t n, 
     // shift the brick-ordered copy, then reorder
     {
       PROF(pl, KP_SHIFT);
-      k_shift_brick<512><<<dim3((unsigned)pl->L.nbins, brick_parts(pl->L.nbins)), 512, 0, pl->stream>>>(
+      const BrickParts parts = brick_parts(pl->L.nbins, n, 128);
+      k_shift_brick<512><<<dim3((unsigned)pl->L.nbins, parts.count), 512, 0, pl->stream>>>(
           pl->sorted, pl->bstart, pl->psi, pl->cic, (float)pl->p.observer[0], (float)pl->p.observer[1],
-          (float)pl->p.observer[2], (float)pl->p.growth, which == RECON_GAL ? 1 : 0, pl->stmp);
+          (float)pl->p.observer[2], (float)pl->p.growth, which == RECON_GAL ? 1 : 0, pl->stmp, parts.least);
       // one trip per block: per XCD, ceil(chunks / 8) chunks of 256 objects in groups of kObjBatch
       const long long chunks = (n + kThreads - 1) / kThreads;
       const long long ub = 8 * (((chunks + 7) / 8 + kObjBatch - 1) / kObjBatch);

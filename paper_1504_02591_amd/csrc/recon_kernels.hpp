@@ -504,13 +504,12 @@ __device__ __forceinline__ void scan_run(const unsigned* __restrict__ in, long l
 }
 
 // Part blockIdx.y of a brick's objects [lo, hi): the launch has gridDim.y blocks per brick, of which a
-// brick uses as many as leave each at least kPartObjects objects.  False for a block with no part.
-constexpr unsigned kPartObjects = 1024;
-__device__ __forceinline__ bool brick_part(unsigned& lo, unsigned& hi) {
+// brick uses one per `least` objects it holds.  False for a block with no part.
+__device__ __forceinline__ bool brick_part(unsigned& lo, unsigned& hi, unsigned least) {
   const unsigned cnt = hi - lo;
   if (cnt == 0) return false;
   if (gridDim.y > 1) {
-    unsigned parts = (cnt + kPartObjects - 1) / kPartObjects;
+    unsigned parts = (cnt - 1) / least + 1;
     if (parts > gridDim.y) parts = gridDim.y;
     if (blockIdx.y >= parts) return false;
     const unsigned first = lo;
@@ -527,12 +526,12 @@ __device__ __forceinline__ bool brick_part(unsigned& lo, unsigned& hi) {
 template <int NT, bool NGP>
 __global__ void __launch_bounds__(NT) k_brick_deposit(const float4* __restrict__ sorted,
                                                       const unsigned* __restrict__ start, CicGeo g,
-                                                      unsigned long long* __restrict__ grid) {
+                                                      unsigned long long* __restrict__ grid, unsigned least) {
   constexpr int T = kBrick + 1;
   __shared__ unsigned long long acc[T * T * T];
   const long long key = brick_of_block();
   unsigned lo = start[key], hi = start[key + 1];
-  if (!brick_part(lo, hi)) return;
+  if (!brick_part(lo, hi, least)) return;
   const int nbs = (g.n + kBrick - 1) / kBrick;
   const long long per = (long long)nbs * nbs * nbs;
   const int b = (int)(key / per);
@@ -2771,12 +2770,12 @@ __global__ void __launch_bounds__(NT) k_shift_brick(const float4* __restrict__ s
                                                     const unsigned* __restrict__ start,
                                                     const float* __restrict__ psi, CicGeo cg, float ox, float oy,
                                                     float oz, float growth, int galaxies,
-                                                    float4* __restrict__ tmp) {
+                                                    float4* __restrict__ tmp, unsigned least) {
   constexpr int F = kBrick + 1, F3 = F * F * F;
   __shared__ float px_[F3], py_[F3], pz_[F3];
   const long long key = brick_of_block();
   unsigned lo = start[key], hi = start[key + 1];
-  if (!brick_part(lo, hi)) return;
+  if (!brick_part(lo, hi, least)) return;
   const int n = cg.n, m = n - 1;
   const int nbs = (n + kBrick - 1) / kBrick;
   const long long per = (long long)nbs * nbs * nbs;
