@@ -101,9 +101,10 @@ extern "C" {
 #define RECON_PAINT_ACCUMULATE 1u  /* add to the grid instead of replacing it */
 #define RECON_PAINT_NGP 2u         /* nearest-grid-point deposit (the paper's binning, Sec. 3.1): the whole
                                       quantised weight on the nearest node (node i + 1 when the FP32
-                                      fraction is >= 1/2); through the bricks from 128^3 on where no
-                                      RECON_SHIFT_AS_PAINTED copy would be lost, else per-object
-                                      atomics (the same grid); the shift stays CIC                   */
+                                      fraction is >= 1/2); through the bricks in a plan with randoms
+                                      from 128^3 on where no RECON_SHIFT_AS_PAINTED copy would be
+                                      lost, else per-object atomics (the same grid); the shift stays
+                                      CIC                                                            */
 
 typedef struct recon_plan_s recon_plan_t;
 
