@@ -139,7 +139,7 @@ Layout make_layout(const recon_params_t* p) {
   L.tpart = take((size_t)b * max_partial_blocks((int)n) * 3 * 8);
   L.dscal = take(b * sizeof(DeltaScal));
   L.act = take(b * 4 * 4);
-  L.err = take(16);
+  L.err = take(32);
   // tile flags of the setup transforms (one byte per z tile; n^2 bytes bound the tile count)
   L.zflag = take((size_t)(randoms ? 2 : 1) * b * n * n);
   L.mflag = randoms ? take((size_t)b * n * n) : 0;
@@ -333,6 +333,10 @@ struct recon_plan_s {
   Geo geo{};
   CicGeo cic{};
   bool painted_g = false, painted_r = false;
+  // objects of a grid's last deposit if that was a nearest-grid-point one through the bricks, and whether it
+  // found them in no spatial order (known from the solve on)
+  long long ngp_n[2] = {0, 0};
+  bool scattered[2] = {false, false};
   int state = ST_EMPTY;
   int start = RECON_START_PLAIN;
   // start of each realisation (a learned start that is rejected restarts from the plain start) and
@@ -344,7 +348,7 @@ struct recon_plan_s {
   std::vector<int> h_fan, h_fin, h_it;
   std::vector<int> up_fan, up_fin, up_it;     // what the device masks hold (empty: not yet uploaded)
   // what the host reads: sums of the pass [2 B] and of a non-gradient start [2 B], the cross sums [2 B],
-  // invalid-object counts [2] and status [B]
+  // invalid-object counts [2], catalogue orders [2] and status [B]
   PinnedDoubles host;
   double *h_red = nullptr, *h_red2 = nullptr, *h_stat = nullptr;
   double *hd_red = nullptr, *hd_red2 = nullptr, *hd_stat = nullptr;   // as kernels address them, or null
@@ -884,9 +888,9 @@ BrickParts brick_parts(long long nbins, long long n, long long unit) {
 
 template <int BINS>
 void launch_bin_count(recon_plan_t* pl, const BinShape& b, const float* pos, const float* w, long long n,
-                      const long long* off) {
-  k_bin_count_lds<1024, BINS><<<(unsigned)b.blocks, 1024, 0, pl->stream>>>(pos, w, n, b.chunk, off, pl->batch, pl->cic,
-                                                                          pl->bcount, pl->errblk, pl->bhist);
+                      const long long* off, int* ordblk) {
+  k_bin_count_lds<1024, BINS><<<(unsigned)b.blocks, 1024, 0, pl->stream>>>(
+      pos, w, n, b.chunk, off, pl->batch, pl->cic, pl->bcount, pl->errblk, pl->bhist, ordblk);
 }
 template <int BINS>
 void launch_bin_scatter(recon_plan_t* pl, const BinShape& b, const float* pos, const float* w, long long n,
@@ -899,16 +903,17 @@ void launch_bin_scatter(recon_plan_t* pl, const BinShape& b, const float* pos, c
 // Objects into brick order (pl->sorted, pl->slot_of, pl->bstart).  The brick counts are zero before and
 // after (cleared at the plan's creation and by every scatter).  prep >= 0: the bricks of `grid` are
 // prepared for a deposit in that mode (k_brick_prepare).  Invalid objects are counted into *errc (replacing
-// it when fresh, else added).
+// it when fresh, else added); order, when not null, receives whether the catalogue is in spatial order.
 int bin_objects(recon_plan_t* pl, const float* pos, const float* w, long long n, const long long* off, int prep,
-                unsigned char* valid, unsigned long long* grid, int* errc, bool fresh) {
+                unsigned char* valid, unsigned long long* grid, int* errc, bool fresh, int* order = nullptr) {
   const long long nb = pl->L.nbins;
   const BinShape bs = bin_shape(nb, n);
+  int* ordblk = order ? pl->errblk + bs.blocks : nullptr;   // (16 bytes per object hold both)
   {
     PROF(pl, KP_BIN);
-    if (bs.bins == kBinsS) launch_bin_count<kBinsS>(pl, bs, pos, w, n, off);
-    else if (bs.bins == kBinsM) launch_bin_count<kBinsM>(pl, bs, pos, w, n, off);
-    else launch_bin_count<kLdsBins>(pl, bs, pos, w, n, off);
+    if (bs.bins == kBinsS) launch_bin_count<kBinsS>(pl, bs, pos, w, n, off, ordblk);
+    else if (bs.bins == kBinsM) launch_bin_count<kBinsM>(pl, bs, pos, w, n, off, ordblk);
+    else launch_bin_count<kLdsBins>(pl, bs, pos, w, n, off, ordblk);
   }
   RECON_TRY(check_launch(pl, "bin count"));
   {
@@ -921,7 +926,7 @@ int bin_objects(recon_plan_t* pl, const float* pos, const float* w, long long n,
     const long long blocks = pl->L.nscan + (prep >= 0 ? nb : 0);
     k_scan_prepare<<<(unsigned)blocks, 256, 0, pl->stream>>>(pl->bcount, nb, bsum, (int)pl->L.nscan, pl->bstart,
                                                              pl->bcursor, pl->n, prep, valid, grid, pl->errblk,
-                                                             (int)bs.blocks, errc, fresh ? 1 : 0);
+                                                             (int)bs.blocks, errc, fresh ? 1 : 0, ordblk, order);
   }
   RECON_TRY(check_launch(pl, "bin scan"));
   {
@@ -1201,7 +1206,7 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
   pl->h_it.assign(pl->batch, 0);
   const size_t parts = (size_t)pl->batch * (n / 2 + 1);
   const bool host_parts = ops_for(n) && ops_for(n)->plane && parts <= kHostParts;
-  if (!pl->host.assign(7 * (size_t)pl->batch + 2 + (host_parts ? 2 * parts : 0), 0.0, pinned) ||
+  if (!pl->host.assign(7 * (size_t)pl->batch + 4 + (host_parts ? 2 * parts : 0), 0.0, pinned) ||
       (pinned && hipEventCreateWithFlags(&pl->ev, hipEventDisableTiming) != hipSuccess)) {
     delete pl;
     return RECON_EDEVICE;
@@ -1214,7 +1219,7 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
     pl->hd_red2 = pl->hd_red + 4 * pl->batch;
     pl->hd_stat = pl->hd_red2 + 2 * pl->batch;
     if (host_parts) {
-      const size_t at = 7 * (size_t)pl->batch + 2;
+      const size_t at = 7 * (size_t)pl->batch + 4;
       pl->h_part = pl->host.p + at;
       pl->hd_part = pl->host.dev + at;
     }
@@ -1332,6 +1337,8 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
   long long* grid = which == RECON_GAL ? pl->grid_g : pl->grid_r;
   const bool first = which == RECON_GAL ? !pl->painted_g : !pl->painted_r;
   int* errc = pl->err + which;   // invalid-object counter of this grid
+  pl->ngp_n[which] = 0;
+  pl->scattered[which] = false;
   const bool fresh = !(flags & RECON_PAINT_ACCUMULATE) || first;
   // brick-sparse grid: bricks tile the grid and the brick buffers exist
   const bool can_sparse = pl->L.nbins > 0 && pl->n >= 2 * kBrick;
@@ -1377,7 +1384,9 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
     pl->srt_which = -1;   // the sorted copy is being replaced
     const long long nb = pl->L.nbins;
     const int prep = can_sparse && (fresh || sparse) ? (fresh ? 0 : 1) : -1;
-    RECON_TRY(bin_objects(pl, pos, w, n, (const long long*)offsets, prep, valid, (unsigned long long*)grid, errc, fresh));
+    RECON_TRY(bin_objects(pl, pos, w, n, (const long long*)offsets, prep, valid, (unsigned long long*)grid, errc, fresh,
+                          ngp ? pl->err + kOrderAt + which : nullptr));
+    if (ngp) pl->ngp_n[which] = n;
     if (prep >= 0) sparse = true;
     {
       PROF(pl, KP_PAINT);
@@ -1444,17 +1453,20 @@ int recon_solve(recon_plan_t* pl, int start, const void* net) {
     // one read-back: invalid-object counters and the totals status of every realisation, once the whole
     // setup is done (the call is a synchronisation point: it leaves nothing of the setup queued).
     std::vector<int> st(pl->batch, 0);
-    int errs[2] = {0, 0};
+    int errs[kOrderAt + 2] = {};
     if (!pl->hd_stat) {
-      HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, 2 * sizeof(int), hipMemcpyDeviceToHost, pl->stream));
+      HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, sizeof errs, hipMemcpyDeviceToHost, pl->stream));
       HIP_TRY(pl, hipMemcpyAsync(st.data(), pl->status, sizeof(int) * pl->batch, hipMemcpyDeviceToHost, pl->stream));
     }
     HIP_TRY(pl, hipStreamSynchronize(pl->stream));
     if (pl->hd_stat) {
-      errs[0] = (int)pl->h_stat[0];
-      errs[1] = (int)pl->h_stat[1];
-      for (int b = 0; b < pl->batch; ++b) st[b] = (int)pl->h_stat[2 + b];
+      for (int k = 0; k < 2; ++k) {
+        errs[k] = (int)pl->h_stat[k];
+        errs[kOrderAt + k] = (int)pl->h_stat[2 + k];
+      }
+      for (int b = 0; b < pl->batch; ++b) st[b] = (int)pl->h_stat[4 + b];
     }
+    for (int k = 0; k < 2; ++k) pl->scattered[k] = pl->ngp_n[k] > 0 && errs[kOrderAt + k] == 0;
     const int errcount = errs[0] + (pl->randoms ? errs[1] : 0);
     if (errcount) return fail(pl, RECON_EINVAL, std::to_string(errcount) + " objects had invalid positions or weights");
     for (int b = 0; b < pl->batch; ++b) {
@@ -1933,10 +1945,15 @@ int recon_shift(recon_plan_t* pl, int which_flags, const float* pos, int64_t n, 
   if (blocks > 8192) blocks = 8192;
   // A catalogue that is not in brick order is put there first where that is cheaper than gathering the
   // displacement object by object: the displacement is larger than the L2s (from 256^3 on), there are
-  // objects enough per brick (staging a brick's footprint costs about as much as 20 objects' gathers), and
-  // the brick-ordered copy of a deposit is not in the way.
+  // objects enough per brick (staging its footprint costs about as much as 70 objects' gathers), the
+  // brick-ordered copy of a deposit is not in the way, and the catalogue is known to be in no spatial order:
+  // its nearest-grid-point deposit through the bricks has found that.  (A catalogue that was not deposited so, or
+  // is of another length than what was, goes object by object, as one in spatial order does.)  us, object by
+  // object / binned: random order at 256^3 300,000 objects 90 / 84, 393,216 119 / 86, 4.3e6 1289 / 268, 1.7e7
+  // 4965 / 751; at 512^3 1.1e6 329 / 694, 2e6 575 / 735, 3.1e6 916 / 783, 3e7 8682 / 2231; sorted along z at 256^3
+  // 4.3e6 522 / 203; in spatial order 4.3e6 77 / 177 (lattice) and 367 / 2210 (a clump of 13 cells).
   const bool bin_first = !as_painted && pl->srt_which < 0 && n <= pl->p.max_objects && pl->n >= 256 &&
-                         n >= 32 * pl->L.nbins && n >= (1 << 18);
+                         n >= 96 * pl->L.nbins && pl->scattered[which] && n == pl->ngp_n[which];
   if (bin_first) {
     RECON_TRY(bin_objects(pl, pos, nullptr, n, (const long long*)offsets, -1, nullptr, nullptr, pl->err + 2, true));
   }

@@ -308,7 +308,8 @@ __device__ __forceinline__ void load_objects(const float* __restrict__ pos, cons
 // Count with a per-block LDS histogram over the bins of the realisation that owns the
 // chunk's first object; one global atomic per (block, non-empty bin).  Objects whose bin
 // lies outside that window (a chunk crossing realisations) use a direct global atomic.
-// The invalid objects of the block go to errblk[block], which the scan adds up.
+// The invalid objects of the block go to errblk[block], which the scan adds up; with ordblk (not null),
+// ordblk[block] says whether the catalogue is in spatial order (count_near: a quarter of the neighbours or more).
 // The block's histogram is also stored in bhist[block][bin], so that the scatter,
 // which splits the catalogue into the same chunks, need not count again.
 // First brick key of the LDS window of the binning block that takes objects [lo, ...): the block's
@@ -333,17 +334,46 @@ __device__ __forceinline__ long long bin_window(const float* __restrict__ pos, l
   return base;
 }
 
+// How many neighbours in a catalogue lie in the same or in touching bricks, from the block's first NT objects
+// (votes[1] of votes[0]; LDS, zero before; every thread of the block takes part).  Nearly all do where the
+// catalogue is stored in spatial order (a lattice plane by plane) or fills a few bricks only, 1 in 28 where it is
+// sorted along one axis of 256^3, 1 in 150 in random order there.
+template <int NT>
+__device__ __forceinline__ void count_near(const float* __restrict__ pos, long long lo, long long hi, const CicGeo& g,
+                                           unsigned* votes) {
+  const long long i = lo + threadIdx.x;
+  int ii[3] = {0, 0, 0};
+  unsigned long long tau[3];
+  const bool ok = i < hi && cic_locate(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], 1.0f, g, ii, tau);
+  bool pair = (threadIdx.x & 63) && ok, near = true;
+  pair = __shfl_up((int)ok, 1, 64) && pair;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int k = ii[a] / kBrick, d = k - __shfl_up(k, 1, 64);
+    near = near && d >= -1 && d <= 1;
+  }
+  const int n0 = __popcll(__ballot(pair)), n1 = __popcll(__ballot(pair && near));
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(votes, (unsigned)n0);
+    atomicAdd(votes + 1, (unsigned)n1);
+  }
+}
+
 template <int NT, int kBins>
 __global__ void __launch_bounds__(NT) k_bin_count_lds(const float* __restrict__ pos, const float* __restrict__ w,
                                                        long long n, long long chunk,
                                                        const long long* __restrict__ off, int batch, CicGeo g,
                                                        unsigned* __restrict__ counts, int* __restrict__ errblk,
-                                                       unsigned* __restrict__ bhist) {
+                                                       unsigned* __restrict__ bhist, int* __restrict__ ordblk) {
   __shared__ unsigned hist[kBins];
   __shared__ int bad;
+  __shared__ unsigned votes[2];
   const long long lo = blockIdx.x * chunk;
   if (lo >= n) {                                         // (whole block)
-    if (threadIdx.x == 0) errblk[blockIdx.x] = 0;
+    if (threadIdx.x == 0) {
+      errblk[blockIdx.x] = 0;
+      if (ordblk) ordblk[blockIdx.x] = 0;
+    }
     return;
   }
   const long long hi = lo + chunk < n ? lo + chunk : n;
@@ -352,7 +382,9 @@ __global__ void __launch_bounds__(NT) k_bin_count_lds(const float* __restrict__ 
   const long long base = bin_window<kBins>(pos, lo, off, batch, g);
   for (int i = threadIdx.x; i < kBins; i += NT) hist[i] = 0u;
   if (threadIdx.x == 0) bad = 0;
+  if (threadIdx.x < 2) votes[threadIdx.x] = 0u;
   __syncthreads();
+  if (ordblk) count_near<NT>(pos, lo, hi, g, votes);
   constexpr int U = kObjBatch;
   for (long long i0 = lo + threadIdx.x; i0 < hi; i0 += (long long)NT * U) {
     float px[U], py[U], pz[U], wv[U];
@@ -375,7 +407,10 @@ __global__ void __launch_bounds__(NT) k_bin_count_lds(const float* __restrict__ 
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) errblk[blockIdx.x] = bad;
+  if (threadIdx.x == 0) {
+    errblk[blockIdx.x] = bad;
+    if (ordblk) ordblk[blockIdx.x] = 4 * votes[1] > votes[0] ? 1 : 0;
+  }
   const long long nb_total = per * batch;
   for (int i = threadIdx.x; i < kBins; i += NT) {
     const unsigned c = hist[i];
@@ -641,17 +676,26 @@ __global__ void __launch_bounds__(256) k_scan_prepare(const unsigned* __restrict
                                                       int mode, unsigned char* __restrict__ valid,
                                                       unsigned long long* __restrict__ grid,
                                                       const int* __restrict__ errblk, int nerr, int* __restrict__ err,
-                                                      int fresh) {
+                                                      int fresh, const int* __restrict__ ordblk,
+                                                      int* __restrict__ order) {
   if (blockIdx.x == 0) {
-    // invalid objects of this deposit: replace the grid's count (new grid) or add to it
-    __shared__ int bad;
-    if (threadIdx.x == 0) bad = 0;
+    // invalid objects of this deposit: replace the grid's count (new grid) or add to it; and whether most of
+    // the binning blocks found the catalogue in spatial order
+    __shared__ int bad, inorder;
+    if (threadIdx.x == 0) bad = inorder = 0;
     __syncthreads();
-    int mine = 0;
-    for (int i = threadIdx.x; i < nerr; i += 256) mine += errblk[i];
+    int mine = 0, ord = 0;
+    for (int i = threadIdx.x; i < nerr; i += 256) {
+      mine += errblk[i];
+      if (ordblk) ord += ordblk[i];
+    }
     if (mine) atomicAdd(&bad, mine);
+    if (ord) atomicAdd(&inorder, ord);
     __syncthreads();
-    if (threadIdx.x == 0) *err = (fresh ? 0 : *err) + bad;
+    if (threadIdx.x == 0) {
+      *err = (fresh ? 0 : *err) + bad;
+      if (ordblk) *order = 2 * inorder > nerr ? 1 : 0;
+    }
   }
   if ((int)blockIdx.x < runs) scan_run(count, nbins, bsum, blockIdx.x, out, cursor);
   else brick_prepare(count, n, mode, (long long)blockIdx.x - runs, valid, grid);
@@ -809,10 +853,12 @@ __global__ void __launch_bounds__(256) k_mask_brick(const long long* __restrict_
   if (fl && (w4.x | w4.y | w4.z | w4.w)) *fl = 1;      // every writer stores the same value
 }
 
+constexpr int kOrderAt = 4;
 // Per-realisation scalars from the exact totals {W_g, W_r, n_occ}:
 //   alpha = W_g / W_r, 1/rho_bar = N^3 / (W_g 2^-32), mask threshold floor(tau 27 W_r / n_occ);
-// status[b] bit 0: galaxy total is zero, bit 1: random total is zero.  host (pinned host memory, or null):
-// the two invalid-object counts, then the status of every realisation.
+// status[b] bit 0: galaxy total is zero, bit 1: random total is zero.  err: invalid objects of the two grids
+// and, from err[kOrderAt], whether their last deposits were in spatial order.  host (pinned host memory, or
+// null): these four, then the status of every realisation.
 // One block per realisation: sums the per-tile integer partials (exact, any order), then derives
 // the scalars; tot[b] keeps the totals.
 __global__ void __launch_bounds__(256) k_scalars(const unsigned long long* __restrict__ tpart, int nblk, long long n3,
@@ -861,8 +907,13 @@ __global__ void __launch_bounds__(256) k_scalars(const unsigned long long* __res
     thr[b] = th;
     status[b] = st;
     if (host) {
-      host[2 + b] = (double)st;
-      if (b == 0) { host[0] = (double)err[0]; host[1] = (double)err[1]; }
+      host[4 + b] = (double)st;
+      if (b == 0) {
+        host[0] = (double)err[0];
+        host[1] = (double)err[1];
+        host[2] = (double)err[kOrderAt];
+        host[3] = (double)err[kOrderAt + 1];
+      }
     }
   }
 }
