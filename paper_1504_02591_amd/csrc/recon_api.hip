@@ -1539,10 +1539,15 @@ double plain_eps1_bound(double beta, double num0, double den0, double s2) {
 }
 
 // eps that realisation b's next pass is likely to give: the last one times the last ratio (after one pass,
-// times the contraction of the pass; before any, unknown).
+// times the contraction of the pass).  Before the plain start's first pass, what it can give at most: the pass
+// adds w f div[...], of norm at most w beta ||Psi_0||, so eps_1 <= w beta / (1 - w beta) (without growth, or with
+// a tolerance above that, the first pass is the last).  Any other start goes on after its first pass.
 double expect_eps(const recon_plan_t* pl, int b, double beta) {
   const std::vector<double>& h = pl->hist[b];
-  if (h.empty()) return INFINITY;
+  if (h.empty()) {
+    const double most = (pl->p.flags & RECON_RELAXED) ? 2.0 * beta / (2.0 + beta) : beta;
+    return pl->start_b[b] == RECON_START_PLAIN && most < 1.0 ? most / (1.0 - most) : INFINITY;
+  }
   const double rate = h.size() > 1 ? h[h.size() - 1] / h[h.size() - 2]
                                    : ((pl->p.flags & RECON_RELAXED) ? beta / (2.0 + beta) : beta);
   return h.back() * rate;
