@@ -47,7 +47,7 @@ struct Layout {
   size_t a1 = 0, a2 = 0, d1 = 0, d2 = 0, ybuf = 0, dybuf = 0, upbuf = 0,
          part_out = 0, part_w1 = 0, part_w2 = 0, gred = 0, grad = 0, lossp = 0, losst = 0, dc = 0, uc = 0,
          wf1 = 0, wf2 = 0, wf2t = 0, dh = 0, uh = 0;
-  long long t_out = 0, t_w = 0, nb_out = 0, nb_w = 0, nslice = 0, nb_loss = 0;   // backward tiles and blocks
+  long long t_out = 0, t_w = 0, nb_w = 0, nslice = 0, nb_loss = 0;   // backward tiles and blocks
   long long cnn_n = 0;
   long long nbins = 0, nscan = 0;
 };
@@ -165,10 +165,8 @@ Layout make_layout(const recon_params_t* p) {
     L.cnn_n = m;
     L.t_out = b * m3 / (FX * FY * FZ);
     L.t_w = b * m3 / VCELLS;
-    L.nb_out = L.t_out < kBwdBlocks ? L.t_out : kBwdBlocks;
-    const long long rows = b * (m / VY) * (m / 4);   // 256 rows at 64^3, 1024 at 128^3: the partial rows are 42 KB each
-    L.nb_w = std::min<long long>(std::min<long long>(L.t_w, rows), kBwdBlocks);
-    L.nslice = std::max<long long>(1, std::min<long long>(kRedSlices, std::max(L.nb_out, L.nb_w) / 64));
+    L.nb_w = wgrad_rows(m, b);
+    L.nslice = std::max<long long>(1, std::min<long long>(kRedSlices, std::max(L.t_out, L.nb_w) / 64));
     L.nb_loss = 1024;
     L.a1 = take(b * m3 * CH * 2);
     L.a2 = take(b * m3 * CH * 2);
@@ -192,7 +190,7 @@ Layout make_layout(const recon_params_t* p) {
     L.wf1 = take(9 * 64 * 16);
     L.wf2 = take(9 * 2 * 64 * 16);
     L.wf2t = take(9 * 2 * 64 * 16);
-    L.part_out = take((size_t)L.nb_out * COL3 * 4);
+    L.part_out = take((size_t)L.t_out * COL3 * 4);
     L.part_w1 = take((size_t)L.nb_w * COL1 * 4);
     L.part_w2 = take((size_t)L.nb_w * COL2 * 4);
     L.gred = take((size_t)L.nslice * NCOLS * 8);
@@ -2103,16 +2101,17 @@ int recon_cnn_train_step(recon_plan_t* pl, float* params, float* adam_m, float* 
   const long long count = pl->cnn_n3 * pl->batch;
   RECON_TRY(cnn_forward_impl(pl, params, delta, u_p, pl->ybuf, 1.0f));
   const dim3 gridf((unsigned)(pl->cnn_n3 / (FX * FY * FZ)), pl->batch);
-  const unsigned nbo = (unsigned)pl->L.nb_out, nbw = (unsigned)pl->L.nb_w;
+  const unsigned nbo = (unsigned)pl->L.t_out, nbw = (unsigned)pl->L.nb_w;
   const Geo3 g = cnn_geo(pl);
   hipStream_t s = pl->stream;
   {
     PROF(pl, KP_CNN_BWD);
     k_loss<<<(unsigned)pl->L.nb_loss, 256, 0, s>>>(pl->ybuf, target_du, count, pl->dybuf, pl->lossp);
-    k_conv_out_bwd<<<nbo, 256, 0, s>>>(pl->dybuf, pl->a2, g, (int)pl->L.t_out, params + OFF_W3, pl->d2, pl->part_out);
-    k_wgrad<CH, K2, 0><<<nbw, 256, 0, s>>>(pl->d2, pl->a1, nullptr, nullptr, g, (int)pl->L.t_w, pl->part_w2);
+    k_conv_out_bwd<<<nbo, 256, 0, s>>>(pl->dybuf, pl->a2, g, params + OFF_W3, pl->d2, pl->part_out);
+    const bool halves = pl->cnn_n == 16;
+    (halves ? k_wgrad<CH, K2, 0, true> : k_wgrad<CH, K2, 0, false>)<<<nbw, 256, 0, s>>>(pl->d2, pl->a1, nullptr, nullptr, g, (int)pl->L.t_w, pl->part_w2);
     k_conv_fwd<CH, 0, 1><<<gridf, 256, 0, s>>>(pl->d2, nullptr, nullptr, g, pl->wf2t, nullptr, pl->d1, pl->a1);
-    k_wgrad<CIN, K1P, 1><<<nbw, 256, 0, s>>>(pl->d1, nullptr, delta, u_p, g, (int)pl->L.t_w, pl->part_w1);
+    (halves ? k_wgrad<CIN, K1P, 1, true> : k_wgrad<CIN, K1P, 1, false>)<<<nbw, 256, 0, s>>>(pl->d1, nullptr, delta, u_p, g, (int)pl->L.t_w, pl->part_w1);
     k_reduce_parts<<<dim3(RB3 + RB2 + RB1 + 1, (unsigned)pl->L.nslice), 256, 0, s>>>(
         pl->part_out, nbo, pl->part_w2, pl->part_w1, nbw, pl->gred, pl->lossp, (int)pl->L.nb_loss, pl->losst);
     float* grad = grad_out ? grad_out : pl->gradbuf;

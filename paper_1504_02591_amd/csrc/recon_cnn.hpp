@@ -332,15 +332,14 @@ __global__ void __launch_bounds__(256) k_loss(const float* __restrict__ y, const
 }
 
 // ---------------------------------------------------------------------------
-// Backward of the training step.  Every kernel takes several tiles per block in a fixed order and leaves
-// one row of partial sums per block; k_reduce_parts adds the rows in FP64 in a fixed order, so a step
-// is deterministic for a given grid and batch.
+// Backward of the training step.  Every block takes its tiles in a fixed order and leaves one row of partial
+// sums; k_reduce_parts adds the rows in FP64 in a fixed order, so a step is deterministic for a given grid and
+// batch.  What is added up in FP32 does not grow with the batch: 256 positions in the output layer's backward
+// (wgrad_rows for the other two).
 // ---------------------------------------------------------------------------
 // 16 bytes as a vector: arrays of the struct uint4 held across a barrier are put in scratch memory (the weight
 // gradients took 120 and 52 us with it, 58 and 35 us as below).
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
-
-constexpr int kBwdBlocks = 1024;   // most blocks (rows of partial sums) of a backward launch
 
 // Output-layer backward: d2[p][i] = bf16((sum_t W3[t][i] dy[p - d_t]) * [a2[p][i] > 0]),
 // and per-block partials of dW3[t][i] = sum_p dy[p - d_t] a2[p][i] (the same sum as over dy[p] a2[p + d_t]:
@@ -349,16 +348,17 @@ constexpr int kBwdBlocks = 1024;   // most blocks (rows of partial sums) of a ba
 // Both sums are contractions with FP32 operands (dy is never rounded) on v_mfma_f32_16x16x4_f32, tile
 // 16 x 8 x 8 cells, four waves of 16 rows: d2 with M = 16 cells of a row, N = 16 channels, K = 27 taps
 // padded to 28; dW3 with M = taps (two tiles), N = channels, K = 4 cells per instruction.  Only dy needs
-// a halo.  Operand layout: lane l holds A[l%16][l/16], B[l/16][l%16], D[4(l/16)+0..3][l%16].
+// a halo.  One tile per block: each wave adds up its 256 positions in FP32, the four waves' sums meet in FP64.
+// Operand layout: lane l holds A[l%16][l/16], B[l/16][l%16], D[4(l/16)+0..3][l%16].
 // 72 us on a 128^3 network grid (0.14 GB, 240 products of 32 cycles per wave and tile), against 200 us
 // with one FMA and two LDS reads per (tap, channel, cell).
 __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ dy, const unsigned short* __restrict__ a2,
-                                                      Geo3 g, int tiles, const float* __restrict__ w3f,
+                                                      Geo3 g, const float* __restrict__ w3f,
                                                       unsigned short* __restrict__ dpre2, float* __restrict__ part) {
   constexpr int ROWW = 27 * CH + 1, CELLS = FX * FY * FZ;
   __shared__ float dyt[GCELLS];
   __shared__ __align__(16) unsigned short tile[CELLS * CH];   // a2, then d2 in place; at the end the wave sums
-  static_assert(sizeof(float) * 4 * ROWW <= sizeof(tile), "the wave sums reuse the tile");
+  static_assert(sizeof(double) * 4 * ROWW <= sizeof(tile), "the wave sums reuse the tile");
   const long long n3 = (long long)g.n * g.n * g.n;
   const int n = g.n, msk = n - 1, nbx = n / FX, nby = n / FY, per = nbx * nby * (n / FZ);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, q = lane >> 4;
@@ -379,79 +379,78 @@ __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ 
   }
   f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
   float bacc = 0.f;
-  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
-    const int b = t / per, tt = t % per;
-    const int x0 = (tt % nbx) * FX, y0 = ((tt / nbx) % nby) * FY, z0 = (tt / (nbx * nby)) * FZ;
-    constexpr int PD = (GCELLS + 255) / 256, PA = CELLS * 2 / 256;
-    float dv[PD];
-    u4 av[PA];
+  const int b = blockIdx.x / per, tt = blockIdx.x % per;
+  const int x0 = (tt % nbx) * FX, y0 = ((tt / nbx) % nby) * FY, z0 = (tt / (nbx * nby)) * FZ;
+  constexpr int PD = (GCELLS + 255) / 256, PA = CELLS * 2 / 256;
+  float dv[PD];
+  u4 av[PA];
 #pragma unroll
-    for (int k = 0; k < PD; ++k) {
-      const int c0 = threadIdx.x + k * 256, c = c0 < GCELLS ? c0 : GCELLS - 1;
-      const int hx = c % GX, hy = (c / GX) % GY, hz = c / (GX * GY);
-      dv[k] = dy[b * n3 + ((long long)((z0 - 1 + hz) & msk) * n + ((y0 - 1 + hy) & msk)) * n + ((x0 - 1 + hx) & msk)];
-    }
-    const u4* a128 = (const u4*)a2;
+  for (int k = 0; k < PD; ++k) {
+    const int c0 = threadIdx.x + k * 256, c = c0 < GCELLS ? c0 : GCELLS - 1;
+    const int hx = c % GX, hy = (c / GX) % GY, hz = c / (GX * GY);
+    dv[k] = dy[b * n3 + ((long long)((z0 - 1 + hz) & msk) * n + ((y0 - 1 + hy) & msk)) * n + ((x0 - 1 + hx) & msk)];
+  }
+  const u4* a128 = (const u4*)a2;
 #pragma unroll
-    for (int k = 0; k < PA; ++k) {
-      const int e = threadIdx.x + k * 256, cell = e >> 1;
-      const int lx = cell % FX, ly = (cell / FX) % FY, lz = cell / (FX * FY);
-      av[k] = a128[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)];
-    }
-    __syncthreads();                                       // the last tile's stores have left the tile
+  for (int k = 0; k < PA; ++k) {
+    const int e = threadIdx.x + k * 256, cell = e >> 1;
+    const int lx = cell % FX, ly = (cell / FX) % FY, lz = cell / (FX * FY);
+    av[k] = a128[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)];
+  }
 #pragma unroll
-    for (int k = 0; k < PD; ++k)
-      if (threadIdx.x + k * 256 < GCELLS) dyt[threadIdx.x + k * 256] = dv[k];
+  for (int k = 0; k < PD; ++k)
+    if (threadIdx.x + k * 256 < GCELLS) dyt[threadIdx.x + k * 256] = dv[k];
 #pragma unroll
-    for (int k = 0; k < PA; ++k) ((u4*)tile)[threadIdx.x + k * 256] = av[k];
-    __syncthreads();
-    for (int c = threadIdx.x; c < CELLS; c += 256)
-      bacc += dyt[((c / (FX * FY) + 1) * GY + (c / FX) % FY + 1) * GX + c % FX + 1];
+  for (int k = 0; k < PA; ++k) ((u4*)tile)[threadIdx.x + k * 256] = av[k];
+  __syncthreads();
+  for (int c = threadIdx.x; c < CELLS; c += 256)
+    bacc += dyt[((c / (FX * FY) + 1) * GY + (c / FX) % FY + 1) * GX + c % FX + 1];
 #pragma unroll 2
-    for (int row = 0; row < 16; ++row) {
-      const int lz = wz0 + (row >> 2), ly = wy0 + (row & 3);
-      const int hrow = ((lz + 1) * GY + ly + 1) * GX + 1;  // halo cell of the row's first cell
-      unsigned short* cells = tile + (lz * FY + ly) * FX * CH;
-      f4 d = {0.f, 0.f, 0.f, 0.f};
+  for (int row = 0; row < 16; ++row) {
+    const int lz = wz0 + (row >> 2), ly = wy0 + (row & 3);
+    const int hrow = ((lz + 1) * GY + ly + 1) * GX + 1;  // halo cell of the row's first cell
+    unsigned short* cells = tile + (lz * FY + ly) * FX * CH;
+    f4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int s = 0; s < 7; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + da[s]], w[s], d, 0, 0, 0);
+    for (int s = 0; s < 7; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + da[s]], w[s], d, 0, 0, 0);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float bv = from_bf16(cells[(4 * k + q) * CH + m]);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + 4 * k + dt[0]], bv, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + 4 * k + dt[1]], bv, acc[1], 0, 0, 0);
-      }
-      // the wave alone reads and writes this row: its reads above are issued before these writes
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        unsigned short* c = cells + (4 * q + i) * CH + m;
-        *c = from_bf16(*c) > 0.f ? to_bf16(d[i]) : (unsigned short)0;
-      }
+    for (int k = 0; k < 4; ++k) {
+      const float bv = from_bf16(cells[(4 * k + q) * CH + m]);
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + 4 * k + dt[0]], bv, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(dyt[hrow + 4 * k + dt[1]], bv, acc[1], 0, 0, 0);
     }
-    __syncthreads();
-    uint4* o128 = (uint4*)dpre2;
+    // the wave alone reads and writes this row: its reads above are issued before these writes
 #pragma unroll
-    for (int k = 0; k < PA; ++k) {
-      const int e = threadIdx.x + k * 256, cell = e >> 1;
-      const int lx = cell % FX, ly = (cell / FX) % FY, lz = cell / (FX * FY);
-      o128[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)] = ((const uint4*)tile)[e];
+    for (int i = 0; i < 4; ++i) {
+      unsigned short* c = cells + (4 * q + i) * CH + m;
+      *c = from_bf16(*c) > 0.f ? to_bf16(d[i]) : (unsigned short)0;
     }
   }
   __syncthreads();
-  float* red = (float*)tile;                               // [4 waves][ROWW]
+  uint4* o128 = (uint4*)dpre2;
+#pragma unroll
+  for (int k = 0; k < PA; ++k) {
+    const int e = threadIdx.x + k * 256, cell = e >> 1;
+    const int lx = cell % FX, ly = (cell / FX) % FY, lz = cell / (FX * FY);
+    o128[(b * n3 + ((long long)(z0 + lz) * n + (y0 + ly)) * n + x0 + lx) * 2 + (e & 1)] = ((const uint4*)tile)[e];
+  }
+  __syncthreads();
+  double* red = (double*)tile;                             // [4 waves][ROWW]
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int t = 16 * a + 4 * q + i;
-      if (t < 27) red[wave * ROWW + t * CH + m] = acc[a][i];
+      if (t < 27) red[wave * ROWW + t * CH + m] = (double)acc[a][i];
     }
+  double bsum = (double)bacc;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) bacc += __shfl_xor(bacc, o, 64);
-  if (lane == 0) red[wave * ROWW + ROWW - 1] = bacc;
+  for (int o = 32; o > 0; o >>= 1) bsum += __shfl_xor(bsum, o, 64);
+  if (lane == 0) red[wave * ROWW + ROWW - 1] = bsum;
   __syncthreads();
   for (int e = threadIdx.x; e < ROWW; e += 256)
-    part[(long long)blockIdx.x * ROWW + e] = (red[e] + red[ROWW + e]) + (red[2 * ROWW + e] + red[3 * ROWW + e]);
+    part[(long long)blockIdx.x * ROWW + e] =
+        (float)((red[e] + red[ROWW + e]) + (red[2 * ROWW + e] + red[3 * ROWW + e]));
 }
 
 // Weight gradient of a 16-output convolution:
@@ -461,13 +460,22 @@ __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ 
 // are needed position-fastest: ds_read_b64_tr_b16 transposes on the way (in each group of 16 lanes, lane
 // 4 r + c reads channels 4c..4c+3 of position r, and lane i receives channel i of positions 0..3), so a
 // tap is only an address offset and nothing is gathered element by element.  A group of lanes reads 128
-// contiguous bytes, free of bank conflicts.  The four waves split the column tiles; a block takes
-// several tiles of 16 x 4 x 8 positions and writes one partial [16][KP + 1] (bias in the last column).
+// contiguous bytes, free of bank conflicts.  The four waves split the column tiles; a block takes the tiles of
+// 16 x 4 x 8 positions that wgrad_rows gives it, adds their products up in FP32 and writes one partial [16][KP + 1]
+// (bias in the last column).  HALVES (16^3): the FP32 sums end with each half of a tile.
 // Bound by the staging of a tile before its products (with a wave taking two z planes and all taps, a third
 // of the LDS reads, 56 us instead of 58).  On a 128^3 network grid 58 us (layer 2) and 35 us (layer 1); with
 // element-by-element gathers of the operand, 225 and 201 us.
 constexpr int VX = 16, VY = 4, VZ = 8, UX = VX + 2, UY = VY + 2, UZ = VZ + 2, UCELLS = UX * UY * UZ;
 constexpr int VCELLS = VX * VY * VZ;
+
+// Blocks of k_wgrad, and so rows of partial sums (42 KB each, both layers): 16 n positions a row, which is what is
+// added up in FP32 (256 at 16^3, where a block's tile of 512 is summed in halves), or one tile.  1,024 rows at
+// 128^3, 4,096 at 256^3.
+inline long long wgrad_rows(long long n, long long batch) {
+  const long long tiles = batch * n * n * n / VCELLS, rows = batch * n * n / 16;
+  return tiles < rows ? tiles : rows;
+}
 
 __device__ __forceinline__ bf8 tr_pair(const unsigned short* p0, const unsigned short* p1) {
   typedef __attribute__((address_space(3))) s4 lds4;
@@ -478,7 +486,7 @@ __device__ __forceinline__ bf8 tr_pair(const unsigned short* p0, const unsigned 
 }
 
 //   SRC 0: x is a bf16 tensor [n^3][C];  SRC 1: x is x0 assembled from (delta, u_p), C = 8
-template <int C, int KP, int SRC>
+template <int C, int KP, int SRC, bool HALVES>
 __global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict__ dpre,
                                                const unsigned short* __restrict__ in, const float* __restrict__ delta,
                                                const float* __restrict__ up, Geo3 g, int tiles,
@@ -503,6 +511,7 @@ __global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict_
   f4 acc[TPW], bacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int k = 0; k < TPW; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+  double sum[TPW][4] = {}, bsum[4] = {};      // HALVES
   for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
     const int b = t / per, tt = t % per;
     const int x0 = (tt % nbx) * VX, y0 = ((tt / nbx) % nby) * VY, z0 = (tt / (nbx * nby)) * VZ;
@@ -568,6 +577,17 @@ __global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict_
 #pragma unroll
       for (int k = 0; k < TPW; ++k) acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[k], acc[k], 0, 0, 0);
       bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, bacc, 0, 0, 0);
+      if (HALVES && (s + 1) % (VY * VZ / 4) == 0) {
+#pragma unroll
+        for (int k = 0; k < TPW; ++k) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sum[k][i] += (double)acc[k][i];
+          acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bsum[i] += (double)bacc[i];
+        bacc = f4{0.f, 0.f, 0.f, 0.f};
+      }
     }
   }
   // D[o = 4q + i][col = m] for each column tile
@@ -577,12 +597,12 @@ __global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict_
     const int nt = wave + 4 * k;
     if (nt < NT) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pb[(4 * q + i) * (KP + 1) + nt * 16 + m] = acc[k][i];
+      for (int i = 0; i < 4; ++i) pb[(4 * q + i) * (KP + 1) + nt * 16 + m] = HALVES ? (float)sum[k][i] : acc[k][i];
     }
   }
   if (wave == 3 && m == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) pb[(4 * q + i) * (KP + 1) + KP] = bacc[i];
+    for (int i = 0; i < 4; ++i) pb[(4 * q + i) * (KP + 1) + KP] = HALVES ? (float)bsum[i] : bacc[i];
   }
 }
 
