@@ -1657,7 +1657,8 @@ __global__ void __launch_bounds__(N, N == 512 ? 4 : 1) k_z_iter_c(float2* __rest
     __syncthreads();                                    // the twiddle factors
   }
   // s = Psi . r (two columns packed as .x / .y) -> q = u_0 / |r|, so that V_j = q r_j
-  float acc1 = 0.f, acc2 = 0.f;          // 32 terms per thread; block and grid sums in FP64
+  float acc1 = 0.f, acc2 = 0.f;          // 16 terms of a thread; everything beyond in FP64
+  double sum1 = 0.0, sum2 = 0.0;
   const float ry = los_comp(g, 1, y);
   const float rx0 = los_comp(g, 0, x0 + c), rx1 = los_comp(g, 0, x0 + c + WP);
   const ZField<N, 4> cf(corr + b * n3, y, x0, c, j), uf(up_in + b * n3, y, x0, c, j);
@@ -1692,6 +1693,11 @@ __global__ void __launch_bounds__(N, N == 512 ? 4 : 1) k_z_iter_c(float2* __rest
       if (h) s[r].y = q; else s[r].x = q;
     }
     v[r] = s[r] * rz;
+    if (MODE != ZI_PLAIN && r % 8 == 7) {
+      sum1 += (double)acc1;
+      sum2 += (double)acc2;
+      acc1 = acc2 = 0.f;
+    }
     if (MODE != ZI_PLAIN && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // few loads in flight at a time
   }
   // Z[q] -> a0 and i k'_z Z[r_z q] -> a1
@@ -1701,7 +1707,7 @@ __global__ void __launch_bounds__(N, N == 512 ? 4 : 1) k_z_iter_c(float2* __rest
   C::template unpack<true, H>(buf, a1, y, x0, g.kf);
   if (MODE != ZI_PLAIN) {
     double t1, t2;
-    block_sum2<N>((double)acc1, (double)acc2, &t1, &t2);
+    block_sum2<N>(sum1, sum2, &t1, &t2);
     if (threadIdx.x == 0) {
       const long long nb = gridDim.x;
       partials[2 * (b * nb + blockIdx.x) + 0] = t1;
