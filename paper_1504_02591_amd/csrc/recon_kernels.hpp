@@ -2623,6 +2623,9 @@ __global__ void __launch_bounds__((Plane<N, 2>::NT)) k_plane_iter(float2* __rest
     }
   }
   pl.template fft_x<false>(v);
+  // (a transform of 8 points has no barrier of its own between the reads of mid above and the writes below;
+  // the two groups are one wave there, and this states the order without a cost)
+  if constexpr (N == 8) __syncthreads();
   // the other group's value of this thread's elements; slot r holds element r of the thread pair
   if (pl.on) {
 #pragma unroll
