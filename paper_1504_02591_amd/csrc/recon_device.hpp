@@ -398,6 +398,12 @@ __device__ __forceinline__ void lds_pass_r8_mfma(float2* buf, const float2* tw) 
   __syncthreads();
 }
 
+// Eight values as they are in registers here: nothing is contracted across this point.
+__device__ __forceinline__ void hold8(float2* v) {
+#pragma unroll
+  for (int r = 0; r < 8; ++r) asm volatile("" : "+v"(v[r].x), "+v"(v[r].y));
+}
+
 // Length-N FFT of the tile, register fragment in and out.  The caller must place a
 // barrier before its next write to the tile.  SPLIT > 0 (N >= 64): the last radix-8 stage runs on
 // the matrix cores with SPLIT bfloat16 terms per operand (lds_pass_r8_mfma).
@@ -405,7 +411,14 @@ template <int N, int W, bool INV, bool JF, int SPLIT = 0>
 __device__ __forceinline__ void fft_rr(float2* v, float2* buf, const float2* tw, int t = threadIdx.x) {
   using L = Lay<N, W, JF>;
   if constexpr (N == 8) {
-    if (t < L::NTF) dft8<INV>(v);
+    // The caller's products are rounded before the transform and its sums after it: with no exchange between
+    // them the compiler would contract the two differently in each kernel, and a result would depend on which
+    // kernels a pass ran in.
+    if (t < L::NTF) {
+      hold8(v);
+      dft8<INV>(v);
+      hold8(v);
+    }
   } else if constexpr (N < 64) {
     first_pass<N, W, INV, JF>(v, buf, t);
     lds_pass<N, W, N / 8, 8, INV, JF>(buf, tw, t);
