@@ -258,6 +258,25 @@ struct PinnedDoubles {
   }
 };
 
+// Makes the device of a stream current while it lives (the null stream belongs to the current device).  What
+// is launched on a stream runs on its device whichever is current, but an event can be recorded only on a stream
+// of the device it was created on.
+struct OnStreamDevice {
+  int before = -1;
+  explicit OnStreamDevice(hipStream_t s) {
+    int cur = 0;
+    hipDevice_t dev = 0;
+    if (s && hipGetDevice(&cur) == hipSuccess && hipStreamGetDevice(s, &dev) == hipSuccess && dev != cur &&
+        hipSetDevice(dev) == hipSuccess)
+      before = cur;
+  }
+  ~OnStreamDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+  OnStreamDevice(const OnStreamDevice&) = delete;
+  OnStreamDevice& operator=(const OnStreamDevice&) = delete;
+};
+
 // The library's own device scratch for plans that cannot allocate (recon_plan_noalloc): one array per
 // GPU, held until the process ends.  Host code never uses the symbol itself as an address (there it
 // is only a host-side stand-in); the device address of each GPU's copy comes from
@@ -1202,6 +1221,7 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
   pl->h_fan.assign(pl->batch, 0);
   pl->h_fin.assign(pl->batch, 0);
   pl->h_it.assign(pl->batch, 0);
+  const OnStreamDevice on_device(pinned ? pl->stream : nullptr);   // for the read-back buffer and its event
   const size_t parts = (size_t)pl->batch * (n / 2 + 1);
   const bool host_parts = ops_for(n) && ops_for(n)->plane && parts <= kHostParts;
   if (!pl->host.assign(7 * (size_t)pl->batch + 4 + (host_parts ? 2 * parts : 0), 0.0, pinned) ||
