@@ -193,7 +193,10 @@ def size_blocks():
 def cmd_write(a):
     meta = json.load(open(os.path.join(a.dir, "result.json")))
     choice, res, n = meta["choice"], meta["times"], meta["n"]
-    if "combined_ms" in meta and meta["combined_ms"] >= res["base"]:
+    if a.keep:
+        choice = meta["base"]
+        note = "the values kept"
+    elif "combined_ms" in meta and meta["combined_ms"] >= res["base"]:
         choice = meta["base"]
         note = f"single-knob winners combined were not faster ({meta['combined_ms']:.4f} ms); kept"
     else:
@@ -257,6 +260,7 @@ def main():
     c.add_argument("--passes", type=int, default=10)
     w = sub.add_parser("write")
     w.add_argument("--dir", required=True)
+    w.add_argument("--keep", action="store_true", help="record the timings, leave the knobs as they are")
     a = ap.parse_args()
     {"build": cmd_build, "time": cmd_time, "one": cmd_one, "write": cmd_write, "combined": cmd_combined}[a.cmd](a)
 

@@ -1472,17 +1472,18 @@ int recon_solve(recon_plan_t* pl, int start, const void* net) {
     // setup is done (the call is a synchronisation point: it leaves nothing of the setup queued).
     std::vector<int> st(pl->batch, 0);
     int errs[kOrderAt + 2] = {};
-    if (!pl->hd_stat) {
-      HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, sizeof errs, hipMemcpyDeviceToHost, pl->stream));
-      HIP_TRY(pl, hipMemcpyAsync(st.data(), pl->status, sizeof(int) * pl->batch, hipMemcpyDeviceToHost, pl->stream));
-    }
-    HIP_TRY(pl, hipStreamSynchronize(pl->stream));
     if (pl->hd_stat) {
+      HIP_TRY(pl, hipEventRecord(pl->ev, pl->stream));
+      RECON_TRY(wait_read(pl));
       for (int k = 0; k < 2; ++k) {
         errs[k] = (int)pl->h_stat[k];
         errs[kOrderAt + k] = (int)pl->h_stat[2 + k];
       }
       for (int b = 0; b < pl->batch; ++b) st[b] = (int)pl->h_stat[4 + b];
+    } else {
+      HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, sizeof errs, hipMemcpyDeviceToHost, pl->stream));
+      HIP_TRY(pl, hipMemcpyAsync(st.data(), pl->status, sizeof(int) * pl->batch, hipMemcpyDeviceToHost, pl->stream));
+      HIP_TRY(pl, hipStreamSynchronize(pl->stream));
     }
     for (int k = 0; k < 2; ++k) pl->scattered[k] = pl->ngp_n[k] > 0 && errs[kOrderAt + k] == 0;
     const int errcount = errs[0] + (pl->randoms ? errs[1] : 0);
