@@ -4,8 +4,8 @@ Knobs (compile-time, see recon_tuning.h): RECON_TILE_Z (packed z column pairs pe
 RECON_TILE_Y (y-pass columns) and RECON_Z_TPB (z tiles per block of the z iteration, whose next
 tile is staged while the current one is finished) of the sizes below 256, RECON_TILE_X (x-pass
 rows) with copies of its own for 256^3 (_256) and 1024^3 (_1024), and RECON_MID_512 /
-RECON_MID_1024 (split of the middle radix factor).  Each grid size tunes its own knobs (SIZE_KNOBS), one knob at a time around the current
-setting: every single-knob variant is compiled (in parallel, on the host), each is timed on the GPU
+RECON_MID_1024 (split of the middle radix factor).  Each grid size tunes its own knobs (SIZE_KNOBS), one
+knob at a time around the current setting: every single-knob variant is compiled (in parallel, on the host), each is timed on the GPU
 in a process of its own on the correction pass of an n^3 field, or of a batch of them (the dominant
 cost of a reconstruction), and each knob takes its fastest value.  The combined choice is timed
 again against the current setting and written to recon_tuning.h only if it is faster; the other
@@ -15,6 +15,7 @@ sizes' knobs and timings are kept.
     python -m paper_1504_02591_amd.autotune time --dir DIR                       # GPU: time, pick
     python -m paper_1504_02591_amd.autotune combined --dir DIR                   # build + time the pick
     python -m paper_1504_02591_amd.autotune write --dir DIR                      # host: write the header
+    python -m paper_1504_02591_amd.autotune write --dir DIR --keep               # ... its timings only
 """
 from __future__ import annotations
 
@@ -30,8 +31,9 @@ import time
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 TUNING = os.path.join(HERE, "csrc", "recon_tuning.h")
-# knobs timed at each grid size (recon_tuning.h): the general ones at 512^3 (every size without its own
-# values takes them), the per-size ones at 256^3 (the batched workload) and 1024^3
+# knobs timed at each grid size (recon_tuning.h): the tiles of the radix-8 engine's z and y passes at 128^3 (a
+# batch fills the chip), the x passes' rows and the radix splits at 256^3 (the batched workload), 512^3 (every
+# size without its own rows takes these) and 1024^3
 SIZE_KNOBS = {
     128: {"RECON_TILE_Z": [8, 16], "RECON_TILE_Y": [8, 16], "RECON_Z_TPB": [1, 2, 4, 8]},
     512: {"RECON_TILE_X": [2, 4, 8], "RECON_MID_512": [0, 1, 2]},
@@ -193,7 +195,7 @@ def size_blocks():
 def cmd_write(a):
     meta = json.load(open(os.path.join(a.dir, "result.json")))
     choice, res, n = meta["choice"], meta["times"], meta["n"]
-    if a.keep:
+    if getattr(a, "keep", False):
         choice = meta["base"]
         note = "the values kept"
     elif "combined_ms" in meta and meta["combined_ms"] >= res["base"]:

@@ -350,7 +350,8 @@ typedef unsigned u4 __attribute__((ext_vector_type(4)));
 // padded to 28; dW3 with M = taps (two tiles), N = channels, K = 4 cells per instruction.  Only dy needs
 // a halo.  One tile per block: each wave adds up its 256 positions in FP32, the four waves' sums meet in FP64.
 // Operand layout: lane l holds A[l%16][l/16], B[l/16][l%16], D[4(l/16)+0..3][l%16].
-// 72 us on a 128^3 network grid (0.14 GB, 240 products of 32 cycles per wave and tile), against 200 us
+// 63 us on a 128^3 network grid (0.14 GB, 240 products of 32 cycles per wave and tile; 72 with several tiles per
+// block, whose loads then wait for the last tile's stores), against 200 us
 // with one FMA and two LDS reads per (tap, channel, cell).
 __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ dy, const unsigned short* __restrict__ a2,
                                                       Geo3 g, const float* __restrict__ w3f,
@@ -464,7 +465,7 @@ __global__ void __launch_bounds__(256) k_conv_out_bwd(const float* __restrict__ 
 // 16 x 4 x 8 positions that wgrad_rows gives it, adds their products up in FP32 and writes one partial [16][KP + 1]
 // (bias in the last column).  HALVES (16^3): the FP32 sums end with each half of a tile.
 // Bound by the staging of a tile before its products (with a wave taking two z planes and all taps, a third
-// of the LDS reads, 56 us instead of 58).  On a 128^3 network grid 58 us (layer 2) and 35 us (layer 1); with
+// of the LDS reads, 56 us instead of 58).  On a 128^3 network grid 57 us (layer 2) and 35 us (layer 1); with
 // element-by-element gathers of the operand, 225 and 201 us.
 constexpr int VX = 16, VY = 4, VZ = 8, UX = VX + 2, UY = VY + 2, UZ = VZ + 2, UCELLS = UX * UY * UZ;
 constexpr int VCELLS = VX * VY * VZ;
@@ -608,7 +609,7 @@ __global__ void __launch_bounds__(256) k_wgrad(const unsigned short* __restrict_
 
 // Sums of the partial rows in FP64, all three layers in one launch: out[slice][column] = sum over the
 // slice's rows, columns in the order layer 3 [433], layer 2 [16][433], layer 1 [16][225].  A block takes
-// 64 columns; its four waves take every fourth row of the slice with four loads in flight each: 11 us
+// 64 columns; its four waves take every fourth row of the slice with four loads in flight each: 14 us
 // at 128^3.  (One thread per column over all rows, 8,192 of them in layer 3, was 3.87 of a 4.84 ms
 // training step: three launches of 2 to 28 blocks, one dependent FP64 add after another.)  The last
 // column block's first slice sums the loss.

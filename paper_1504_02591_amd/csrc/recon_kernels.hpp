@@ -53,11 +53,11 @@ template <int N> constexpr int tile_x() {
   return N == 256 ? RECON_TILE_X_256 : (N == 1024 ? RECON_TILE_X_1024 : RECON_TILE_X);
 }
 // The z and y passes run on the column engine from 256 on: tiles of 16 columns (packed, in z) and one block
-// of N threads per tile, 16 elements each.  Below 256 a grid has too few tiles to fill the chip with
-// N-thread blocks, and the radix-8 engine with its tile knobs stays; so it does for the matrix-core variants
-// of the z iteration at every size, with 8 columns at 1024 (more would not fit the LDS).  Both sides on a
-// batch of eight 256^3 (where the engine gives least; ms): z iteration 0.404 against 0.523, y passes 0.412
-// against 0.440; one 512^3: 0.462 / 0.556 and 0.473 / 0.488; one 1024^3: 6.3 / 8.4 and 4.0 / 5.9.
+// of N threads per tile, 16 elements each.  Below 256 there is no such engine (its second pass is of radix 16
+// and more), and the radix-8 engine with its tile knobs stays, for a single grid and for a batch; so it does for
+// the matrix-core variants of the z iteration at every size, with 8 columns at 1024 (more would not fit the LDS).
+// Both sides on a batch of eight 256^3 (where the engine gives least; ms): z iteration 0.404 against 0.523, y
+// passes 0.412 against 0.440; one 512^3: 0.462 / 0.556 and 0.473 / 0.488; one 1024^3: 6.3 / 8.4 and 4.0 / 5.9.
 template <int N> constexpr bool z_col() { return N >= 256; }
 template <int N> constexpr int wz() { return z_col<N>() ? 16 : cmin(N / 2, RECON_TILE_Z); }
 template <int N, int SPLIT> constexpr int wzs() { return SPLIT > 0 && N >= 1024 ? 8 : wz<N>(); }
@@ -1615,10 +1615,11 @@ __global__ void __launch_bounds__((ntzs<N, SPLIT>())) k_z_iter(float2* __restric
 }
 
 // The z iteration of k_z_iter on the column engine, one tile per block.  It moves 4 spectrum passes (2.15 GB
-// at 512^3, 0.34 ms at the chip's streaming rate); what bounds it is the latency of a block's own chain of
-// loads, three transforms and stores, so the blocks are small (N threads) and two or more share a CU, one
-// loading or storing while another transforms.  512^3 0.556 -> 0.462 ms (1024-thread blocks of the radix-8
-// engine with wave-local transforms before), 256^3 69 -> 56 us, 1024^3 8.4 -> 6.3 ms.
+// at 512^3, 0.34 ms at the chip's streaming rate) and issues 2,985 VALU instructions a wave, 64 waves per SIMD:
+// 0.32 of its 0.44 ms.  Both come near what it takes, and a block's chain of loads, four transforms and stores
+// runs one after the other, so the blocks are small (N threads) and two or more share a CU, one loading or
+// storing while another transforms.  512^3 0.556 -> 0.44 ms (1024-thread blocks of the radix-8 engine with
+// wave-local transforms before), 256^3 69 -> 56 us, 1024^3 8.4 -> 6.3 ms.
 template <int N, int MODE, int H = stream_of<N>()>
 __global__ void __launch_bounds__(N, N == 512 ? 4 : 1) k_z_iter_c(float2* __restrict__ a0, float2* __restrict__ a1,
                                                   const float2* __restrict__ a2, Geo g, float* __restrict__ corr,
