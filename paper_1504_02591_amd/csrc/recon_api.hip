@@ -351,8 +351,8 @@ struct recon_plan_s {
   CicGeo cic{};
   bool painted_g = false, painted_r = false;
   // objects of a grid's last deposit if that was a nearest-grid-point one through the bricks, and whether it
-  // found them in no spatial order (known from the solve on)
-  long long ngp_n[2] = {0, 0};
+  // found them in no spatial order, in how many bricks (known from the solve on)
+  long long ngp_n[2] = {0, 0}, occupied[2] = {0, 0};
   bool scattered[2] = {false, false};
   int state = ST_EMPTY;
   int start = RECON_START_PLAIN;
@@ -365,7 +365,7 @@ struct recon_plan_s {
   std::vector<int> h_fan, h_fin, h_it;
   std::vector<int> up_fan, up_fin, up_it;     // what the device masks hold (empty: not yet uploaded)
   // what the host reads: sums of the pass [2 B] and of a non-gradient start [2 B], the cross sums [2 B],
-  // invalid-object counts [2], catalogue orders [2] and status [B]
+  // invalid-object counts [2], catalogue orders [2], occupied bricks [2] and status [B]
   PinnedDoubles host;
   double *h_red = nullptr, *h_red2 = nullptr, *h_stat = nullptr;
   double *hd_red = nullptr, *hd_red2 = nullptr, *hd_stat = nullptr;   // as kernels address them, or null
@@ -905,9 +905,9 @@ BrickParts brick_parts(long long nbins, long long n, long long unit) {
 
 template <int BINS>
 void launch_bin_count(recon_plan_t* pl, const BinShape& b, const float* pos, const float* w, long long n,
-                      const long long* off, int* ordblk) {
+                      const long long* off, int* ordblk, int* occupied) {
   k_bin_count_lds<1024, BINS><<<(unsigned)b.blocks, 1024, 0, pl->stream>>>(
-      pos, w, n, b.chunk, off, pl->batch, pl->cic, pl->bcount, pl->errblk, pl->bhist, ordblk);
+      pos, w, n, b.chunk, off, pl->batch, pl->cic, pl->bcount, pl->errblk, pl->bhist, ordblk, occupied);
 }
 template <int BINS>
 void launch_bin_scatter(recon_plan_t* pl, const BinShape& b, const float* pos, const float* w, long long n,
@@ -920,17 +920,19 @@ void launch_bin_scatter(recon_plan_t* pl, const BinShape& b, const float* pos, c
 // Objects into brick order (pl->sorted, pl->slot_of, pl->bstart).  The brick counts are zero before and
 // after (cleared at the plan's creation and by every scatter).  prep >= 0: the bricks of `grid` are
 // prepared for a deposit in that mode (k_brick_prepare).  Invalid objects are counted into *errc (replacing
-// it when fresh, else added); order, when not null, receives whether the catalogue is in spatial order.
+// it when fresh, else added); order and occupied, when not null, receive whether the catalogue is in spatial
+// order and how many bricks hold objects of it.
 int bin_objects(recon_plan_t* pl, const float* pos, const float* w, long long n, const long long* off, int prep,
-                unsigned char* valid, unsigned long long* grid, int* errc, bool fresh, int* order = nullptr) {
+                unsigned char* valid, unsigned long long* grid, int* errc, bool fresh, int* order = nullptr,
+                int* occupied = nullptr) {
   const long long nb = pl->L.nbins;
   const BinShape bs = bin_shape(nb, n);
   int* ordblk = order ? pl->errblk + bs.blocks : nullptr;   // (16 bytes per object hold both)
   {
     PROF(pl, KP_BIN);
-    if (bs.bins == kBinsS) launch_bin_count<kBinsS>(pl, bs, pos, w, n, off, ordblk);
-    else if (bs.bins == kBinsM) launch_bin_count<kBinsM>(pl, bs, pos, w, n, off, ordblk);
-    else launch_bin_count<kLdsBins>(pl, bs, pos, w, n, off, ordblk);
+    if (bs.bins == kBinsS) launch_bin_count<kBinsS>(pl, bs, pos, w, n, off, ordblk, occupied);
+    else if (bs.bins == kBinsM) launch_bin_count<kBinsM>(pl, bs, pos, w, n, off, ordblk, occupied);
+    else launch_bin_count<kLdsBins>(pl, bs, pos, w, n, off, ordblk, occupied);
   }
   RECON_TRY(check_launch(pl, "bin count"));
   {
@@ -943,7 +945,7 @@ int bin_objects(recon_plan_t* pl, const float* pos, const float* w, long long n,
     const long long blocks = pl->L.nscan + (prep >= 0 ? nb : 0);
     k_scan_prepare<<<(unsigned)blocks, 256, 0, pl->stream>>>(pl->bcount, nb, bsum, (int)pl->L.nscan, pl->bstart,
                                                              pl->bcursor, pl->n, prep, valid, grid, pl->errblk,
-                                                             (int)bs.blocks, errc, fresh ? 1 : 0, ordblk, order);
+                                                             (int)bs.blocks, errc, fresh ? 1 : 0, ordblk, order, occupied);
   }
   RECON_TRY(check_launch(pl, "bin scan"));
   {
@@ -1224,7 +1226,7 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
   const OnStreamDevice on_device(pinned ? pl->stream : nullptr);   // for the read-back buffer and its event
   const size_t parts = (size_t)pl->batch * (n / 2 + 1);
   const bool host_parts = ops_for(n) && ops_for(n)->plane && parts <= kHostParts;
-  if (!pl->host.assign(7 * (size_t)pl->batch + 4 + (host_parts ? 2 * parts : 0), 0.0, pinned) ||
+  if (!pl->host.assign(7 * (size_t)pl->batch + 6 + (host_parts ? 2 * parts : 0), 0.0, pinned) ||
       (pinned && hipEventCreateWithFlags(&pl->ev, hipEventDisableTiming) != hipSuccess)) {
     delete pl;
     return RECON_EDEVICE;
@@ -1237,7 +1239,7 @@ int plan_create(recon_plan_t** out, const recon_params_t* params, const Layout& 
     pl->hd_red2 = pl->hd_red + 4 * pl->batch;
     pl->hd_stat = pl->hd_red2 + 2 * pl->batch;
     if (host_parts) {
-      const size_t at = 7 * (size_t)pl->batch + 4;
+      const size_t at = 7 * (size_t)pl->batch + 6;
       pl->h_part = pl->host.p + at;
       pl->hd_part = pl->host.dev + at;
     }
@@ -1403,7 +1405,7 @@ int recon_paint(recon_plan_t* pl, int which, const float* pos, const float* w, i
     const long long nb = pl->L.nbins;
     const int prep = can_sparse && (fresh || sparse) ? (fresh ? 0 : 1) : -1;
     RECON_TRY(bin_objects(pl, pos, w, n, (const long long*)offsets, prep, valid, (unsigned long long*)grid, errc, fresh,
-                          ngp ? pl->err + kOrderAt + which : nullptr));
+                          ngp ? pl->err + kOrderAt + which : nullptr, pl->err + kOccupiedAt + which));
     if (ngp) pl->ngp_n[which] = n;
     if (prep >= 0) sparse = true;
     {
@@ -1471,21 +1473,25 @@ int recon_solve(recon_plan_t* pl, int start, const void* net) {
     // one read-back: invalid-object counters and the totals status of every realisation, once the whole
     // setup is done (the call is a synchronisation point: it leaves nothing of the setup queued).
     std::vector<int> st(pl->batch, 0);
-    int errs[kOrderAt + 2] = {};
+    int errs[kOccupiedAt + 2] = {};
     if (pl->hd_stat) {
       HIP_TRY(pl, hipEventRecord(pl->ev, pl->stream));
       RECON_TRY(wait_read(pl));
       for (int k = 0; k < 2; ++k) {
         errs[k] = (int)pl->h_stat[k];
         errs[kOrderAt + k] = (int)pl->h_stat[2 + k];
+        errs[kOccupiedAt + k] = (int)pl->h_stat[4 + k];
       }
-      for (int b = 0; b < pl->batch; ++b) st[b] = (int)pl->h_stat[4 + b];
+      for (int b = 0; b < pl->batch; ++b) st[b] = (int)pl->h_stat[6 + b];
     } else {
       HIP_TRY(pl, hipMemcpyAsync(errs, pl->err, sizeof errs, hipMemcpyDeviceToHost, pl->stream));
       HIP_TRY(pl, hipMemcpyAsync(st.data(), pl->status, sizeof(int) * pl->batch, hipMemcpyDeviceToHost, pl->stream));
       HIP_TRY(pl, hipStreamSynchronize(pl->stream));
     }
-    for (int k = 0; k < 2; ++k) pl->scattered[k] = pl->ngp_n[k] > 0 && errs[kOrderAt + k] == 0;
+    for (int k = 0; k < 2; ++k) {
+      pl->scattered[k] = pl->ngp_n[k] > 0 && errs[kOrderAt + k] == 0;
+      pl->occupied[k] = errs[kOccupiedAt + k];
+    }
     const int errcount = errs[0] + (pl->randoms ? errs[1] : 0);
     if (errcount) return fail(pl, RECON_EINVAL, std::to_string(errcount) + " objects had invalid positions or weights");
     for (int b = 0; b < pl->batch; ++b) {
@@ -1968,16 +1974,20 @@ int recon_shift(recon_plan_t* pl, int which_flags, const float* pos, int64_t n, 
   long long blocks = (n + kThreads - 1) / kThreads;
   if (blocks > 8192) blocks = 8192;
   // A catalogue that is not in brick order is put there first where that is cheaper than gathering the
-  // displacement object by object: the displacement is larger than the L2s (from 256^3 on), there are
-  // objects enough per brick (staging its footprint costs about as much as 70 objects' gathers), the
-  // brick-ordered copy of a deposit is not in the way, and the catalogue is known to be in no spatial order:
-  // its nearest-grid-point deposit through the bricks has found that.  (A catalogue that was not deposited so, or
-  // is of another length than what was, goes object by object, as one in spatial order does.)  us, object by
-  // object / binned: random order at 256^3 300,000 objects 90 / 84, 393,216 119 / 86, 4.3e6 1289 / 268, 1.7e7
-  // 4965 / 751; at 512^3 1.1e6 329 / 694, 2e6 575 / 735, 3.1e6 916 / 783, 3e7 8682 / 2231; sorted along z at 256^3
-  // 4.3e6 522 / 203; in spatial order 4.3e6 77 / 177 (lattice) and 367 / 2210 (a clump of 13 cells).
+  // displacement object by object: the displacement is larger than the L2s (from 256^3 on), the brick-ordered
+  // copy of a deposit is not in the way, and the catalogue is known to be in no spatial order: its
+  // nearest-grid-point deposit through the bricks has found that.  (A catalogue that was not deposited so, or is
+  // of another length than what was, goes object by object, as one in spatial order does.)  An object's gathers
+  // cost 0.25 us a thousand; the binning costs 30 us, 3.5 us for a thousand bricks of the grid, and the staging of
+  // a brick that holds objects as much as 64 of them (28 at 256^3, whose displacement the memory-side cache holds).
+  // us, object by object / binned: random order over the box at 256^3 262,144 objects 79 / 82, 303,104 88 / 83,
+  // 393,216 116 / 86, 4.3e6 1239 / 268; at 512^3 1.1e6 321 / 696, 2.6e6 752 / 767, 3.1e6 914 / 790; in a survey's
+  // cone (a sixth of the bricks) at 256^3 262,144 60 / 53, at 512^3 800,000 229 / 254, 1.1e6 307 / 263, 8e6
+  // 2271 / 578; sorted along z at 256^3 4.3e6 522 / 203; in spatial order 4.3e6 77 / 176 (lattice) and 367 / 2183
+  // (a clump of 13 cells).
+  const long long least = (1 << 17) + 14 * pl->L.nbins + (pl->n >= 512 ? 64 : 28) * pl->occupied[which];
   const bool bin_first = !as_painted && pl->srt_which < 0 && n <= pl->p.max_objects && pl->n >= 256 &&
-                         n >= 96 * pl->L.nbins && pl->scattered[which] && n == pl->ngp_n[which];
+                         pl->scattered[which] && n == pl->ngp_n[which] && n >= least;
   if (bin_first) {
     RECON_TRY(bin_objects(pl, pos, nullptr, n, (const long long*)offsets, -1, nullptr, nullptr, pl->err + 2, true));
   }

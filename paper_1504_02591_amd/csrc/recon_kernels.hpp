@@ -309,7 +309,8 @@ __device__ __forceinline__ void load_objects(const float* __restrict__ pos, cons
 // chunk's first object; one global atomic per (block, non-empty bin).  Objects whose bin
 // lies outside that window (a chunk crossing realisations) use a direct global atomic.
 // The invalid objects of the block go to errblk[block], which the scan adds up; with ordblk (not null),
-// ordblk[block] says whether the catalogue is in spatial order (count_near: a quarter of the neighbours or more).
+// ordblk[block] says whether the catalogue is in spatial order (count_near: a quarter of the neighbours or more),
+// and *occupied is cleared for the scan, which counts the bricks that hold objects.
 // The block's histogram is also stored in bhist[block][bin], so that the scatter,
 // which splits the catalogue into the same chunks, need not count again.
 // First brick key of the LDS window of the binning block that takes objects [lo, ...): the block's
@@ -364,10 +365,12 @@ __global__ void __launch_bounds__(NT) k_bin_count_lds(const float* __restrict__ 
                                                        long long n, long long chunk,
                                                        const long long* __restrict__ off, int batch, CicGeo g,
                                                        unsigned* __restrict__ counts, int* __restrict__ errblk,
-                                                       unsigned* __restrict__ bhist, int* __restrict__ ordblk) {
+                                                       unsigned* __restrict__ bhist, int* __restrict__ ordblk,
+                                                       int* __restrict__ occupied) {
   __shared__ unsigned hist[kBins];
   __shared__ int bad;
   __shared__ unsigned votes[2];
+  if (ordblk && blockIdx.x == 0 && threadIdx.x == 0) *occupied = 0;
   const long long lo = blockIdx.x * chunk;
   if (lo >= n) {                                         // (whole block)
     if (threadIdx.x == 0) {
@@ -498,7 +501,8 @@ __global__ void __launch_bounds__(256) k_scan_blocks(const unsigned* __restrict_
 // every 256 counts took 20 us at any size.
 __device__ __forceinline__ void scan_run(const unsigned* __restrict__ in, long long n,
                                          const unsigned* __restrict__ bsum, long long run,
-                                         unsigned* __restrict__ out, unsigned* __restrict__ cursor) {
+                                         unsigned* __restrict__ out, unsigned* __restrict__ cursor,
+                                         int* __restrict__ occupied) {
   __shared__ unsigned ws[2][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long long first = run * 256 * kScanItems;
@@ -514,6 +518,14 @@ __device__ __forceinline__ void scan_run(const unsigned* __restrict__ in, long l
   for (int k = 0; k < kScanItems; ++k) {
     v[k] = i0 + k < n ? in[i0 + k] : 0u;
     sum += v[k];
+  }
+  if (occupied) {                                        // (not null: how many of the counts are not zero)
+    int held = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) held += v[k] != 0u;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) held += __shfl_xor(held, o, 64);
+    if (lane == 0 && held) atomicAdd(occupied, held);
   }
   unsigned inc = sum;
 #pragma unroll
@@ -677,7 +689,7 @@ __global__ void __launch_bounds__(256) k_scan_prepare(const unsigned* __restrict
                                                       unsigned long long* __restrict__ grid,
                                                       const int* __restrict__ errblk, int nerr, int* __restrict__ err,
                                                       int fresh, const int* __restrict__ ordblk,
-                                                      int* __restrict__ order) {
+                                                      int* __restrict__ order, int* __restrict__ occupied) {
   if (blockIdx.x == 0) {
     // invalid objects of this deposit: replace the grid's count (new grid) or add to it; and whether most of
     // the binning blocks found the catalogue in spatial order
@@ -697,7 +709,7 @@ __global__ void __launch_bounds__(256) k_scan_prepare(const unsigned* __restrict
       if (ordblk) *order = 2 * inorder > nerr ? 1 : 0;
     }
   }
-  if ((int)blockIdx.x < runs) scan_run(count, nbins, bsum, blockIdx.x, out, cursor);
+  if ((int)blockIdx.x < runs) scan_run(count, nbins, bsum, blockIdx.x, out, cursor, ordblk ? occupied : nullptr);
   else brick_prepare(count, n, mode, (long long)blockIdx.x - runs, valid, grid);
 }
 
@@ -853,12 +865,12 @@ __global__ void __launch_bounds__(256) k_mask_brick(const long long* __restrict_
   if (fl && (w4.x | w4.y | w4.z | w4.w)) *fl = 1;      // every writer stores the same value
 }
 
-constexpr int kOrderAt = 4;
+constexpr int kOrderAt = 4, kOccupiedAt = 6;
 // Per-realisation scalars from the exact totals {W_g, W_r, n_occ}:
 //   alpha = W_g / W_r, 1/rho_bar = N^3 / (W_g 2^-32), mask threshold floor(tau 27 W_r / n_occ);
 // status[b] bit 0: galaxy total is zero, bit 1: random total is zero.  err: invalid objects of the two grids
-// and, from err[kOrderAt], whether their last deposits were in spatial order.  host (pinned host memory, or
-// null): these four, then the status of every realisation.
+// and of their last deposits, from err[kOrderAt] whether in spatial order and from err[kOccupiedAt] the bricks
+// with objects.  host (pinned host memory, or null): these six, then the status of every realisation.
 // One block per realisation: sums the per-tile integer partials (exact, any order), then derives
 // the scalars; tot[b] keeps the totals.
 __global__ void __launch_bounds__(256) k_scalars(const unsigned long long* __restrict__ tpart, int nblk, long long n3,
@@ -907,12 +919,13 @@ __global__ void __launch_bounds__(256) k_scalars(const unsigned long long* __res
     thr[b] = th;
     status[b] = st;
     if (host) {
-      host[4 + b] = (double)st;
+      host[6 + b] = (double)st;
       if (b == 0) {
-        host[0] = (double)err[0];
-        host[1] = (double)err[1];
-        host[2] = (double)err[kOrderAt];
-        host[3] = (double)err[kOrderAt + 1];
+        for (int k = 0; k < 2; ++k) {
+          host[k] = (double)err[k];
+          host[2 + k] = (double)err[kOrderAt + k];
+          host[4 + k] = (double)err[kOccupiedAt + k];
+        }
       }
     }
   }

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
-LEAST = 96 * 16 ** 3                                       # objects from which 256^3 may bin first
+LEAST = 2 ** 17 + 42 * 16 ** 3                             # objects over all of 256^3 from which they are binned
 
 
 def catalogue(n, m, order, seed):
@@ -25,18 +25,22 @@ def catalogue(n, m, order, seed):
         pos[:q.shape[0]] = (q + pos[:q.shape[0]] / k)[:m]
     elif order == "clump":
         pos = pos * 0.02 + 0.31 * box
+    elif order == "eighth":                                # in no order over 8^3 of the 16^3 bricks
+        pos = pos * 0.4999
     return pos.contiguous()
 
 
 @pytest.mark.parametrize("order,m,bins", [("random", LEAST - 1, False), ("random", LEAST, True),
                                           ("random", 500000, True), ("x", 500000, True), ("y", 500000, True),
-                                          ("z", 500000, True), ("lattice", 512000, False), ("clump", 400000, False)])
+                                          ("z", 500000, True), ("lattice", 512000, False), ("clump", 400000, False),
+                                          ("eighth", 2 ** 17 + 14 * 4096 + 28 * 512 - 1, False),
+                                          ("eighth", 2 ** 17 + 14 * 4096 + 28 * 512, True)])
 def test_route_follows_the_order_of_the_catalogue(gpu_lib, order, m, bins):
     from paper_1504_02591_amd import native
     n = 256
     kw = dict(box_len=10.0 * n, observer=(-300.0, 4.0 * n, 7.0 * n), bias=1.5, growth=0.8, smooth_r=10.0)
-    gal, ran = catalogue(n, m, order, 5), catalogue(n, m + 17, "random", 6)
-    direct, plan = native.Plan(n, **kw), native.Plan(n, max_objects=m + 17, **kw)
+    gal, ran = catalogue(n, m, order, 5), catalogue(n, LEAST + m + 17, "random", 6)
+    direct, plan = native.Plan(n, **kw), native.Plan(n, max_objects=LEAST + m + 17, **kw)
     for p in (direct, plan):
         p.paint(native.GAL, gal, ngp=True)
         p.paint(native.RAN, ran, ngp=True)
@@ -92,7 +96,7 @@ def test_route_without_a_deposit_and_without_randoms(gpu_lib):
 
 def test_batch_in_no_order_is_binned(gpu_lib):
     from paper_1504_02591_amd import native
-    n, batch, m = 256, 2, 2 * LEAST + 1001
+    n, batch, m = 256, 2, 2 * LEAST + 1001                 # (twice the bricks, 14 and 28 for each)
     pos = catalogue(n, m, "random", 9)
     off = torch.tensor([0, 300007, m], device=pos.device)
     kw = dict(box_len=10.0 * n, observer=(-300.0, 4.0 * n, 7.0 * n), bias=1.5, growth=0.8, smooth_r=10.0, batch=batch)
